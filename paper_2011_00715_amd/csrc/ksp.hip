@@ -715,10 +715,14 @@ static int grid_n(int64_t n)
 // SpMV into tmp then the update pass for the others (V = double, or float
 // with the handle's FP32 values).
 template <class V>
-int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s)
+int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s, int *np)
 {
     constexpr bool f64 = std::is_same<V, double>::value;
     const dim3 g(A->nblk), t(kBlock);
+    if ((c.b || c.b64) && !cheb_zero_fused(A)) {
+        set_error("internal: Chebyshev start from zero without a SELL layout");
+        return SPK_EINVAL;
+    }
     if (A->kernel == SPK_KERNEL_SELL) {
         const SellView sv{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain, A->sell_len16, A->sell_perm, A->sell_mask};
         // up to one wavefront per slice (no partial sums to keep per block)
@@ -726,26 +730,41 @@ int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s)
         const int n = A->n;
         const V *sval = f64 ? (const V *)A->sell_val : (const V *)A->sell_val32;
         if (!sval) { set_error("internal: no SELL values of this precision"); return SPK_EINVAL; }
-        with_sell_u(A->sell_u, [&](auto uc) {
-            constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2) hipLaunchKernelGGL((k_cheb_sell<V, int16_t, U>), gs, t, 0, s, n, sv, sval, c);
-            else hipLaunchKernelGGL((k_cheb_sell<V, int32_t, U>), gs, t, 0, s, n, sv, sval, c);
-        });
+        auto from_zero = [&](auto *b) {
+            using B = std::remove_const_t<std::remove_pointer_t<decltype(b)>>;
+            with_sell_u(A->sell_u, [&](auto uc) {
+                constexpr int U = decltype(uc)::value;
+                if (A->sell_cw == 2)
+                    hipLaunchKernelGGL((k_cheb_sell_zero<V, B, int16_t, U>), gs, t, 0, s, n, sv, sval, c, b);
+                else hipLaunchKernelGGL((k_cheb_sell_zero<V, B, int32_t, U>), gs, t, 0, s, n, sv, sval, c, b);
+            });
+        };
+        if (c.b64) from_zero(c.b64);
+        else if (c.b) from_zero(c.b);
+        else
+            with_sell_u(A->sell_u, [&](auto uc) {
+                constexpr int U = decltype(uc)::value;
+                if (A->sell_cw == 2) hipLaunchKernelGGL((k_cheb_sell<V, int16_t, U>), gs, t, 0, s, n, sv, sval, c);
+                else hipLaunchKernelGGL((k_cheb_sell<V, int32_t, U>), gs, t, 0, s, n, sv, sval, c);
+            });
+        if (np) *np = (int)gs.x;
     } else if (A->kernel == SPK_KERNEL_STREAM) {
         const V *val = f64 ? (const V *)A->val : (const V *)A->val32;
         hipLaunchKernelGGL((k_cheb_stream<V>), g, t, 0, s, A->n, A->R, A->ntiles, A->nblk, A->rowptr, A->col, val,
                            c);
+        if (np) *np = A->nblk;
     } else {
         const V *val = f64 ? (const V *)A->val : (const V *)A->val32;
         SPK_TRY(launch_spmv<V>(A, val, c.dk, tmp, s, c.gate, c.gate ? kGateInner64 : kGateNone));
         hipLaunchKernelGGL((k_cheb_update<V>), dim3(grid_n(A->n)), t, 0, s, A->n, (const V *)tmp, c);
+        if (np) *np = grid_n(A->n);
     }
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
 
-template int cheb_step<double>(spk_mat *, const ChebStep<double> &, double *, hipStream_t);
-template int cheb_step<float>(spk_mat *, const ChebStep<float> &, float *, hipStream_t);
+template int cheb_step<double>(spk_mat *, const ChebStep<double> &, double *, hipStream_t, int *);
+template int cheb_step<float>(spk_mat *, const ChebStep<float> &, float *, hipStream_t, int *);
 
 }  // namespace spk
 
@@ -785,29 +804,45 @@ int spk_pc_chebyshev(const spk_mat *Ac, const double *b, double *x, double *r_ou
     double *r = r_out ? r_out : w->r;
     double *dbuf[2] = {w->z, w->p};
     double *tmp = w->q;
-    if (x0_nonzero) SPK_TRY(launch_spmv<double>(A, A->val, x, tmp, s, nullptr, kGateNone));
-    hipLaunchKernelGGL((k_cheb_init<double, double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n, b,
-                       x0_nonzero ? (const double *)tmp : nullptr, x, r, dbuf[0], (const double *)A->dinv,
-                       1.0 / theta, (const SysState *)nullptr, (double *)nullptr);
-    SPK_HIP(hipGetLastError());
+    if (steps == 1 && !r_out && !x0_nonzero) {
+        hipLaunchKernelGGL((k_cheb_one<double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n, b,
+                           (const double *)A->dinv, 1.0 / theta, x);
+        SPK_HIP(hipGetLastError());
+        return SPK_OK;
+    }
+    // from zero on SELL the first step forms its own start
+    const bool zero_fused = !x0_nonzero && steps >= 1 && cheb_zero_fused(A);
+    if (!zero_fused) {
+        if (x0_nonzero) SPK_TRY(launch_spmv<double>(A, A->val, x, tmp, s, nullptr, kGateNone));
+        hipLaunchKernelGGL((k_cheb_init<double, double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n, b,
+                           x0_nonzero ? (const double *)tmp : nullptr, x, r, dbuf[0], (const double *)A->dinv,
+                           1.0 / theta, (const SysState *)nullptr, (double *)nullptr);
+        SPK_HIP(hipGetLastError());
+    }
+    if (steps == 1 && !r_out) {
+        hipLaunchKernelGGL((k_cheb_last<double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n,
+                           (const double *)dbuf[0], x, (const SysState *)nullptr);
+        SPK_HIP(hipGetLastError());
+        return SPK_OK;
+    }
     double rho = 1.0 / sigma;
-    for (int k = 0; k < steps; ++k) {
-        const bool last = k == steps - 1;
-        if (last && !r_out) {  // the residual is not wanted: skip the last SpMV
-            hipLaunchKernelGGL((k_cheb_last<double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n,
-                               (const double *)dbuf[k & 1], x, (const SysState *)nullptr);
-            SPK_HIP(hipGetLastError());
-            break;
-        }
+    // without a residual the last step is only x += d: the pass before adds it
+    const int passes = r_out ? steps : steps - 1;
+    for (int k = 0; k < passes; ++k) {
         const double rho_next = 1.0 / (2.0 * sigma - rho);
         ChebStep<double> c;
         c.dk = dbuf[k & 1];
-        c.dn = last ? nullptr : dbuf[(k + 1) & 1];
+        c.dn = k == steps - 1 ? nullptr : dbuf[(k + 1) & 1];
         c.r = r;
         c.x = x;
         c.dinv = A->dinv;
         c.c1 = rho_next * rho;
         c.c2 = 2.0 * rho_next / delta;
+        if (k == 0 && zero_fused) {
+            c.b = b;
+            c.inv_theta = 1.0 / theta;
+        }
+        c.close = !r_out && k == passes - 1;
         SPK_TRY(cheb_step(A, c, tmp, s));
         rho = rho_next;
     }

@@ -193,15 +193,23 @@ static void finish(spk_mg *M, const V *d, const SysState *gate, const CycleIo *i
     if (io->np) *io->np = g;
 }
 
-// Chebyshev steps on level l after the smoother's start (r, d_0 and the
-// level's current x set).  keep_r: the last step also updates r (its result
-// is restricted).  Otherwise the last step only adds d to x: on level 0 it
-// is finish() (z = x + d in FP64, with the CG partial sums), on a coarser
-// level with defer_last it is left to the parent's prolongation (L.dpend).
+// Whether level l's smoother from zero forms its start inside the first step
+// (SELL, at least one step): then no pass writes x, r and d_0 before it.
+static bool zero_fused(const spk_mg *M, int l) { return M->o.smooth_steps >= 1 && cheb_zero_fused(M->lev[l].A); }
+
+// Chebyshev steps on level l.  from_zero: the first step starts from x = 0
+// and the level's right-hand side (zero_fused levels); otherwise the
+// smoother's start has set r, d_0 and the level's current x.  keep_r: the
+// last step also updates r (its result is restricted).  Otherwise the last
+// step only adds d to x, which the step before it does (on level 0 with
+// z = x + d in FP64 and the CG partial sums); a single step leaves it to
+// finish() on level 0 and, with defer_last, to the parent's prolongation
+// (L.dpend) on a coarser level.
 template <class V>
-static int cheb_steps(spk_mg *M, int l, bool keep_r, bool defer_last, const CycleIo *io, const SysState *gate,
-                      hipStream_t s)
+static int cheb_steps(spk_mg *M, int l, bool from_zero, bool keep_r, bool defer_last, const CycleIo *io,
+                      const SysState *gate, hipStream_t s)
 {
+    constexpr bool f32 = std::is_same<V, float>::value;
     MgLevel &L = M->lev[l];
     spk_mat *A = L.A;
     const int n = L.n, steps = M->o.smooth_steps;
@@ -215,26 +223,46 @@ static int cheb_steps(spk_mg *M, int l, bool keep_r, bool defer_last, const Cycl
         SPK_HIP(hipGetLastError());
         return SPK_OK;
     }
+    if (steps == 1 && !keep_r) {
+        if (l == 0) finish<V>(M, (const V *)d[0], gate, io, s);
+        else if (defer_last) L.dpend = d[0];
+        else hipLaunchKernelGGL((k_cheb_last<V>), gn, tb, 0, s, n, (const V *)d[0], x, gate);
+        SPK_HIP(hipGetLastError());
+        return SPK_OK;
+    }
     double rho = 1.0 / sigma;
-    for (int k = 0; k < steps; ++k) {
-        const bool last = k == steps - 1;
-        if (last && !keep_r) {
-            if (l == 0) finish<V>(M, (const V *)d[k & 1], gate, io, s);
-            else if (defer_last) L.dpend = d[k & 1];
-            else hipLaunchKernelGGL((k_cheb_last<V>), gn, tb, 0, s, n, (const V *)d[k & 1], x, gate);
-            break;
-        }
+    const int passes = keep_r ? steps : steps - 1;
+    for (int k = 0; k < passes; ++k) {
         const double rho_next = 1.0 / (2.0 * sigma - rho);
         ChebStep<V> c;
         c.dk = d[k & 1];
-        c.dn = last ? nullptr : d[(k + 1) & 1];
+        c.dn = k == steps - 1 ? nullptr : d[(k + 1) & 1];
         c.r = r;
         c.x = x;
         c.dinv = dinv_of<V>(A);
         c.c1 = (V)(rho_next * rho);
         c.c2 = (V)(2.0 * rho_next / delta);
         c.gate = gate;
-        SPK_TRY(cheb_step<V>(A, c, tmp, s));
+        if (k == 0 && from_zero) {
+            if (f32 && l == 0) {  // the FP64 right-hand side, rounded and kept
+                c.b64 = io->b64;
+                c.bcopy = (V *)L.b;
+            } else {
+                c.b = (const V *)L.b;
+            }
+            c.inv_theta = (V)(1.0 / theta);
+        }
+        int *np = nullptr;
+        if (!keep_r && k == passes - 1) {
+            c.close = true;
+            if (l == 0) {
+                c.z = io->z64;
+                c.rcg = io->rcg;
+                c.part = io->dotpart;
+                np = io->np;
+            }
+        }
+        SPK_TRY(cheb_step<V>(A, c, tmp, s, np));
         rho = rho_next;
     }
     SPK_HIP(hipGetLastError());
@@ -286,8 +314,8 @@ static void launch_resid_prolong(spk_mg *M, int l, const SysState *gate, hipStre
 }
 
 // One cycle on level l: x_l from b_l, or from x_l when x0_nonzero.
-// pre_inited: the parent already formed this level's start from zero
-// together with the restriction.  defer_last: leave the last smoothing
+// pre_inited: the parent set the level up for a start from zero (its start
+// vectors with the restriction, or, where the first step forms them, b).  defer_last: leave the last smoothing
 // step's x += d to the parent's prolongation.  io is set on level 0 only.
 template <class V>
 static int enqueue_cycle(spk_mg *M, int l, bool x0_nonzero, bool pre_inited, bool defer_last,
@@ -311,12 +339,14 @@ static int enqueue_cycle(spk_mg *M, int l, bool x0_nonzero, bool pre_inited, boo
     MgLevel &C = M->lev[l + 1];
     const bool c_direct = l + 1 == M->nlev - 1;
     SPK_TRY(timer_mark(M, l, s));
+    const bool from_zero = !x0_nonzero && zero_fused(M, l);
     if (!pre_inited) {
         if (!x0_nonzero) L.xcur = L.x;
-        SPK_TRY(smoother_start<V>(M, l, x0_nonzero, io, gate, s));
+        if (!from_zero) SPK_TRY(smoother_start<V>(M, l, x0_nonzero, io, gate, s));
     }
-    SPK_TRY(cheb_steps<V>(M, l, true, false, io, gate, s));
-    if (c_direct) {
+    SPK_TRY(cheb_steps<V>(M, l, from_zero, true, false, io, gate, s));
+    if (c_direct || zero_fused(M, l + 1)) {
+        C.xcur = C.x;
         hipLaunchKernelGGL((k_mg_restrict<V>), dim3(grid_n(C.n)), dim3(kBlock), 0, s, L.g, C.g, (const V *)L.r,
                            (V *)C.b, gate);
     } else {  // restriction and the coarse level's start from zero in one pass
@@ -340,7 +370,7 @@ static int enqueue_cycle(spk_mg *M, int l, bool x0_nonzero, bool pre_inited, boo
         launch_resid_prolong<V, 8>(M, l, gate, s);
         SPK_HIP(hipGetLastError());
     }
-    SPK_TRY(cheb_steps<V>(M, l, false, defer_last, io, gate, s));
+    SPK_TRY(cheb_steps<V>(M, l, false, false, defer_last, io, gate, s));
     SPK_TRY(timer_mark(M, l, s));
     return SPK_OK;
 }

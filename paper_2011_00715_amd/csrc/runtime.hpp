@@ -185,8 +185,11 @@ int launch_sliced(const spk_mat *A, const V *x, V *y, hipStream_t s, const SysSt
 template <class V>
 struct ChebStep;
 // One Chebyshev smoothing step on A (fused with its SpMV where the family
-// allows); V = double, or float with the handle's FP32 values.
+// allows); V = double, or float with the handle's FP32 values.  The number
+// of partial sums a closing step writes to c.part goes to *np.
 template <class V>
-int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s);
+int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s, int *np = nullptr);
+// Whether the family's first step may start from zero (ChebStep::b, b64).
+inline bool cheb_zero_fused(const spk_mat *A) { return A->kernel == SPK_KERNEL_SELL; }
 
 }  // namespace spk

@@ -122,3 +122,24 @@ def test_chebyshev_smooths_high_frequencies():
         x, _ = _run(spk, M, b, 4, 0.0, 0.0)
         red = np.linalg.norm(e0 - x) / np.linalg.norm(e0)
         assert (red <= bound * (1 + 1e-9)) if shrinks else (red > 0.9), (red, bound)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 257])
+@pytest.mark.parametrize("offsets", [1, 16, 32])
+def test_chebyshev_start_and_end_folded(n, offsets):
+    """The start from zero and the closing x += d run inside the SELL passes:
+    slice remainders, each offset form, and a first step that also closes."""
+    spk = need_gpu()
+    A = spkgen.banded_spd(n, [1, 7] if n > 7 else [1], seed=n)
+    M = mat_on_gpu(spk, A)
+    spk.mat_set_kernel(M, spk.KERNEL_SELL, offsets)
+    g = oracle.gershgorin(A)
+    b = spkgen.rhs_uniform(n, 3)
+    for steps in (1, 2, 3, 4):
+        xo, ro = oracle.chebyshev(A, b, steps, 0.1 * g, g)
+        for want_r in (False, True):
+            x, r = _run(spk, M, b, steps, 0.1 * g, g, want_r=want_r)
+            _close(x, xo, f"n {n} steps {steps}")
+            if want_r:
+                _close(r, ro, f"n {n} steps {steps} r")
+    M.close()
