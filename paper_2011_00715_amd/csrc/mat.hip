@@ -9,6 +9,8 @@
 #include <mutex>
 
 #include "runtime.hpp"
+#include "scan.hpp"
+#include "sellset.hpp"
 #include "spmv.hpp"
 
 namespace spk {
@@ -584,97 +586,67 @@ static void free_sell(spk_mat *A)
 }
 
 
-// Shared offsets for a SELL-64 layout of rows in matrix order: every slice's
-// rows must have strictly increasing columns and use between them at most
-// kSellSharedMax distinct offsets, and the padding may grow by at most 1/16
-// over the per-lane layout.  On success: slice widths u (the list sizes),
-// the concatenated offset lists and each row's position mask.
-static bool shared_offsets(const std::vector<int32_t> &rp, const std::vector<int32_t> &cl, int n,
-                           std::vector<int32_t> &u, std::vector<int32_t> &offs, std::vector<uint32_t> &mask)
+// The shared-offset layout of rows in matrix order, built on the device:
+// every slice's rows must have strictly increasing columns and use between
+// them at most kSellSharedMax distinct offsets, and the padding may grow by at
+// most 1/16 over the per-lane layout.  *fits says whether it is so; if not,
+// nothing is left behind.  Slice s spans 64 u[s] elements (u: the list
+// lengths); its offsets sit at element sell_ptr[s] / 64 of sell_col (int32).
+static int build_sell_shared(spk_mat *A, hipStream_t s, bool *fits)
 {
-    const int ns = ceil_div(n, kSell);
-    u.assign((size_t)ns, 0);
-    offs.clear();
-    mask.assign((size_t)n, 0u);
-    int64_t shared = 0, lane = 0;
-    std::vector<int32_t> un, tmp;
-    un.reserve(2 * kSellSharedMax);
-    tmp.reserve(2 * kSellSharedMax);
-    for (int k = 0; k < ns; ++k) {
-        const int r0 = k * kSell, r1 = std::min(n, r0 + kSell);
-        un.clear();
-        int mx = 0;
-        for (int r = r0; r < r1; ++r) {
-            const int a = rp[r], e = rp[r + 1];
-            mx = std::max(mx, e - a);
-            // merge the row's sorted offsets into the slice's list
-            tmp.clear();
-            size_t i = 0;
-            for (int j = a; j < e; ++j) {
-                if (j > a && cl[j] <= cl[j - 1]) return false;  // unsorted or repeated column
-                const int32_t o = cl[j] - r;
-                while (i < un.size() && un[i] < o) tmp.push_back(un[i++]);
-                if (i < un.size() && un[i] == o) ++i;
-                tmp.push_back(o);
-            }
-            while (i < un.size()) tmp.push_back(un[i++]);
-            un.swap(tmp);
-            if ((int)un.size() > kSellSharedMax) return false;
-        }
-        for (int r = r0; r < r1; ++r) {
-            uint32_t m = 0;
-            size_t i = 0;
-            for (int j = rp[r]; j < rp[r + 1]; ++j) {
-                const int32_t o = cl[j] - r;
-                while (un[i] != o) ++i;
-                m |= 1u << i;
-            }
-            mask[(size_t)r] = m;
-        }
-        u[(size_t)k] = (int32_t)un.size();
-        offs.insert(offs.end(), un.begin(), un.end());
-        shared += (int64_t)un.size();
-        lane += mx;
-    }
-    return shared * 16 <= lane * 17;
-}
-
-// The shared-offset layout from shared_offsets' result: slice s spans
-// 64 u[s] elements; its offsets sit at element sell_ptr[s] / 64 of sell_col
-// (int32); values are filled on the device from the row masks.
-static int build_sell_shared(spk_mat *A, hipStream_t s, const std::vector<int32_t> &u,
-                             const std::vector<int32_t> &offs, const std::vector<uint32_t> &mask)
-{
+    *fits = false;
     const int n = A->n;
     const int ns = ceil_div(n, kSell);
-    std::vector<int32_t> sp((size_t)ns + 1);
-    int64_t acc = 0;
-    int wmax = 0;
-    for (int k = 0; k < ns; ++k) {
-        sp[k] = (int32_t)acc;
-        acc += (int64_t)kSell * u[(size_t)k];
-        wmax = std::max(wmax, u[(size_t)k]);
-        if (acc > 0x7fffffffLL) { set_error("SELL layout exceeds 2^31 entries"); return SPK_EINVAL; }
+    const int g = scan_blocks(ns);
+    struct Temp {
+        void *p[5] = {};
+        SharedStats *host = nullptr;
+        ~Temp()
+        {
+            for (void *q : p) hipFree(q);
+            hipHostFree(host);
+        }
+    } t;
+    const size_t sizes[5] = {sizeof(SharedStats), sizeof(int32_t) * (size_t)ns,
+                             sizeof(int32_t) * (size_t)ns * kSellSharedMax, sizeof(int32_t) * ((size_t)ns + 1),
+                             sizeof(long long) * ((size_t)g + 1)};
+    for (int i = 0; i < 5; ++i) SPK_HIP(hipMalloc(&t.p[i], sizes[i]));
+    SPK_HIP(hipHostMalloc((void **)&t.host, sizeof(SharedStats), hipHostMallocDefault));
+    SPK_HIP(hipMalloc(&A->sell_mask, sizeof(uint32_t) * (size_t)n));
+    auto *stats = (SharedStats *)t.p[0];
+    auto *width = (int32_t *)t.p[1], *list = (int32_t *)t.p[2], *base = (int32_t *)t.p[3];
+    const int blocks = std::min(ceil_div(ns, kBlock / kWave), kMaxBlocksSingle);
+    *t.host = SharedStats{};
+    SPK_HIP(hipMemcpyAsync(stats, t.host, sizeof(SharedStats), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_shared_lists, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->col, width, list,
+                       A->sell_mask, stats);
+    SPK_HIP(scan_exclusive(ns, width, base, (long long *)t.p[4], s));
+    SPK_HIP(hipMemcpyAsync(t.host, stats, sizeof(SharedStats), hipMemcpyDeviceToHost, s));
+    SPK_HIP(hipStreamSynchronize(s));
+    const SharedStats st = *t.host;
+    const int64_t acc = (int64_t)kSell * (int64_t)st.shared;
+    if (st.bad || st.shared * 16 > st.lane * 17) {
+        hipFree(A->sell_mask);
+        A->sell_mask = nullptr;
+        return SPK_OK;
     }
-    sp[ns] = (int32_t)acc;
+    *fits = true;
+    if (acc > 0x7fffffffLL) { set_error("SELL layout exceeds 2^31 entries"); return SPK_EINVAL; }
     const size_t m = acc > 0 ? (size_t)acc : 1;
-    const size_t no = offs.size() > 0 ? offs.size() : 1;
+    const size_t no = st.shared > 0 ? (size_t)st.shared : 1;
     SPK_HIP(hipMalloc(&A->sell_ptr, sizeof(int32_t) * ((size_t)ns + 1)));
     SPK_HIP(hipMalloc(&A->sell_col, sizeof(int32_t) * no));
-    SPK_HIP(hipMalloc(&A->sell_mask, sizeof(uint32_t) * (size_t)n));
     SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * m));
-    SPK_HIP(hipMemcpyAsync(A->sell_ptr, sp.data(), sizeof(int32_t) * ((size_t)ns + 1), hipMemcpyHostToDevice, s));
-    if (!offs.empty())
-        SPK_HIP(hipMemcpyAsync(A->sell_col, offs.data(), sizeof(int32_t) * offs.size(), hipMemcpyHostToDevice, s));
-    SPK_HIP(hipMemcpyAsync(A->sell_mask, mask.data(), sizeof(uint32_t) * (size_t)n, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_sell_fill_shared, dim3(grid_for(n)), dim3(kBlock), 0, s, n, A->rowptr, A->val,
-                       A->sell_ptr, A->sell_mask, A->sell_val);
+    hipLaunchKernelGGL(k_shared_pack, dim3(ceil_div((int64_t)(ns + 1) * kSellSharedMax, kBlock)), dim3(kBlock), 0, s,
+                       ns, (const int32_t *)base, (const int32_t *)list, A->sell_ptr, (int32_t *)A->sell_col);
+    hipLaunchKernelGGL(k_shared_fill, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
+                       (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val);
     SPK_HIP(hipGetLastError());
     A->sell_cw = 4;
     A->sell_sigma = 0;
-    A->sell_u = pick_sell_u(wmax);
+    A->sell_u = pick_sell_u(st.widest);
     A->sell_nnz = acc;
-    A->sell_idx_bytes = 4 * (int64_t)offs.size() + 4ll * n;
+    A->sell_idx_bytes = 4 * (int64_t)st.shared + 4ll * n;
     // the load policy counts cw bytes per entry plus one byte per row:
     // here no bytes per entry and the rest of the index bytes in the budget
     const int64_t extra = A->sell_idx_bytes - n;
@@ -688,8 +660,7 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, const std::vector<int32_
         SPK_HIP(hipGetLastError());
         A->bytes += 4 * acc;
     }
-    // the host vectors are read by the copies above
-    SPK_HIP(hipStreamSynchronize(s));
+    SPK_HIP(hipStreamSynchronize(s));  // the passes above read the temporaries
     return SPK_OK;
 }
 
@@ -723,20 +694,13 @@ static int setup_sell(spk_mat *A, hipStream_t s, int cw, int sigma = 0)
     }
     free_sell(A);
     const int n = A->n;
-    std::vector<int32_t> rp((size_t)n + 1);
-    SPK_HIP(hipMemcpyAsync(rp.data(), A->rowptr, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToHost, s));
-    SPK_HIP(hipStreamSynchronize(s));
     if (try_shared) {
-        std::vector<int32_t> cl((size_t)A->nnz), u, offs;
-        std::vector<uint32_t> mask;
-        if (A->nnz > 0) {
-            SPK_HIP(hipMemcpyAsync(cl.data(), A->col, sizeof(int32_t) * (size_t)A->nnz, hipMemcpyDeviceToHost, s));
-            SPK_HIP(hipStreamSynchronize(s));
-        }
-        if (shared_offsets(rp, cl, n, u, offs, mask)) {
-            const int rc = build_sell_shared(A, s, u, offs, mask);
-            if (rc == SPK_OK) A->sell_req = req;
-            return rc;
+        bool fits = false;
+        const int rc = build_sell_shared(A, s, &fits);
+        if (rc != SPK_OK) return rc;
+        if (fits) {
+            A->sell_req = req;
+            return SPK_OK;
         }
         if (req == 1) {
             set_error("the rows of a slice use more than %d distinct column offsets (or are unsorted)",
@@ -744,6 +708,9 @@ static int setup_sell(spk_mat *A, hipStream_t s, int cw, int sigma = 0)
             return SPK_EINVAL;
         }
     }
+    std::vector<int32_t> rp((size_t)n + 1);
+    SPK_HIP(hipMemcpyAsync(rp.data(), A->rowptr, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToHost, s));
+    SPK_HIP(hipStreamSynchronize(s));
     std::vector<int32_t> perm;
     if (sigma > 0) {
         perm.resize((size_t)n);

@@ -490,28 +490,6 @@ __global__ void k_sell_fill(int n, const int32_t *__restrict__ rowptr,
     }
 }
 
-// Shared-offset fill: row i (no permutation) has the positions of the set
-// bits of mask[i] in its slice's offset list, in column order; its k-th
-// entry goes to the position of the k-th set bit, the other positions get
-// zeros.
-static __global__ void k_sell_fill_shared(int n, const int32_t *__restrict__ rowptr,
-                                          const double *__restrict__ val, const int32_t *__restrict__ sptr,
-                                          const uint32_t *__restrict__ mask, double *__restrict__ sval)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int s = i / kSell, lane = i % kSell;
-        const int b = sptr[s];
-        const int w = (sptr[s + 1] - b) / kSell;
-        const uint32_t m = mask[i];
-        int k = rowptr[i];
-        for (int j = 0; j < w; ++j) {
-            const bool real = (m >> j) & 1u;
-            sval[(size_t)b + sell_pos(j, w, lane)] = real ? val[k] : 0.0;
-            k += real;
-        }
-    }
-}
-
 // ------------------------------------------------------------------ merge path
 // Split point of diagonal d on the merge of row ends (rowptr[i+1]) with
 // nonzero indices: (i, d - i) with i the number of completed rows.
