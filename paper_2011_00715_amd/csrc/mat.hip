@@ -400,7 +400,7 @@ void update_info(spk_mat *A)
     I.bytes_pcg_iter_f32 = 8 * nz + 4 * (nn + 1) + 44 * nn;
     I.device_bytes = A->bytes + (A->ws ? A->ws->bytes : 0);
     I.zero_diag_rows = S.zero_diag;
-    I.cached_loads = A->kernel == SPK_KERNEL_SELL ? A->sell_plain | A->sell_plain_spmv << 2 : 0;
+    I.cached_loads = A->kernel == SPK_KERNEL_SELL ? (A->sell_plain & 3) | (A->sell_plain_spmv & 3) << 2 : 0;
     double g = 0.0;
     memcpy(&g, &S.gersh_bits, sizeof g);  // bits of a non-negative double
     I.gershgorin = S.zero_diag ? 0.0 : g;
@@ -592,7 +592,8 @@ static void free_sell(spk_mat *A)
 // most 1/16 over the per-lane layout.  *fits says whether it is so; if not,
 // nothing is left behind.  Slice s spans 64 u[s] elements (u: the list
 // lengths); its offsets sit at element sell_ptr[s] / 64 of sell_col (int32).
-static int build_sell_shared(spk_mat *A, hipStream_t s, bool *fits)
+// With may_unify a matrix of one value per slice position stores those only.
+static int build_sell_shared(spk_mat *A, hipStream_t s, bool may_unify, bool *fits)
 {
     *fits = false;
     const int n = A->n;
@@ -624,7 +625,7 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, bool *fits)
     SPK_HIP(hipMemcpyAsync(t.host, stats, sizeof(SharedStats), hipMemcpyDeviceToHost, s));
     SPK_HIP(hipStreamSynchronize(s));
     const SharedStats st = *t.host;
-    const int64_t acc = (int64_t)kSell * (int64_t)st.shared;
+    int64_t acc = (int64_t)kSell * (int64_t)st.shared;
     if (st.bad || st.shared * 16 > st.lane * 17) {
         hipFree(A->sell_mask);
         A->sell_mask = nullptr;
@@ -632,15 +633,34 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, bool *fits)
     }
     *fits = true;
     if (acc > 0x7fffffffLL) { set_error("SELL layout exceeds 2^31 entries"); return SPK_EINVAL; }
-    const size_t m = acc > 0 ? (size_t)acc : 1;
     const size_t no = st.shared > 0 ? (size_t)st.shared : 1;
     SPK_HIP(hipMalloc(&A->sell_ptr, sizeof(int32_t) * ((size_t)ns + 1)));
     SPK_HIP(hipMalloc(&A->sell_col, sizeof(int32_t) * no));
-    SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * m));
     hipLaunchKernelGGL(k_shared_pack, dim3(ceil_div((int64_t)(ns + 1) * kSellSharedMax, kBlock)), dim3(kBlock), 0, s,
                        ns, (const int32_t *)base, (const int32_t *)list, A->sell_ptr, (int32_t *)A->sell_col);
-    hipLaunchKernelGGL(k_shared_fill, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
-                       (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val);
+    bool uniform = false;
+    if (may_unify) {
+        int32_t *varied = &stats->bad;  // zero here
+        SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * no));
+        hipLaunchKernelGGL(k_shared_uniform, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
+                           (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val, varied);
+        SPK_HIP(hipMemcpyAsync(&t.host->bad, varied, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        SPK_HIP(hipStreamSynchronize(s));
+        uniform = t.host->bad == 0;
+        if (!uniform) {
+            hipFree(A->sell_val);
+            A->sell_val = nullptr;
+        }
+    }
+    // the load policy below is that of a value per entry either way
+    const int64_t entries = acc;
+    if (uniform) acc = (int64_t)st.shared;
+    const size_t m = acc > 0 ? (size_t)acc : 1;
+    if (!uniform) {
+        SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * m));
+        hipLaunchKernelGGL(k_shared_fill, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
+                           (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val);
+    }
     SPK_HIP(hipGetLastError());
     A->sell_cw = 4;
     A->sell_sigma = 0;
@@ -650,8 +670,12 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, bool *fits)
     // the load policy counts cw bytes per entry plus one byte per row:
     // here no bytes per entry and the rest of the index bytes in the budget
     const int64_t extra = A->sell_idx_bytes - n;
-    A->sell_plain = A->stream_loads ? 0 : sell_load_policy(acc, 0, ns, n, 6, kIterCacheBudget - extra);
-    A->sell_plain_spmv = A->stream_loads ? 0 : sell_load_policy(acc, 0, ns, n, 2, kSpmvCacheBudget - extra);
+    A->sell_plain = A->stream_loads ? 0 : sell_load_policy(entries, 0, ns, n, 6, kIterCacheBudget - extra);
+    A->sell_plain_spmv = A->stream_loads ? 0 : sell_load_policy(entries, 0, ns, n, 2, kSpmvCacheBudget - extra);
+    if (uniform) {
+        A->sell_plain |= kSellUniform;
+        A->sell_plain_spmv |= kSellUniform;
+    }
     A->bytes += 4 * ((int64_t)ns + 1) + 8 * acc + A->sell_idx_bytes;
     if (A->val32) {
         SPK_HIP(hipMalloc(&A->sell_val32, sizeof(float) * m));
@@ -696,7 +720,7 @@ static int setup_sell(spk_mat *A, hipStream_t s, int cw, int sigma = 0)
     const int n = A->n;
     if (try_shared) {
         bool fits = false;
-        const int rc = build_sell_shared(A, s, &fits);
+        const int rc = build_sell_shared(A, s, req == 0, &fits);
         if (rc != SPK_OK) return rc;
         if (fits) {
             A->sell_req = req;

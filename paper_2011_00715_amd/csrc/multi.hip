@@ -72,7 +72,8 @@ static MultiDesc multi_desc(const spk_mat *A, int K)
     d.col = A->col;
     d.val = A->val;
     d.dinv = A->dinv;
-    d.sv = SellView{A->sell_ptr, A->sell_col, A->sell_len, 0, nullptr, nullptr, A->sell_mask};
+    d.sv = SellView{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain & kSellUniform, nullptr, nullptr,
+                    A->sell_mask};
     d.sell_val = A->sell_val;
     return d;
 }

@@ -96,13 +96,14 @@ constexpr int kOneRoundPairs = 3;
 
 //
 // SH: shared offsets (see the SELL-64 notes): offsets from the slice's list,
-// rlen the row's position mask, gathered rows clamped into [0, n).
+// rlen the row's position mask, gathered rows clamped into [0, n).  UNI: one
+// value per slice position, from the slice's list too.
 //
 // pdiag (the pipelined walk only; null otherwise): where to keep the row's
 // own gathered X row, the gather of its diagonal entry (offset 0; the
 // solve's matrices have one in every row), so that the caller need not read
 // it again.
-template <class CI, int K, bool kOneRound = false, bool SH = false>
+template <class CI, int K, bool kOneRound = false, bool SH = false, bool UNI = false>
 __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double *__restrict__ val,
                                                const double *__restrict__ X, int32_t b, int slen,
                                                int rlen, int lane, int row, int n, double acc[K],
@@ -113,9 +114,20 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
     using CP = typename Pair2<CI>::type;
     using VP = typename Pair2<double>::type;
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
-    const int32_t *__restrict__ ou =
-        reinterpret_cast<const int32_t *>(sv.col) + (__builtin_amdgcn_readfirstlane(b) >> 6);
+    const int32_t first = __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
+    const int32_t *__restrict__ ou = reinterpret_cast<const int32_t *>(sv.col) + first;
+    const double *__restrict__ uv = val + first;
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
+    auto values = [&](int p) -> VP {
+        if constexpr (UNI) {
+            VP a;
+            a.x = uv[2 * p];
+            a.y = uv[2 * p + 1];
+            return a;
+        } else {
+            return ld_stream(vp + (size_t)p * kSell);
+        }
+    };
     auto offsets = [&](int p) -> CP {
         if constexpr (SH) {
             CP c;
@@ -138,7 +150,8 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
         const size_t t = (size_t)b + (size_t)np * (2 * kSell) + lane;
         if constexpr (SH) ct = ou[2 * np];
         else ct = ld_stream(reinterpret_cast<const CI *>(sv.col) + t);
-        at = ld_stream(val + t);
+        if constexpr (UNI) at = uv[2 * np];
+        else at = ld_stream(val + t);
     }
 #pragma unroll
     for (int q = 0; q < K; ++q) acc[q] = 0.0;
@@ -173,7 +186,7 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
             for (int u = 0; u < P1; ++u) {
                 const int p = u < np ? u : np - 1;
                 c[u] = offsets(p);
-                a[u] = ld_stream(vp + (size_t)p * kSell);
+                a[u] = values(p);
             }
         double xv[2 * P1 + 1][K];
 #pragma unroll
@@ -199,7 +212,7 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
         for (int u = 0; u < PM; ++u) {
             const int p = u < np ? u : np - 1;
             c[u] = offsets(p);
-            a[u] = ld_stream(vp + (size_t)p * kSell);
+            a[u] = values(p);
         }
         double xa[2][K], xb[2][K];
         gather((int)c[0].x, xa[0]);
@@ -230,7 +243,7 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
         // wide slices (or K = 16): one pair per round
         for (int p = 0; p < np; ++p) {
             const CP c = offsets(p);
-            const VP a = ld_stream(vp + (size_t)p * kSell);
+            const VP a = values(p);
             double x0[K], x1[K];
             gather((int)c.x, x0);
             gather((int)c.y, x1);
@@ -260,7 +273,7 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
 // products are 8K contiguous bytes, so storing them from the lanes directly
 // writes 64 partial segments per instruction; the flat pass writes whole
 // ones (K = 8: 118 -> 99 us on the 7-point 128^3 product).
-template <class CI, int K, bool kOneRound, bool SH, class Flat>
+template <class CI, int K, bool kOneRound, bool SH, bool UNI, class Flat>
 __device__ __forceinline__ void multi_sell_walk(const MultiDesc &d, int l, const double *__restrict__ X,
                                                 double *stage, double *pstage, Flat &&flat)
 {
@@ -272,7 +285,7 @@ __device__ __forceinline__ void multi_sell_walk(const MultiDesc &d, int l, const
         if (row < d.n) {
             double acc[K];
             const int rl = SH ? (int)d.sv.mask[row] : (int)d.sv.len[row];
-            sell_row_multi<CI, K, kOneRound, SH>(d.sv, d.sell_val, X, b, (e - b) / kSell, rl, lane, row, d.n,
+            sell_row_multi<CI, K, kOneRound, SH, UNI>(d.sv, d.sell_val, X, b, (e - b) / kSell, rl, lane, row, d.n,
                                                  acc, pstage ? pstage + lane * K : nullptr);
 #pragma unroll
             for (int q = 0; q < K; ++q) stage[lane * K + q] = acc[q];
@@ -293,11 +306,12 @@ __device__ __forceinline__ void multi_sell_staged(const MultiDesc &d, int l, con
 {
     if constexpr (std::is_same<CI, int32_t>::value) {
         if (d.sv.mask) {
-            multi_sell_walk<CI, K, kOneRound, true>(d, l, X, stage, pstage, flat);
+            if (d.sv.plain & kSellUniform) multi_sell_walk<CI, K, kOneRound, true, true>(d, l, X, stage, pstage, flat);
+            else multi_sell_walk<CI, K, kOneRound, true, false>(d, l, X, stage, pstage, flat);
             return;
         }
     }
-    multi_sell_walk<CI, K, kOneRound, false>(d, l, X, stage, pstage, flat);
+    multi_sell_walk<CI, K, kOneRound, false, false>(d, l, X, stage, pstage, flat);
 }
 
 // Row walk of block l (of nblk) of a multi kernel: SELL slices in
@@ -317,8 +331,12 @@ __device__ __forceinline__ void multi_rows(const MultiDesc &d, int l, int j, con
             if (row < d.n) {
                 if constexpr (std::is_same<CI, int32_t>::value) {
                     if (d.sv.mask) {
-                        sell_row_multi<CI, K, false, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
-                                                           (int)d.sv.mask[row], lane, row, d.n, acc);
+                        if (d.sv.plain & kSellUniform)
+                            sell_row_multi<CI, K, false, true, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
+                                                                     (int)d.sv.mask[row], lane, row, d.n, acc);
+                        else
+                            sell_row_multi<CI, K, false, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
+                                                               (int)d.sv.mask[row], lane, row, d.n, acc);
                         fn(row, acc);
                         continue;
                     }

@@ -167,4 +167,41 @@ static __global__ __launch_bounds__(kBlock) void k_shared_fill(int n, const int3
     }
 }
 
+// One value per slice position: uval takes, at each offset's index, the value
+// of the position's first row; *varied is set when some row's differs (in its
+// bits).  Every slice position has a row, so every element is written.
+static __global__ __launch_bounds__(kBlock) void k_shared_uniform(int n, const int32_t *__restrict__ rowptr,
+                                                                  const double *__restrict__ val,
+                                                                  const int32_t *__restrict__ sptr,
+                                                                  const uint32_t *__restrict__ mask,
+                                                                  double *__restrict__ uval, int32_t *varied)
+{
+    __shared__ double stage[kBlock / kWave][kSharedCap];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int ns = (n + kSell - 1) / kSell;
+    double *sc = stage[w];
+    for (int s = blockIdx.x * (kBlock / kWave) + w; s < ns; s += gridDim.x * (kBlock / kWave)) {
+        if (__hip_atomic_load(varied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+        const int row = s * kSell + lane;
+        const int base = rowptr[s * kSell], total = rowptr[min(n, (s + 1) * kSell)] - base;
+        const int first = sptr[s] / kSell, slen = sptr[s + 1] / kSell - first;
+        const uint32_t m = row < n ? mask[row] : 0u;
+        int k = rowptr[min(row, n)] - base;
+        wave_lds_sync();
+        for (int i = lane; i < total; i += kWave) sc[i] = val[base + i];
+        wave_lds_sync();
+        bool differs = false;
+        for (int j = 0; j < slen; ++j) {
+            const bool has = (m >> j) & 1u;
+            const long long v = has ? __double_as_longlong(sc[k++]) : 0;
+            const int holder = __ffsll((unsigned long long)__ballot(has)) - 1;
+            const long long v0 = __shfl(v, holder, kWave);
+            differs |= has && v != v0;
+            if (lane == 0) uval[first + j] = __longlong_as_double(v0);
+        }
+        if (__any(differs) && lane == 0)
+            __hip_atomic_store(varied, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 }  // namespace spk

@@ -241,7 +241,7 @@ struct SellView {
     const void *col;       // int16 or int32 row-relative column offsets (per entry, or
                            // per slice position with shared offsets)
     const uint8_t *len;    // row lengths (rows of at most 255 entries), or null
-    int plain;             // load policy of offsets and values, see kSellPlain64/32
+    int plain;             // load policy of offsets and values, see kSellPlain64/32; kSellUniform
     const uint16_t *len16; // row lengths when some row has more than 255 entries
     const int32_t *perm;   // SELL-C-sigma: matrix row of each sorted position, or null
     const uint32_t *mask;  // shared offsets: per-row position masks (col then holds
@@ -254,6 +254,9 @@ struct SellView {
 // one is streamed with nontemporal loads, which keep it from evicting the
 // vectors that do fit.  One bit per value precision (FP64 / FP32 kernels).
 constexpr int kSellPlain64 = 1, kSellPlain32 = 2;
+// Third bit: one value per slice position (val then holds one element per
+// offset, at the offset's index).
+constexpr int kSellUniform = 4;
 
 template <bool NT, class T>
 __device__ __forceinline__ T sell_ld(const T *p)
@@ -276,16 +279,19 @@ __device__ __forceinline__ T sell_ld(const T *p)
 // SH (shared offsets, CI = int32): the offsets come from the slice's list
 // (wave-uniform, scalar loads), rlen is the row's position mask, and gathered
 // columns are clamped into [0, n) for the positions the row does not use.
-template <class V, class CI, int UP, bool NT, bool SH, class G>
+// UNI (with SH): the values come from the slice's list too.
+template <class V, class CI, int UP, bool NT, bool SH, bool UNI, class G>
 __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ val, G &&gat,
                                       int32_t b, int slen, int rlen, int lane, int row, int n)
 {
     static_assert(!SH || std::is_same<CI, int32_t>::value, "shared offsets are int32");
+    static_assert(!UNI || SH, "one value per position needs shared offsets");
     using CP = typename Pair2<CI>::type;
     using VP = typename Pair2<V>::type;
+    const int32_t first = __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
-    const int32_t *__restrict__ ou =
-        reinterpret_cast<const int32_t *>(sv.col) + (__builtin_amdgcn_readfirstlane(b) >> 6);
+    const int32_t *__restrict__ ou = reinterpret_cast<const int32_t *>(sv.col) + first;
+    const V *__restrict__ uv = val + first;
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
     auto offsets = [&](int p) -> CP {
         if constexpr (SH) {
@@ -295,6 +301,16 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
             return c;
         } else {
             return sell_ld<NT>(cp + (size_t)p * kSell);
+        }
+    };
+    auto values = [&](int p) -> VP {
+        if constexpr (UNI) {
+            VP a;
+            a.x = uv[2 * p];
+            a.y = uv[2 * p + 1];
+            return a;
+        } else {
+            return sell_ld<NT>(vp + (size_t)p * kSell);
         }
     };
     auto column = [&](int off) -> int {
@@ -315,7 +331,8 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
         const size_t t = (size_t)b + (size_t)np * (2 * kSell) + lane;
         if constexpr (SH) ct = ou[2 * np];
         else ct = sell_ld<NT>(reinterpret_cast<const CI *>(sv.col) + t);
-        at = sell_ld<NT>(val + t);
+        if constexpr (UNI) at = uv[2 * np];
+        else at = sell_ld<NT>(val + t);
     }
     V acc = V(0);
     for (int p0 = 0; p0 < np; p0 += UP) {
@@ -325,7 +342,7 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
         for (int u = 0; u < UP; ++u) {
             const int p = p0 + u < np ? p0 + u : np - 1;
             c[u] = offsets(p);
-            a[u] = sell_ld<NT>(vp + (size_t)p * kSell);
+            a[u] = values(p);
         }
         V xv[2 * UP];
 #pragma unroll
@@ -356,7 +373,7 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
 // flight at any moment are adjacent in memory (one DRAM stream front rather
 // than one per block).  The first slice's header is loaded before go() is
 // asked whether to run (go holds no barrier: waves may own different counts).
-template <class V, class CI, int U, bool NT, bool SH, class G, class Go, class Fn>
+template <class V, class CI, int U, bool NT, bool SH, bool UNI, class G, class Go, class Fn>
 __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const SellView &sv,
                                                 const V *__restrict__ val, G &&gat, Go &&go, Fn &&fn)
 {
@@ -380,7 +397,7 @@ __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const 
     if (!go()) return;
     while (s < ns) {
         const int slen = (e - b) / kSell;
-        if (s * kSell + lane < n) fn(row, sell_row<V, CI, U, NT, SH>(sv, val, gat, b, slen, rlen, lane, row, n));
+        if (s * kSell + lane < n) fn(row, sell_row<V, CI, U, NT, SH, UNI>(sv, val, gat, b, slen, rlen, lane, row, n));
         s += stride;
         if (s >= ns) break;
         b = sv.ptr[s];
@@ -399,13 +416,14 @@ __device__ __forceinline__ void sell_slices_g(int n, int s, int stride, const Se
     const bool plain = sv.plain & (sizeof(V) == 4 ? kSellPlain32 : kSellPlain64);
     if constexpr (std::is_same<CI, int32_t>::value) {
         if (sv.mask) {
-            if (plain) sell_slices_run<V, CI, U, false, true>(n, s, stride, sv, val, gat, go, fn);
-            else sell_slices_run<V, CI, U, true, true>(n, s, stride, sv, val, gat, go, fn);
+            if (sv.plain & kSellUniform) sell_slices_run<V, CI, U, false, true, true>(n, s, stride, sv, val, gat, go, fn);
+            else if (plain) sell_slices_run<V, CI, U, false, true, false>(n, s, stride, sv, val, gat, go, fn);
+            else sell_slices_run<V, CI, U, true, true, false>(n, s, stride, sv, val, gat, go, fn);
             return;
         }
     }
-    if (plain) sell_slices_run<V, CI, U, false, false>(n, s, stride, sv, val, gat, go, fn);
-    else sell_slices_run<V, CI, U, true, false>(n, s, stride, sv, val, gat, go, fn);
+    if (plain) sell_slices_run<V, CI, U, false, false, false>(n, s, stride, sv, val, gat, go, fn);
+    else sell_slices_run<V, CI, U, true, false, false>(n, s, stride, sv, val, gat, go, fn);
 }
 
 // The plain product: the gathered operand is x.

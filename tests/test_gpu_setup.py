@@ -75,3 +75,83 @@ def test_shared_lists_refused(where, what):
     spk.mat_mult(M, to_dev(x), y)
     assert np.array_equal(y.cpu().numpy(), oracle.spmv(B, x))
     M.close()
+
+
+def _outputs(spk, M, n):
+    """Products (FP64, FP32, eight columns), smoother and solves of a handle."""
+    import torch
+
+    x = to_dev(spkgen.rhs_uniform(n, 2))
+    y, y32 = torch.full_like(x, np.nan), torch.full_like(x.float(), np.nan)
+    spk.mat_mult(M, x, y)
+    spk.mat_mult_f32(M, x.float(), y32)
+    X = torch.stack([x, x + 1, 2 * x, x * x, -x, x - 3, x / 3, x * 5], dim=1).contiguous()
+    Y = torch.full_like(X, np.nan)
+    spk.mat_mult_multi(M, X, Y)
+    out = [y, y32, Y]
+    if M.info.zero_diag_rows == 0:
+        s = torch.full_like(x, np.nan)
+        spk.pc_chebyshev(M, x, s, 3, 0.2, 2.0)
+        out.append(s)
+        for kw in ({}, {"precision": spk.PREC_MIXED}, {"single_reduction": 1}):
+            z = torch.zeros_like(x)
+            r = spk.ksp_solve(M, x, z, spk.ksp_opts(**kw))
+            assert r.reason == spk.CONVERGED_RTOL
+            out.append(z)
+        Z = torch.zeros_like(X[:, :4]).contiguous()
+        spk.ksp_solve_multi(M, X[:, :4].contiguous(), Z)
+        out.append(Z)
+    return [o.cpu().numpy() for o in out]
+
+
+@pytest.mark.parametrize("case", ["lap2d_61", "lap3d_23", "box_13", "grid_1d_130", "empty_rows"])
+def test_uniform_values_same_bits(case):
+    """A matrix of one value per slice position stores those only (automatic
+    choice); every kernel family of the layout gives the bits of a value per
+    entry."""
+    spk = need_gpu()
+    A = {"lap2d_61": lambda: spkgen.laplace2d5(61, 0.3), "lap3d_23": lambda: spkgen.laplace3d7(23),
+         "box_13": lambda: spkgen.diffusion3d27_lognormal(13, seed=1),
+         "grid_1d_130": lambda: spkgen.laplace_grid((130,), 0.5),
+         "empty_rows": lambda: _band(200, 5, drop={3, 64, 65, 199})}[case]()
+    if case == "box_13":  # 27 points, constant coefficients
+        r = np.repeat(np.arange(A.n), np.diff(A.rowptr))
+        A = spkgen.CSR(A.n, A.rowptr, A.col, np.where(A.col == r, 27.0, -1.0 + 0.25 * (np.abs(A.col - r) == 1)))
+    if case == "empty_rows":
+        A = spkgen.CSR(A.n, A.rowptr, A.col, np.repeat(np.arange(A.n), np.diff(A.rowptr)) * 0 + 1.5)
+    widths, nlist = _shared_layout(A)
+    res = []
+    for param in (0, spk.SELL_SHARED, 16):
+        M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, param)
+        assert M.info.stored_nnz == (nlist if param == 0 else 64 * sum(widths)) or param == 16
+        res.append(_outputs(spk, M, A.n))
+        M.close()
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("entry", ["first", "last", "sign_of_zero"])
+def test_uniform_values_need_every_entry(entry):
+    """One entry that differs, in its sign bit alone too, keeps a value per entry."""
+    spk = need_gpu()
+    A = spkgen.laplace2d5(37)
+    val = A.val.copy()
+    k = {"first": 0, "last": A.nnz - 1, "sign_of_zero": 700}[entry]
+    if entry == "sign_of_zero":
+        val[A.val < 0] = 0.0
+        k = int(np.nonzero(A.val < 0)[0][k])
+        val[k] = -0.0
+    else:
+        val[k] += 2.0 ** -40
+    B = spkgen.CSR(A.n, A.rowptr, A.col, val)
+    widths, _ = _shared_layout(B)
+    M = mat_on_gpu(spk, B)
+    assert M.info.lanes == 0 and M.info.stored_nnz == 64 * sum(widths)
+    x = spkgen.rhs_uniform(A.n, 2)
+    y = to_dev(np.full(A.n, np.nan))
+    spk.mat_mult(M, to_dev(x), y)
+    yo = oracle.spmv(B, x)
+    assert np.all(np.abs(y.cpu().numpy() - yo) <= 8 * 2.0 ** -53 * oracle.spmv_abs(B, x))
+    M.close()
