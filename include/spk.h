@@ -176,8 +176,8 @@ typedef struct {
                                        4 n (masks) + 16 n) */
     int64_t format_bytes_spmv_f32;  /* same for FP32 values and vectors */
     int64_t stored_nnz;             /* values the kernel reads, padding included
-                                       (one per offset-list entry where every
-                                       slice position holds one number) */
+                                       (one per offset where the entries of
+                                       an offset are all the same number) */
     double gershgorin;              /* max_i sum_j |a_ij| / |a_ii|: a bound on the
                                        spectrum of D^-1 A (0 with a zero diagonal) */
     int32_t sell_sigma;             /* SPK_KERNEL_SELL_SIGMA: the window (rows) */
@@ -219,9 +219,9 @@ int spk_mat_create_csr(int32_t n, int64_t nnz, const int32_t *rowptr,
  * columns, every slice's rows use at most 32 distinct offsets and the
  * stored entries grow by at most 1/16) or 0 (automatic: shared when the
  * matrix qualifies, which stencils do, else 16 when the offsets fit, else
- * 32; a shared layout whose every list position holds one and the same
- * number in all rows that use it, as constant coefficients give, keeps that
- * number instead of a value per entry), the window sigma for SELL_SIGMA
+ * 32; a matrix of at most 27 distinct offsets whose entries of one offset
+ * are all the same number, as constant coefficients give, keeps one list of
+ * offsets and numbers instead of a value per entry), the window sigma for SELL_SIGMA
  * (a multiple of 64; 0 = 4096; offsets per lane, 16 bits when they fit,
  * else 32), for SLICED 0
  * (automatic: the merge path over the slices when 8n + nnz < 2^31, else

@@ -52,34 +52,49 @@ __device__ __forceinline__ bool cheb_go(const SysState *gate)
     return !gate || gate_open(gate, kGateInner64);
 }
 
-// Row i of a step whose d_k, x and r on entry are di, xi, ri and whose
-// product is y.  Returns its term of rcg . z (0 when none is wanted).
+// A row's own operands of a step: d_k, x, r, D^-1, and rcg where a closing
+// step sums rcg . z.
 template <class V>
-__device__ __forceinline__ double cheb_row(const ChebStep<V> &c, int i, V y, V di, V xi, V ri)
+struct ChebOwn {
+    V d, x, r, dinv;
+    double rcg;
+};
+
+template <class V>
+__device__ __forceinline__ ChebOwn<V> cheb_own(const ChebStep<V> &c, int i)
+{
+    return ChebOwn<V>{c.dk[i], c.x[i], c.r[i], c.dinv[i], c.part ? c.rcg[i] : 0.0};
+}
+
+// Row i of a step whose product is y.  Returns its term of rcg . z (0 when
+// none is wanted).
+template <class V>
+__device__ __forceinline__ double cheb_row(const ChebStep<V> &c, int i, V y, const ChebOwn<V> &o)
 {
 #pragma clang fp contract(off)  // x = (x + d_k) + d_{k+1}, each sum rounded
-    const V r1 = ri - y;
-    const V x1 = xi + di;
+    const V r1 = o.r - y;
+    const V x1 = o.x + o.d;
+    const V dn = fma(c.c1, o.d, c.c2 * (o.dinv * r1));
     if (c.close) {
-        const V x2 = x1 + fma(c.c1, di, c.c2 * (c.dinv[i] * r1));
+        const V x2 = x1 + dn;
         if (!c.z) {
             c.x[i] = x2;
             return 0.0;
         }
         const double zi = (double)x2;
         c.z[i] = zi;
-        return c.part ? c.rcg[i] * zi : 0.0;
+        return o.rcg * zi;
     }
     c.r[i] = r1;
     c.x[i] = x1;
-    if (c.dn) c.dn[i] = fma(c.c1, di, c.c2 * (c.dinv[i] * r1));
+    if (c.dn) c.dn[i] = dn;
     return 0.0;
 }
 
 template <class V>
 __device__ __forceinline__ double cheb_row(const ChebStep<V> &c, int i, V y)
 {
-    return cheb_row(c, i, y, c.dk[i], c.x[i], c.r[i]);
+    return cheb_row(c, i, y, cheb_own(c, i));
 }
 
 // Per-block sums of a closing step's rcg . z terms.
@@ -98,29 +113,48 @@ __global__ __launch_bounds__(kBlock) void k_cheb_sell(int n, SellView sv, const 
     bool run = true;
     sell_slices<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
                           gridDim.x * (kBlock / kWave), sv, val, c.dk, [&] { return run = cheb_go(c.gate); },
-                          [&](int i, V y) { acc += cheb_row(c, i, y); });
+                          [&](int i) { return cheb_own(c, i); },
+                          [&](int i, V y, const ChebOwn<V> &o) { acc += cheb_row(c, i, y, o); });
     if (c.part && run) cheb_part(acc, c.part);
 }
 
-// The first step from zero: d_0 = (D^-1 b) / theta is formed at every gather.
+// d_0 = (D^-1 b) / theta of a start from zero.
+template <class V, class B>
+struct GatherD0 {
+    const V *__restrict__ dinv;
+    const B *__restrict__ b;
+    V it;
+    struct Raw {
+        V dinv;
+        B b;
+    };
+    __device__ Raw at(int j) const { return Raw{dinv[j], b[j]}; }
+    __device__ Raw sh(int64_t base, unsigned l) const { return Raw{(dinv + base)[l], (b + base)[l]}; }
+    __device__ V of(const Raw &r) const
+    {
+#pragma clang fp contract(off)
+        return r.dinv * (V)r.b * it;
+    }
+};
+
+// The first step from zero: d_0 is formed at every gather.
 template <class V, class B, class CI, int U>
 __global__ __launch_bounds__(kBlock) void k_cheb_sell_zero(int n, SellView sv, const V *__restrict__ val,
                                                            ChebStep<V> c, const B *__restrict__ b)
 {
-    const V *__restrict__ dinv = c.dinv;
-    const V it = c.inv_theta;
-    auto d0 = [=](int j) {
-#pragma clang fp contract(off)
-        return dinv[j] * (V)b[j] * it;
-    };
+    const GatherD0<V, B> d0{c.dinv, b, c.inv_theta};
     double acc = 0.0;
     bool run = true;
     sell_slices_g<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
                             gridDim.x * (kBlock / kWave), sv, val, d0, [&] { return run = cheb_go(c.gate); },
-                            [&](int i, V y) {
-                                const V bi = (V)b[i];
-                                if (c.bcopy) c.bcopy[i] = bi;
-                                acc += cheb_row(c, i, y, d0(i), V(0), bi);
+                            [&](int i) {
+#pragma clang fp contract(off)
+                                const V bi = (V)b[i], di = c.dinv[i];
+                                return ChebOwn<V>{di * bi * c.inv_theta, V(0), bi, di, c.part ? c.rcg[i] : 0.0};
+                            },
+                            [&](int i, V y, const ChebOwn<V> &o) {
+                                if (c.bcopy) c.bcopy[i] = o.r;
+                                acc += cheb_row(c, i, y, o);
                             });
     if (c.part && run) cheb_part(acc, c.part);
 }

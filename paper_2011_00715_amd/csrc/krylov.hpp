@@ -303,8 +303,8 @@ __global__ __launch_bounds__(kBlock) void k_resid_sell(B a)
     const SellView sv{d.sell_ptr, d.sell_col, d.sell_len, d.sell_plain, d.sell_len16, d.sell_perm, d.sell_mask};
     double rr = 0.0, bb = 0.0;
     sell_slices<double, CI, U>(d.n, sell_first(local_block(a)), d.nblk * (kBlock / kWave), sv,
-                               d.sell_val, d.x, [] { return true; }, [&](int i, double y) {
-        const double bi = b[i];
+                               d.sell_val, d.x, [] { return true; }, [b](int i) { return b[i]; },
+                               [&](int i, double y, double bi) {
         const double ri = bi - y;
         r[i] = ri;
         rr = fma(ri, ri, rr);
@@ -595,9 +595,10 @@ __global__ __launch_bounds__(kBlock) void k_pcg_spmv_sell(B a)
     const bool run = gate_ok(g, Vecs<V>::gate);
     sell_slices<V, CI, U>(
         d.n, sell_first(local_block(a)), d.nblk * (kBlock / kWave), sv, val, p, [&] { return run; },
-        [&](int i, V y) {
+        [p](int i) { return p[i]; },
+        [&](int i, V y, V pi) {
             q[i] = y;
-            acc = fma(y, p[i], acc);
+            acc = fma(y, pi, acc);
         });
     if (!run) return;
     const double blk = block_sum((double)acc, red);
@@ -622,9 +623,10 @@ __global__ __launch_bounds__(kBlock) void k_pcg_spmv_sell_wide(One a, double *__
     const bool run = gate_ok(g, Vecs<V>::gate);
     sell_slices<V, CI, U>(
         d.n, sell_first((int)blockIdx.x), (int)gridDim.x * (kBlock / kWave), sv, val, p, [&] { return run; },
-        [&](int i, V y) {
+        [p](int i) { return p[i]; },
+        [&](int i, V y, V pi) {
             q[i] = y;
-            acc = fma(y, p[i], acc);
+            acc = fma(y, pi, acc);
         });
     if (!run) return;
     const double blk = block_sum((double)acc, red);
@@ -909,6 +911,25 @@ __global__ __launch_bounds__(kBlock) void k_pcg_px(B a)
         });
 }
 
+// The direction the product of F gathers: p' = z + beta p (z alone where a
+// sequence starts afresh).
+template <class V, bool kStart>
+struct GatherP {
+    const V *__restrict__ z;
+    const V *__restrict__ p;
+    V beta;
+    bool fresh;
+    struct Raw {
+        V z, p;
+    };
+    __device__ Raw at(int j) const { return Raw{z[j], kStart && fresh ? V(0) : p[j]}; }
+    __device__ Raw sh(int64_t base, unsigned l) const
+    {
+        return Raw{(z + base)[l], kStart && fresh ? V(0) : (p + base)[l]};
+    }
+    __device__ V of(const Raw &r) const { return kStart && fresh ? r.z : fma(beta, r.p, r.z); }
+};
+
 // F: C of iteration k fused with A of iteration k + 1, for systems with the
 // SELL product on the persistent grid and a second p buffer (p2).  An
 // iteration is then two kernels (B, F) and moves 88n vector bytes, the
@@ -974,13 +995,21 @@ __global__ __launch_bounds__(kBlock) void k_pcg_fused_sell(B a)
         rows_unrolled(rb, re, [&](int i) { x[i] = fma(alpha, pold[i], x[i]); });
         return;
     }
-    auto pn = [&](int c) -> V { return fresh ? z[c] : fma(beta, pold[c], z[c]); };
+    const GatherP<V, kStart> pn{z, pold, beta, fresh};
     const SellView sv{d.sell_ptr, d.sell_col, d.sell_len, d.sell_plain, d.sell_len16, d.sell_perm, d.sell_mask};
     V acc = V(0);
     sell_slices_g<V, CI, U>(d.n, sell_first(local_block(a)), d.nblk * (kBlock / kWave), sv, sell_vals<V>(d), pn,
-                            [] { return true; }, [&](int i, V y) {
-                                const V pi = pn(i);
-                                if (!kStart) x[i] = fma(alpha, pold[i], x[i]);
+                            [] { return true; },
+                            [&](int i) {
+                                Trio<V> o{};
+                                if (!kStart || !fresh) o.a = pold[i];
+                                o.b = z[i];
+                                if (!kStart) o.c = x[i];
+                                return o;
+                            },
+                            [&](int i, V y, const Trio<V> &o) {
+                                const V pi = kStart && fresh ? o.b : fma(beta, o.a, o.b);
+                                if (!kStart) x[i] = fma(alpha, o.a, o.c);
                                 pnew[i] = pi;
                                 q[i] = y;
                                 acc = fma(y, pi, acc);

@@ -225,15 +225,11 @@ static int launch_resid(spk_mat *A, Workspace *w, int purpose, bool gated, hipSt
         if (gated) hipLaunchKernelGGL((k_resid_stream<kGateResid, One>), g, t, 0, s, b);
         else hipLaunchKernelGGL((k_resid_stream<kGateNone, One>), g, t, 0, s, b);
     } else if (A->kernel == SPK_KERNEL_SELL) {
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2) {
-                if (gated) hipLaunchKernelGGL((k_resid_sell<kGateResid, int16_t, U, One>), g, t, 0, s, b);
-                else hipLaunchKernelGGL((k_resid_sell<kGateNone, int16_t, U, One>), g, t, 0, s, b);
-            } else {
-                if (gated) hipLaunchKernelGGL((k_resid_sell<kGateResid, int32_t, U, One>), g, t, 0, s, b);
-                else hipLaunchKernelGGL((k_resid_sell<kGateNone, int32_t, U, One>), g, t, 0, s, b);
-            }
+            if (gated) hipLaunchKernelGGL((k_resid_sell<kGateResid, CI, U, One>), g, t, 0, s, b);
+            else hipLaunchKernelGGL((k_resid_sell<kGateNone, CI, U, One>), g, t, 0, s, b);
         });
     } else {
         SPK_TRY(launch_spmv<double>(A, A->val, w->x, w->r, s, gated ? w->st : nullptr,
@@ -278,10 +274,12 @@ static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
         hipLaunchKernelGGL((k_pcg_spmv_stream<V, One>), g, t, 0, s, b);
     } else if (A->kernel == SPK_KERNEL_SELL && w->wpart) {
         const dim3 gw(w->nwpart);
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2) hipLaunchKernelGGL((k_pcg_spmv_sell_wide<V, int16_t, U>), gw, t, 0, s, b, w->wpart);
-            else hipLaunchKernelGGL((k_pcg_spmv_sell_wide<V, int32_t, U>), gw, t, 0, s, b, w->wpart);
+            // (a list for the whole matrix streams too little for the rule)
+            if constexpr (!std::is_same<CI, Stencil>::value)
+                hipLaunchKernelGGL((k_pcg_spmv_sell_wide<V, CI, U>), gw, t, 0, s, b, w->wpart);
         });
         // the pair times the slice kernel, which moves the bytes; the fold
         // of its per-block partials (one block, a few microseconds) is outside
@@ -291,10 +289,10 @@ static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
         }
         hipLaunchKernelGGL((k_fin_pq<V>), one, dim3(kFinPqThreads), 0, s, b, (const double *)w->wpart, w->nwpart);
     } else if (A->kernel == SPK_KERNEL_SELL) {
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2) hipLaunchKernelGGL((k_pcg_spmv_sell<V, int16_t, U, One>), g, t, 0, s, b);
-            else hipLaunchKernelGGL((k_pcg_spmv_sell<V, int32_t, U, One>), g, t, 0, s, b);
+            hipLaunchKernelGGL((k_pcg_spmv_sell<V, CI, U, One>), g, t, 0, s, b);
         });
     } else {
         const V *val = std::is_same<V, double>::value ? (const V *)A->val : (const V *)A->val32;
@@ -316,10 +314,10 @@ static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
 {
     const One b = batch_of(w);
     const dim3 g(A->nblk), t(kBlock);
-    with_sell_u(A->sell_u, [&](auto uc) {
+    with_sell(A, [&](auto ci, auto uc) {
+        using CI = decltype(ci);
         constexpr int U = decltype(uc)::value;
-        if (A->sell_cw == 2) hipLaunchKernelGGL((k_pcg_fused_sell<V, int16_t, U, kStart, One>), g, t, 0, s, b);
-        else hipLaunchKernelGGL((k_pcg_fused_sell<V, int32_t, U, kStart, One>), g, t, 0, s, b);
+        hipLaunchKernelGGL((k_pcg_fused_sell<V, CI, U, kStart, One>), g, t, 0, s, b);
     });
 }
 
@@ -567,10 +565,10 @@ static int sr_spmv(spk_mat *A, Workspace *w, const SrDesc &a, int m, hipStream_t
 {
     const dim3 g(A->nblk), t(kBlock);
     if (A->kernel == SPK_KERNEL_SELL) {
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2) hipLaunchKernelGGL((k_sr_spmv_sell<int16_t, U>), g, t, 0, s, a, m);
-            else hipLaunchKernelGGL((k_sr_spmv_sell<int32_t, U>), g, t, 0, s, a, m);
+            hipLaunchKernelGGL((k_sr_spmv_sell<CI, U>), g, t, 0, s, a, m);
         });
     } else if (A->kernel == SPK_KERNEL_STREAM) {
         hipLaunchKernelGGL(k_sr_spmv_stream, g, t, 0, s, a, m);
@@ -732,20 +730,19 @@ int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s, int *np)
         if (!sval) { set_error("internal: no SELL values of this precision"); return SPK_EINVAL; }
         auto from_zero = [&](auto *b) {
             using B = std::remove_const_t<std::remove_pointer_t<decltype(b)>>;
-            with_sell_u(A->sell_u, [&](auto uc) {
+            with_sell(A, [&](auto ci, auto uc) {
+                using CI = decltype(ci);
                 constexpr int U = decltype(uc)::value;
-                if (A->sell_cw == 2)
-                    hipLaunchKernelGGL((k_cheb_sell_zero<V, B, int16_t, U>), gs, t, 0, s, n, sv, sval, c, b);
-                else hipLaunchKernelGGL((k_cheb_sell_zero<V, B, int32_t, U>), gs, t, 0, s, n, sv, sval, c, b);
+                hipLaunchKernelGGL((k_cheb_sell_zero<V, B, CI, U>), gs, t, 0, s, n, sv, sval, c, b);
             });
         };
         if (c.b64) from_zero(c.b64);
         else if (c.b) from_zero(c.b);
         else
-            with_sell_u(A->sell_u, [&](auto uc) {
+            with_sell(A, [&](auto ci, auto uc) {
+                using CI = decltype(ci);
                 constexpr int U = decltype(uc)::value;
-                if (A->sell_cw == 2) hipLaunchKernelGGL((k_cheb_sell<V, int16_t, U>), gs, t, 0, s, n, sv, sval, c);
-                else hipLaunchKernelGGL((k_cheb_sell<V, int32_t, U>), gs, t, 0, s, n, sv, sval, c);
+                hipLaunchKernelGGL((k_cheb_sell<V, CI, U>), gs, t, 0, s, n, sv, sval, c);
             });
         if (np) *np = (int)gs.x;
     } else if (A->kernel == SPK_KERNEL_STREAM) {

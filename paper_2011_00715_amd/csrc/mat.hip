@@ -311,12 +311,10 @@ int launch_spmv(const spk_mat *A, const V *val, const V *x, V *y, hipStream_t s,
         // up to one wavefront per slice
         const dim3 grid(std::max(1, std::min(ceil_div(ceil_div(A->n, kSell), kBlock / kWave), 16384)));
         const int n = A->n;
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2)
-                hipLaunchKernelGGL((k_spmv_sell<V, int16_t, U>), grid, dim3(kBlock), 0, s, n, sv, sval, x, y);
-            else
-                hipLaunchKernelGGL((k_spmv_sell<V, int32_t, U>), grid, dim3(kBlock), 0, s, n, sv, sval, x, y);
+            hipLaunchKernelGGL((k_spmv_sell<V, CI, U>), grid, dim3(kBlock), 0, s, n, sv, sval, x, y);
         });
         break;
     }
@@ -409,9 +407,9 @@ void update_info(spk_mat *A)
         I.stored_nnz = A->sell_nnz;
         // offsets and row lengths (or shared offsets and row masks), plus the
         // row permutation of SELL-C-sigma
-        const int64_t extra = A->sell_idx_bytes + (A->sell_perm ? 4 * nn : 0);
-        I.format_bytes_spmv_f64 = 8 * A->sell_nnz + 4 * (ns + 1) + 16 * nn + extra;
-        I.format_bytes_spmv_f32 = 4 * A->sell_nnz + 4 * (ns + 1) + 8 * nn + extra;
+        const int64_t extra = A->sell_idx_bytes + (A->sell_perm ? 4 * nn : 0) + (A->sell_ptr ? 4 * (ns + 1) : 0);
+        I.format_bytes_spmv_f64 = 8 * A->sell_nnz + 16 * nn + extra;
+        I.format_bytes_spmv_f32 = 4 * A->sell_nnz + 8 * nn + extra;
     } else if (A->kernel == SPK_KERNEL_SLICED && A->xs_ptr) {
         // stacked slices: 8n + 1 row pointers; the 8n partial products are
         // written once and read once by the summing pass
@@ -556,7 +554,7 @@ static void free_sell(spk_mat *A)
 {
     if (A->sell_cw) {
         const int64_t ns = (A->n + kSell - 1) / kSell;
-        A->bytes -= 4 * (ns + 1) + 8 * A->sell_nnz + A->sell_idx_bytes;
+        A->bytes -= (A->sell_ptr ? 4 * (ns + 1) : 0) + 8 * A->sell_nnz + A->sell_idx_bytes;
         if (A->sell_perm) A->bytes -= 4ll * A->n;
         if (A->sell_val32) A->bytes -= 4 * A->sell_nnz;
     }
@@ -592,7 +590,9 @@ static void free_sell(spk_mat *A)
 // most 1/16 over the per-lane layout.  *fits says whether it is so; if not,
 // nothing is left behind.  Slice s spans 64 u[s] elements (u: the list
 // lengths); its offsets sit at element sell_ptr[s] / 64 of sell_col (int32).
-// With may_unify a matrix of one value per slice position stores those only.
+// With may_unify a matrix of one value per offset stores one list for all
+// slices (kSellUniform), if that leaves the gathers of positions that rows do
+// not use below a quarter.
 static int build_sell_shared(spk_mat *A, hipStream_t s, bool may_unify, bool *fits)
 {
     *fits = false;
@@ -618,6 +618,7 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, bool may_unify, bool *fi
     auto *width = (int32_t *)t.p[1], *list = (int32_t *)t.p[2], *base = (int32_t *)t.p[3];
     const int blocks = std::min(ceil_div(ns, kBlock / kWave), kMaxBlocksSingle);
     *t.host = SharedStats{};
+    std::fill(t.host->offs, t.host->offs + kSell, kNoOffset);
     SPK_HIP(hipMemcpyAsync(stats, t.host, sizeof(SharedStats), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_shared_lists, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->col, width, list,
                        A->sell_mask, stats);
@@ -633,50 +634,72 @@ static int build_sell_shared(spk_mat *A, hipStream_t s, bool may_unify, bool *fi
     }
     *fits = true;
     if (acc > 0x7fffffffLL) { set_error("SELL layout exceeds 2^31 entries"); return SPK_EINVAL; }
-    const size_t no = st.shared > 0 ? (size_t)st.shared : 1;
-    SPK_HIP(hipMalloc(&A->sell_ptr, sizeof(int32_t) * ((size_t)ns + 1)));
-    SPK_HIP(hipMalloc(&A->sell_col, sizeof(int32_t) * no));
-    hipLaunchKernelGGL(k_shared_pack, dim3(ceil_div((int64_t)(ns + 1) * kSellSharedMax, kBlock)), dim3(kBlock), 0, s,
-                       ns, (const int32_t *)base, (const int32_t *)list, A->sell_ptr, (int32_t *)A->sell_col);
+    // one list for the whole matrix?
+    StencilList l{};
+    if (may_unify && !st.many) {
+        std::vector<std::pair<int32_t, int32_t>> all;
+        for (const unsigned long long v : st.offs)
+            if (v != kNoOffset) all.emplace_back((int32_t)(v >> 32), (int32_t)v);
+        std::sort(all.begin(), all.end());
+        if ((int)all.size() <= kSellUniformMax && 4 * (uint64_t)all.size() * ns <= 5 * st.shared) {
+            l.w = (int)all.size();
+            for (int j = 0; j < l.w; ++j) {
+                l.off[j] = all[j].first;
+                l.entry[j] = all[j].second;
+            }
+        }
+    }
     bool uniform = false;
-    if (may_unify) {
-        int32_t *varied = &stats->bad;  // zero here
-        SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * no));
-        hipLaunchKernelGGL(k_shared_uniform, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
-                           (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val, varied);
-        SPK_HIP(hipMemcpyAsync(&t.host->bad, varied, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        SPK_HIP(hipStreamSynchronize(s));
-        uniform = t.host->bad == 0;
+    if (l.w > 0) {
+        uint32_t *mask = nullptr;
+        SPK_HIP(hipMalloc(&A->sell_col, sizeof(int32_t) * l.w));
+        SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * l.w));
+        SPK_HIP(hipMalloc(&mask, sizeof(uint32_t) * (size_t)n));
+        hipLaunchKernelGGL(k_stencil_masks, dim3(std::min(ceil_div(2 * ns, kBlock / kWave), kMaxBlocksSingle)),
+                           dim3(kBlock), 0, s, n, l, A->rowptr, A->col, A->val, mask, (int32_t *)A->sell_col,
+                           A->sell_val, &stats->varied);
+        hipError_t e = hipMemcpyAsync(&t.host->varied, &stats->varied, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        uniform = e == hipSuccess && t.host->varied == 0;
+        if (uniform) std::swap(mask, A->sell_mask);
+        hipFree(mask);
+        if (e != hipSuccess) return hip_fail(e, "stencil masks", __FILE__, __LINE__);
         if (!uniform) {
+            hipFree(A->sell_col);
             hipFree(A->sell_val);
+            A->sell_col = nullptr;
             A->sell_val = nullptr;
         }
     }
     // the load policy below is that of a value per entry either way
-    const int64_t entries = acc;
-    if (uniform) acc = (int64_t)st.shared;
+    const int64_t entries = acc, offsets = uniform ? l.w : (int64_t)st.shared;
+    if (uniform) acc = l.w;
     const size_t m = acc > 0 ? (size_t)acc : 1;
     if (!uniform) {
+        SPK_HIP(hipMalloc(&A->sell_ptr, sizeof(int32_t) * ((size_t)ns + 1)));
+        SPK_HIP(hipMalloc(&A->sell_col, sizeof(int32_t) * (st.shared > 0 ? (size_t)st.shared : 1)));
         SPK_HIP(hipMalloc(&A->sell_val, sizeof(double) * m));
+        hipLaunchKernelGGL(k_shared_pack, dim3(ceil_div((int64_t)(ns + 1) * kSellSharedMax, kBlock)), dim3(kBlock), 0,
+                           s, ns, (const int32_t *)base, (const int32_t *)list, A->sell_ptr, (int32_t *)A->sell_col);
         hipLaunchKernelGGL(k_shared_fill, dim3(blocks), dim3(kBlock), 0, s, n, A->rowptr, A->val,
                            (const int32_t *)A->sell_ptr, (const uint32_t *)A->sell_mask, A->sell_val);
     }
     SPK_HIP(hipGetLastError());
     A->sell_cw = 4;
     A->sell_sigma = 0;
-    A->sell_u = pick_sell_u(st.widest);
+    A->sell_u = pick_sell_u(uniform ? l.w : st.widest);
     A->sell_nnz = acc;
-    A->sell_idx_bytes = 4 * (int64_t)st.shared + 4ll * n;
+    A->sell_idx_bytes = 4 * offsets + 4ll * n;
     // the load policy counts cw bytes per entry plus one byte per row:
     // here no bytes per entry and the rest of the index bytes in the budget
-    const int64_t extra = A->sell_idx_bytes - n;
+    const int64_t extra = 4 * (int64_t)st.shared + 3ll * n;
     A->sell_plain = A->stream_loads ? 0 : sell_load_policy(entries, 0, ns, n, 6, kIterCacheBudget - extra);
     A->sell_plain_spmv = A->stream_loads ? 0 : sell_load_policy(entries, 0, ns, n, 2, kSpmvCacheBudget - extra);
     if (uniform) {
-        A->sell_plain |= kSellUniform;
-        A->sell_plain_spmv |= kSellUniform;
+        A->sell_plain |= kSellUniform | l.w << kSellWidthShift;
+        A->sell_plain_spmv |= kSellUniform | l.w << kSellWidthShift;
     }
-    A->bytes += 4 * ((int64_t)ns + 1) + 8 * acc + A->sell_idx_bytes;
+    A->bytes += (uniform ? 0 : 4 * ((int64_t)ns + 1)) + 8 * acc + A->sell_idx_bytes;
     if (A->val32) {
         SPK_HIP(hipMalloc(&A->sell_val32, sizeof(float) * m));
         hipLaunchKernelGGL(k_to_f32, dim3(grid_for((int64_t)m)), dim3(kBlock), 0, s, (int64_t)m, A->sell_val,

@@ -146,14 +146,11 @@ static int launch_rows(spk_mat *A, const V *x, F f, double *part, int *np, const
         const SellView sv{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain, A->sell_len16, A->sell_perm, A->sell_mask};
         const int grid = std::max(1, std::min(ceil_div(ceil_div(n, kSell), kBlock / kWave), kMgMaxPart));
         const V *sval = f64 ? (const V *)A->sell_val : (const V *)A->sell_val32;
-        with_sell_u(A->sell_u, [&](auto uc) {
+        with_sell(A, [&](auto ci, auto uc) {
+            using CI = decltype(ci);
             constexpr int U = decltype(uc)::value;
-            if (A->sell_cw == 2)
-                hipLaunchKernelGGL((k_mg_rows_sell<V, int16_t, U, F>), dim3(grid), dim3(kBlock), 0, s, n, sv, sval, x,
-                                   f, part, gate);
-            else
-                hipLaunchKernelGGL((k_mg_rows_sell<V, int32_t, U, F>), dim3(grid), dim3(kBlock), 0, s, n, sv, sval, x,
-                                   f, part, gate);
+            hipLaunchKernelGGL((k_mg_rows_sell<V, CI, U, F>), dim3(grid), dim3(kBlock), 0, s, n, sv, sval, x, f, part,
+                               gate);
         });
         if (np) *np = grid;
     } else if (A->kernel == SPK_KERNEL_STREAM) {

@@ -377,8 +377,9 @@ static __global__ void k_mg_round(int n, const double *__restrict__ a, float *__
 }
 
 // ------------------------------------------------------------------ SpMV rows with an epilogue
-// Row epilogues: f(i, y = (A x)_i) stores what the row produces and returns
-// its contribution to an inner product (0 when none is wanted).
+// Row epilogues: f.own(i) loads the row's own operands, f(i, y = (A x)_i, own)
+// stores what the row produces and returns its contribution to an inner
+// product (0 when none is wanted).
 
 // Smoother start from a nonzero x: r = b - A x, d_0 = D^-1 r / theta.
 template <class V>
@@ -387,11 +388,15 @@ struct RowResid {
     V *r, *d0;
     const V *dinv;
     V inv_theta;
-    __device__ double operator()(int i, V y) const
+    struct Own {
+        V b, dinv;
+    };
+    __device__ Own own(int i) const { return Own{b[i], dinv[i]}; }
+    __device__ double operator()(int i, V y, const Own &o) const
     {
-        const V ri = b[i] - y;
+        const V ri = o.b - y;
         r[i] = ri;
-        d0[i] = dinv[i] * ri * inv_theta;
+        d0[i] = o.dinv * ri * inv_theta;
         return 0.0;
     }
 };
@@ -400,10 +405,11 @@ struct RowResid {
 struct RowPq {
     const double *p;
     double *q;
-    __device__ double operator()(int i, double y) const
+    __device__ double own(int i) const { return p[i]; }
+    __device__ double operator()(int i, double y, double pi) const
     {
         q[i] = y;
-        return p[i] * y;
+        return pi * y;
     }
 };
 
@@ -411,9 +417,10 @@ struct RowPq {
 struct RowTrue {
     const double *b;
     double *r;
-    __device__ double operator()(int i, double y) const
+    __device__ double own(int i) const { return b[i]; }
+    __device__ double operator()(int i, double y, double bi) const
     {
-        const double ri = b[i] - y;
+        const double ri = bi - y;
         r[i] = ri;
         return ri * ri;
     }
@@ -435,7 +442,8 @@ __global__ __launch_bounds__(kBlock) void k_mg_rows_sell(int n, SellView sv, con
     bool run = true;
     sell_slices<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
                           gridDim.x * (kBlock / kWave), sv, val, x, [&] { return run = mg_go(gate); },
-                          [&](int i, V y) { acc += f(i, y); });
+                          [&](int i) { return f.own(i); },
+                          [&](int i, V y, const decltype(f.own(0)) &o) { acc += f(i, y, o); });
     if (part && run) store_partial(acc, part);
 }
 
@@ -455,7 +463,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_rows_stream(int n, int R, int nti
     for (int t = t0; t < t1; ++t) {
         const int r0 = t * R;
         const int r1 = min(r0 + R, n);
-        stream_tile<V>(r0, r1, rowptr, col, val, x, sm, [&](int i, V y) { acc += f(i, y); });
+        stream_tile<V>(r0, r1, rowptr, col, val, x, sm, [&](int i, V y) { acc += f(i, y, f.own(i)); });
     }
     if (part) store_partial(acc, part);
 }
@@ -467,7 +475,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_rows_y(int n, const V *__restrict
 {
     if (!mg_go(gate)) return;
     double acc = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) acc += f(i, y[i]);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) acc += f(i, y[i], f.own(i));
     if (part) store_partial(acc, part);
 }
 

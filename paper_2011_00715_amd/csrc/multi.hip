@@ -72,7 +72,7 @@ static MultiDesc multi_desc(const spk_mat *A, int K)
     d.col = A->col;
     d.val = A->val;
     d.dinv = A->dinv;
-    d.sv = SellView{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain & kSellUniform, nullptr, nullptr,
+    d.sv = SellView{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain & ~(kSellPlain64 | kSellPlain32), nullptr, nullptr,
                     A->sell_mask};
     d.sell_val = A->sell_val;
     return d;
@@ -83,7 +83,7 @@ template <class F>
 static void with_multi(const spk_mat *A, int K, F &&f)
 {
     auto ci = [&](auto kc) {
-        if (A->kernel == SPK_KERNEL_SELL && A->sell_cw == 4) f(int32_t{}, kc);
+        if (A->kernel == SPK_KERNEL_SELL) with_sell_ci(A->sell_cw, A->sell_plain, [&](auto ci) { f(ci, kc); });
         else f(int16_t{}, kc);
     };
     switch (K) {

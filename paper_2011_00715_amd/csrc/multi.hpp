@@ -97,7 +97,7 @@ constexpr int kOneRoundPairs = 3;
 //
 // SH: shared offsets (see the SELL-64 notes): offsets from the slice's list,
 // rlen the row's position mask, gathered rows clamped into [0, n).  UNI: one
-// value per slice position, from the slice's list too.
+// value per offset, both from the matrix's one list.
 //
 // pdiag (the pipelined walk only; null otherwise): where to keep the row's
 // own gathered X row, the gather of its diagonal entry (offset 0; the
@@ -114,7 +114,7 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
     using CP = typename Pair2<CI>::type;
     using VP = typename Pair2<double>::type;
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
-    const int32_t first = __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
+    const int32_t first = UNI ? 0 : __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
     const int32_t *__restrict__ ou = reinterpret_cast<const int32_t *>(sv.col) + first;
     const double *__restrict__ uv = val + first;
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
@@ -280,7 +280,11 @@ __device__ __forceinline__ void multi_sell_walk(const MultiDesc &d, int l, const
     const int lane = threadIdx.x & (kWave - 1);
     const int ns = (d.n + kSell - 1) / kSell;
     for (int s = l * (kBlock / kWave) + (int)threadIdx.x / kWave; s < ns; s += d.nblk * (kBlock / kWave)) {
-        const int32_t b = d.sv.ptr[s], e = d.sv.ptr[s + 1];
+        int32_t b = 0, e = (d.sv.plain >> kSellWidthShift) * kSell;
+        if constexpr (!UNI) {
+            b = d.sv.ptr[s];
+            e = d.sv.ptr[s + 1];
+        }
         const int row = s * kSell + lane;
         if (row < d.n) {
             double acc[K];
@@ -304,14 +308,17 @@ template <class CI, int K, bool kOneRound, class Flat>
 __device__ __forceinline__ void multi_sell_staged(const MultiDesc &d, int l, const double *__restrict__ X,
                                                   double *stage, double *pstage, Flat &&flat)
 {
-    if constexpr (std::is_same<CI, int32_t>::value) {
-        if (d.sv.mask) {
-            if (d.sv.plain & kSellUniform) multi_sell_walk<CI, K, kOneRound, true, true>(d, l, X, stage, pstage, flat);
-            else multi_sell_walk<CI, K, kOneRound, true, false>(d, l, X, stage, pstage, flat);
-            return;
+    if constexpr (std::is_same<CI, Stencil>::value) {
+        multi_sell_walk<int32_t, K, kOneRound, true, true>(d, l, X, stage, pstage, flat);
+    } else {
+        if constexpr (std::is_same<CI, int32_t>::value) {
+            if (d.sv.mask) {
+                multi_sell_walk<CI, K, kOneRound, true, false>(d, l, X, stage, pstage, flat);
+                return;
+            }
         }
+        multi_sell_walk<CI, K, kOneRound, false, false>(d, l, X, stage, pstage, flat);
     }
-    multi_sell_walk<CI, K, kOneRound, false, false>(d, l, X, stage, pstage, flat);
 }
 
 // Row walk of block l (of nblk) of a multi kernel: SELL slices in
@@ -326,24 +333,25 @@ __device__ __forceinline__ void multi_rows(const MultiDesc &d, int l, int j, con
         const int lane = threadIdx.x & (kWave - 1);
         const int ns = (d.n + kSell - 1) / kSell;
         for (int s = l * (kBlock / kWave) + (int)threadIdx.x / kWave; s < ns; s += d.nblk * (kBlock / kWave)) {
-            const int32_t b = d.sv.ptr[s], e = d.sv.ptr[s + 1];
             const int row = s * kSell + lane;
-            if (row < d.n) {
+            if (row >= d.n) continue;
+            if constexpr (std::is_same<CI, Stencil>::value) {
+                sell_row_multi<int32_t, K, false, true, true>(d.sv, d.sell_val, X, 0, d.sv.plain >> kSellWidthShift,
+                                                              (int)d.sv.mask[row], lane, row, d.n, acc);
+            } else {
+                const int32_t b = d.sv.ptr[s], e = d.sv.ptr[s + 1];
+                bool done = false;
                 if constexpr (std::is_same<CI, int32_t>::value) {
                     if (d.sv.mask) {
-                        if (d.sv.plain & kSellUniform)
-                            sell_row_multi<CI, K, false, true, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
-                                                                     (int)d.sv.mask[row], lane, row, d.n, acc);
-                        else
-                            sell_row_multi<CI, K, false, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
-                                                               (int)d.sv.mask[row], lane, row, d.n, acc);
-                        fn(row, acc);
-                        continue;
+                        sell_row_multi<CI, K, false, true>(d.sv, d.sell_val, X, b, (e - b) / kSell,
+                                                           (int)d.sv.mask[row], lane, row, d.n, acc);
+                        done = true;
                     }
                 }
-                sell_row_multi<CI, K>(d.sv, d.sell_val, X, b, (e - b) / kSell, d.sv.len[row], lane, row, d.n, acc);
-                fn(row, acc);
+                if (!done)
+                    sell_row_multi<CI, K>(d.sv, d.sell_val, X, b, (e - b) / kSell, d.sv.len[row], lane, row, d.n, acc);
             }
+            fn(row, acc);
         }
     } else {
         int t0, t1;

@@ -161,6 +161,14 @@ struct spk_mat {
 
 namespace spk {
 
+// The handle's SELL kernels: f(offset type CI, integral_constant U).
+template <class F>
+inline void with_sell(const spk_mat *A, F &&f)
+{
+    with_sell_ci(A->sell_cw, A->sell_plain,
+                 [&](auto ci) { with_sell_u(A->sell_u, [&](auto uc) { f(ci, uc); }); });
+}
+
 // y = A x with the handle's kernel (V = double or float); optional gate for
 // launches inside captured solver graphs.
 template <class V>

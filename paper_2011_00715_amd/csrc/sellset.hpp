@@ -20,7 +20,35 @@ struct SharedStats {
     unsigned long long lane;    // sum of the longest rows
     int32_t widest;             // longest list
     int32_t bad;                // slices with over kSellSharedMax offsets, or rows not strictly ascending
+    int32_t many;               // the matrix has more distinct offsets than the table holds
+    int32_t varied;             // entries of one offset differ
+    // the matrix's distinct offsets, in no order: offset in the high word,
+    // one entry that has it in the low one
+    unsigned long long offs[kSell];
 };
+
+// A free slot of the table: no offset is -2^31.
+constexpr unsigned long long kNoOffset = 0x8000000000000000ull;
+
+// Puts (offset, entry) into the table unless the offset is there.  seen: the
+// block's LDS memory of offsets it has put there (kSell slots), which spares
+// nearly every slice the look at the table (128^3: 400 -> 118 us).
+__device__ __forceinline__ void note_offset(SharedStats *st, int32_t *seen, int off, int entry)
+{
+    const unsigned at = (uint32_t)off * 2654435761u >> 26;
+    if (seen[at] == off) return;
+    seen[at] = off;
+    if (__hip_atomic_load(&st->many, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const unsigned long long v = ((unsigned long long)(uint32_t)off << 32) | (uint32_t)entry;
+    unsigned h = at;
+    for (int i = 0; i < kSell; ++i, h = (h + 1) & (kSell - 1)) {
+        unsigned long long have =
+            __hip_atomic_load(&st->offs[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (have == kNoOffset) have = atomicCAS(&st->offs[h], kNoOffset, v);
+        if (have == kNoOffset || (have ^ v) >> 32 == 0) return;
+    }
+    __hip_atomic_store(&st->many, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 constexpr int kSharedCap = kSell * kSellSharedMax;  // entries of a slice whose rows all fit
 
@@ -56,6 +84,9 @@ static __global__ __launch_bounds__(kBlock) void k_shared_lists(int n, const int
 {
     constexpr int kNone = 0x7fffffff;
     __shared__ int32_t stage[kBlock / kWave][kSharedCap];
+    __shared__ int32_t seen[kSell];
+    if (threadIdx.x < kSell) seen[threadIdx.x] = (int32_t)0x80000000;
+    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int ns = (n + kSell - 1) / kSell;
     int32_t *sc = stage[w];
@@ -78,6 +109,7 @@ static __global__ __launch_bounds__(kBlock) void k_shared_lists(int n, const int
                 wrong = 1;
                 break;
             }
+            const int holder = __ffsll((unsigned long long)__ballot(cur == least)) - 1;
             if (cur == least) {
                 m |= 1u << count;
                 ++k;
@@ -86,6 +118,7 @@ static __global__ __launch_bounds__(kBlock) void k_shared_lists(int n, const int
                 cur = next;
             }
             if (lane == 0) list[(size_t)s * kSellSharedMax + count] = least;
+            if (holder == lane) note_offset(out, seen, least, base + k - 1);
             ++count;
             if (__any(wrong)) break;
         }
@@ -167,39 +200,65 @@ static __global__ __launch_bounds__(kBlock) void k_shared_fill(int n, const int3
     }
 }
 
-// One value per slice position: uval takes, at each offset's index, the value
-// of the position's first row; *varied is set when some row's differs (in its
-// bits).  Every slice position has a row, so every element is written.
-static __global__ __launch_bounds__(kBlock) void k_shared_uniform(int n, const int32_t *__restrict__ rowptr,
-                                                                  const double *__restrict__ val,
-                                                                  const int32_t *__restrict__ sptr,
-                                                                  const uint32_t *__restrict__ mask,
-                                                                  double *__restrict__ uval, int32_t *varied)
+// The one list of a matrix of one value per offset, ascending, each with an
+// entry that has it.
+struct StencilList {
+    int32_t w;
+    int32_t off[kSellUniformMax];
+    int32_t entry[kSellUniformMax];
+};
+
+// Row masks over the list, the list's offsets and values; *varied is set when
+// some entry differs (in its bits) from its offset's.
+static __global__ __launch_bounds__(kBlock) void k_stencil_masks(int n, StencilList l,
+                                                                 const int32_t *__restrict__ rowptr,
+                                                                 const int32_t *__restrict__ col,
+                                                                 const double *__restrict__ val,
+                                                                 uint32_t *__restrict__ mask,
+                                                                 int32_t *__restrict__ offs,
+                                                                 double *__restrict__ uval, int32_t *varied)
 {
-    __shared__ double stage[kBlock / kWave][kSharedCap];
+    __shared__ double stage[kBlock / kWave][kSharedCap / 2];
+    __shared__ int32_t cols[kBlock / kWave][kSharedCap / 2];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int ns = (n + kSell - 1) / kSell;
-    double *sc = stage[w];
+    const int ns = (n + kSell / 2 - 1) / (kSell / 2);  // half slices, so that both stages fit
+    if (blockIdx.x == 0 && (int)threadIdx.x < l.w) {
+        int32_t o = 0, k = 0;
+#pragma unroll
+        for (int j = 0; j < kSellUniformMax; ++j)
+            if (j == (int)threadIdx.x) {
+                o = l.off[j];
+                k = l.entry[j];
+            }
+        offs[threadIdx.x] = o;
+        uval[threadIdx.x] = val[k];
+    }
     for (int s = blockIdx.x * (kBlock / kWave) + w; s < ns; s += gridDim.x * (kBlock / kWave)) {
         if (__hip_atomic_load(varied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-        const int row = s * kSell + lane;
-        const int base = rowptr[s * kSell], total = rowptr[min(n, (s + 1) * kSell)] - base;
-        const int first = sptr[s] / kSell, slen = sptr[s + 1] / kSell - first;
-        const uint32_t m = row < n ? mask[row] : 0u;
+        const int r0 = s * (kSell / 2), row = r0 + (lane & (kSell / 2 - 1));
+        const int base = rowptr[r0], total = rowptr[min(n, r0 + kSell / 2)] - base;
         int k = rowptr[min(row, n)] - base;
+        const int e = rowptr[min(row + 1, n)] - base;
         wave_lds_sync();
-        for (int i = lane; i < total; i += kWave) sc[i] = val[base + i];
-        wave_lds_sync();
-        bool differs = false;
-        for (int j = 0; j < slen; ++j) {
-            const bool has = (m >> j) & 1u;
-            const long long v = has ? __double_as_longlong(sc[k++]) : 0;
-            const int holder = __ffsll((unsigned long long)__ballot(has)) - 1;
-            const long long v0 = __shfl(v, holder, kWave);
-            differs |= has && v != v0;
-            if (lane == 0) uval[first + j] = __longlong_as_double(v0);
+        for (int i = lane; i < total; i += kWave) {
+            stage[w][i] = val[base + i];
+            cols[w][i] = col[base + i];
         }
-        if (__any(differs) && lane == 0)
+        wave_lds_sync();
+        uint32_t m = 0;
+        bool differs = false;
+#pragma unroll
+        for (int j = 0; j < kSellUniformMax; ++j) {
+            if (j >= l.w) break;
+            const double v = val[l.entry[j]];
+            if (k < e && cols[w][k] - row == l.off[j]) {
+                differs |= __double_as_longlong(stage[w][k]) != __double_as_longlong(v);
+                m |= 1u << j;
+                ++k;
+            }
+        }
+        if (row < n && lane < kSell / 2) mask[row] = m;
+        if (__any(differs || k < e) && lane == 0)
             __hip_atomic_store(varied, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }

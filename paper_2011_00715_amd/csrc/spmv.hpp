@@ -218,6 +218,15 @@ __global__ __launch_bounds__(kBlock) void k_spmv_vector(int n, const int32_t *__
 // masked positions are multiplied, so the sums are the same as with
 // per-lane offsets.  Gathers of unmasked positions read a clamped valid
 // element of x and are discarded.
+//
+// One value per offset (constant coefficients): where a stencil matrix has at
+// most 27 distinct column offsets and every offset carries one and the same
+// number in all rows that have it (Laplacians and other constant-coefficient
+// stencils, and their Galerkin products), the layout is one list of offsets
+// and numbers for the whole matrix and each row's mask over it.  A product
+// then reads 4 bytes per row of matrix instead of 8 per entry, with the same
+// operands in the same order and so the same bits.  A matrix that varies
+// anywhere keeps a value per entry (stencil_slices below).
 constexpr int kSell = 64;
 constexpr int kSellSharedMax = 32;
 
@@ -254,9 +263,14 @@ struct SellView {
 // one is streamed with nontemporal loads, which keep it from evicting the
 // vectors that do fit.  One bit per value precision (FP64 / FP32 kernels).
 constexpr int kSellPlain64 = 1, kSellPlain32 = 2;
-// Third bit: one value per slice position (val then holds one element per
-// offset, at the offset's index).
-constexpr int kSellUniform = 4;
+// Third bit: one value per offset (col and val then hold the matrix's one
+// list, its length in the bits from kSellWidthShift on, and ptr is null).
+constexpr int kSellUniform = 4, kSellWidthShift = 8;
+constexpr int kSellUniformMax = 27;  // offsets of such a list: one round of the widest walk built
+// The kernels' offset type CI for it (beside int16_t and int32_t): a kernel of
+// its own, because as a branch of the int32_t kernels its scalars cost those
+// registers (27-point 160^3 solve 96.6 -> 100.0 ms).
+struct Stencil {};
 
 template <bool NT, class T>
 __device__ __forceinline__ T sell_ld(const T *p)
@@ -264,6 +278,23 @@ __device__ __forceinline__ T sell_ld(const T *p)
     if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
 }
+
+// What a row gathers: at(j) loads what the operand at column j is made of,
+// sh(base, l) the same for column base + l with base wave-uniform, which costs
+// no vector address arithmetic (scalar base, lane offset), and of(raw) forms
+// the operand.  Loading and forming are apart so that a round's loads are all
+// issued before the first is used: formed in the same breath, the compiler
+// waited for each operand in turn (the fused kernel of the 7-point 128^3
+// system 37.7 -> 29.1 us with the list in scalar
+// registers).
+template <class V>
+struct GatherX {
+    const V *__restrict__ x;
+    using Raw = V;
+    __device__ V at(int j) const { return x[j]; }
+    __device__ V sh(int64_t base, unsigned l) const { return (x + base)[l]; }
+    __device__ V of(V v) const { return v; }
+};
 
 // Row sum of lane `lane` of the slice starting at element b with slen
 // entries per row; the row has rlen of them.  Entries in column order, FMA.
@@ -273,25 +304,22 @@ __device__ __forceinline__ T sell_ld(const T *p)
 // last pair and padding has offset 0, so every gather reads a valid element
 // of x; only the row's own entries are multiplied.  UP is chosen per matrix
 // from the widest slice (3 for a 7-point stencil: one round and the tail).
-// gat(j) is the gathered operand at column j: x[j] for a plain product; the
-// fused PCG kernels form p = z + beta p there.
+// gat gives the gathered operands: x[j] for a plain product; the fused PCG
+// kernels form p = z + beta p there.
 //
 // SH (shared offsets, CI = int32): the offsets come from the slice's list
 // (wave-uniform, scalar loads), rlen is the row's position mask, and gathered
 // columns are clamped into [0, n) for the positions the row does not use.
-// UNI (with SH): the values come from the slice's list too.
-template <class V, class CI, int UP, bool NT, bool SH, bool UNI, class G>
+template <class V, class CI, int UP, bool NT, bool SH, class G>
 __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ val, G &&gat,
                                       int32_t b, int slen, int rlen, int lane, int row, int n)
 {
     static_assert(!SH || std::is_same<CI, int32_t>::value, "shared offsets are int32");
-    static_assert(!UNI || SH, "one value per position needs shared offsets");
     using CP = typename Pair2<CI>::type;
     using VP = typename Pair2<V>::type;
-    const int32_t first = __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
-    const int32_t *__restrict__ ou = reinterpret_cast<const int32_t *>(sv.col) + first;
-    const V *__restrict__ uv = val + first;
+    const int32_t *__restrict__ ou =
+        reinterpret_cast<const int32_t *>(sv.col) + (__builtin_amdgcn_readfirstlane(b) >> 6);
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
     auto offsets = [&](int p) -> CP {
         if constexpr (SH) {
@@ -301,16 +329,6 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
             return c;
         } else {
             return sell_ld<NT>(cp + (size_t)p * kSell);
-        }
-    };
-    auto values = [&](int p) -> VP {
-        if constexpr (UNI) {
-            VP a;
-            a.x = uv[2 * p];
-            a.y = uv[2 * p + 1];
-            return a;
-        } else {
-            return sell_ld<NT>(vp + (size_t)p * kSell);
         }
     };
     auto column = [&](int off) -> int {
@@ -326,13 +344,14 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
     // so an odd width costs no extra memory round trip; it is added last
     const bool odd = slen & 1;
     CI ct = CI(0);
-    V at = V(0), xt = V(0);
+    using Raw = typename std::remove_reference_t<G>::Raw;
+    V at = V(0);
+    Raw xt{};
     if (odd) {
         const size_t t = (size_t)b + (size_t)np * (2 * kSell) + lane;
         if constexpr (SH) ct = ou[2 * np];
         else ct = sell_ld<NT>(reinterpret_cast<const CI *>(sv.col) + t);
-        if constexpr (UNI) at = uv[2 * np];
-        else at = sell_ld<NT>(val + t);
+        at = sell_ld<NT>(val + t);
     }
     V acc = V(0);
     for (int p0 = 0; p0 < np; p0 += UP) {
@@ -342,40 +361,43 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
         for (int u = 0; u < UP; ++u) {
             const int p = p0 + u < np ? p0 + u : np - 1;
             c[u] = offsets(p);
-            a[u] = values(p);
+            a[u] = sell_ld<NT>(vp + (size_t)p * kSell);
         }
-        V xv[2 * UP];
+        Raw xv[2 * UP];
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
-            xv[2 * u] = gat(column((int)c[u].x));
-            xv[2 * u + 1] = gat(column((int)c[u].y));
+            xv[2 * u] = gat.at(column((int)c[u].x));
+            xv[2 * u + 1] = gat.at(column((int)c[u].y));
         }
-        if (p0 == 0 && odd) xt = gat(column((int)ct));
+        if (p0 == 0 && odd) xt = gat.at(column((int)ct));
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
             const int k = 2 * (p0 + u);
             if (p0 + u < np) {
-                if (real(k)) acc = fma(a[u].x, xv[2 * u], acc);
-                if (real(k + 1)) acc = fma(a[u].y, xv[2 * u + 1], acc);
+                if (real(k)) acc = fma(a[u].x, gat.of(xv[2 * u]), acc);
+                if (real(k + 1)) acc = fma(a[u].y, gat.of(xv[2 * u + 1]), acc);
             }
         }
     }
     if (odd) {
-        if (np == 0) xt = gat(column((int)ct));
-        if (real(slen - 1)) acc = fma(at, xt, acc);
+        if (np == 0) xt = gat.at(column((int)ct));
+        if (real(slen - 1)) acc = fma(at, gat.of(xt), acc);
     }
     return acc;
 }
 
+
 // Slices s, s + stride, ... below ceil(n/64), one per wavefront at a time;
-// fn(row, y) is called by the lane that owns row (< n).  Callers pass
+// fn(row, y, own) is called by the lane that owns row (< n), own being what
+// pre(row) loaded of the row's own operands (which no other row's fn
+// writes).  Callers pass
 // s = 4 * (physical block) + wave and stride = 4 * (blocks), so the slices in
 // flight at any moment are adjacent in memory (one DRAM stream front rather
 // than one per block).  The first slice's header is loaded before go() is
 // asked whether to run (go holds no barrier: waves may own different counts).
-template <class V, class CI, int U, bool NT, bool SH, bool UNI, class G, class Go, class Fn>
+template <class V, class CI, int U, bool NT, bool SH, class G, class Go, class Pre, class Fn>
 __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const SellView &sv,
-                                                const V *__restrict__ val, G &&gat, Go &&go, Fn &&fn)
+                                                const V *__restrict__ val, G &&gat, Go &&go, Pre &&pre, Fn &&fn)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int ns = (n + kSell - 1) / kSell;
@@ -397,7 +419,10 @@ __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const 
     if (!go()) return;
     while (s < ns) {
         const int slen = (e - b) / kSell;
-        if (s * kSell + lane < n) fn(row, sell_row<V, CI, U, NT, SH, UNI>(sv, val, gat, b, slen, rlen, lane, row, n));
+        if (s * kSell + lane < n) {
+            const V y = sell_row<V, CI, U, NT, SH>(sv, val, gat, b, slen, rlen, lane, row, n);
+            fn(row, y, pre(row));
+        }
         s += stride;
         if (s >= ns) break;
         b = sv.ptr[s];
@@ -406,34 +431,128 @@ __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const 
     }
 }
 
+// Memory that no kernel writes while this one runs, for scalar loads.
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *as_constant(const T *p)
+{
+    return (const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
+// The same walk for a matrix of one value per offset.  With 4 bytes of matrix
+// per row the walk is bound by its instructions and its round trips, no
+// longer by HBM: so a slice whose rows' offsets all stay inside [0, n), known
+// from the list's ends alone, gathers at scalar bases without clamping (the
+// lane is the only vector part of an address), all of a slice's gathers and
+// its rows' own operands are issued together, and the next slice's masks
+// before them.  Entries a row does not have are loaded (in the other slices
+// at columns clamped into the matrix) and not multiplied.  The list is never
+// empty.  7-point 128^3, against the walk of a value per entry: an FP64 PCG
+// iteration 61 -> 46.5 us (F 43.4 -> 29.1), the FP32 one 40.2 -> 30.3, two
+// smoothing steps 39.6 -> 20.0, the product 25.9 -> 15.
+template <class V, int U, class G, class Go, class Pre, class Fn>
+__device__ __forceinline__ void stencil_slices(int n, int s0, int stride, const SellView &sv,
+                                               const V *__restrict__ val, G &&gat, Go &&go, Pre &&pre, Fn &&fn)
+{
+    constexpr int W = 2 * U + 1;  // at least the list's length
+    const unsigned lane = threadIdx.x & (kWave - 1);
+    const int ns = (n + kSell - 1) / kSell;
+    const int w = sv.plain >> kSellWidthShift;
+    // constant for the kernel's life: read by scalar loads
+    const auto *ou = as_constant(reinterpret_cast<const int32_t *>(sv.col));
+    const auto *uv = as_constant(val);
+    const int64_t lo = ou[0], hi = ou[w - 1];
+    // positions past the list repeat its last one; no mask has their bits.  A
+    // short list stays in registers; a long one is read from the scalar cache
+    // for each slice (kept across the loop it spills).
+    constexpr bool kKeep = W <= 9;
+    int ok[kKeep ? W : 1];
+    V vk[kKeep ? W : 1];
+    if constexpr (kKeep) {
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            ok[k] = ou[min(k, w - 1)];
+            vk[k] = uv[min(k, w - 1)];
+        }
+    }
+    int s = __builtin_amdgcn_readfirstlane(s0);
+    auto masks = [&](int t) -> uint32_t {
+        const int j = t * kSell + (int)lane;
+        return j < n ? sv.mask[j] : 0u;
+    };
+    uint32_t next = s < ns ? masks(s) : 0u;
+    if (!go()) return;
+    while (s < ns) {
+        const int r0 = s * kSell, row = r0 + (int)lane;
+        const uint32_t m = next;
+        s += stride;
+        if (s < ns) next = masks(s);
+        const auto *o = ou;
+        const auto *v = uv;
+        if constexpr (!kKeep) asm volatile("" : "+s"(o), "+s"(v));
+        auto off = [&](int k) -> int {
+            if constexpr (kKeep) return ok[k];
+            else return o[min(k, w - 1)];
+        };
+        auto value = [&](int k) -> V {
+            if constexpr (kKeep) return vk[k];
+            else return v[min(k, w - 1)];
+        };
+        // before the gathers, and without a branch, which would keep them waiting
+        const auto own = pre(min(row, n - 1));
+        typename std::remove_reference_t<G>::Raw xv[W];
+        if (r0 + lo >= 0 && r0 + (kSell - 1) + hi < n) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) xv[k] = gat.sh((int64_t)r0 + off(k), lane);
+        } else {
+#pragma unroll
+            for (int k = 0; k < W; ++k) xv[k] = gat.at(min(max(row + off(k), 0), n - 1));
+        }
+        V acc = V(0);
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const V t = fma(value(k), gat.of(xv[k]), acc);
+            acc = (m >> k) & 1u ? t : acc;
+        }
+        if (row < n) fn(row, acc, own);
+    }
+}
+
 // The load policy is chosen here, around the whole slice loop, so that the
 // two variants stay separate code (a branch inside the round lets the
 // compiler merge the loads and drop the nontemporal hint).
-template <class V, class CI, int U, class G, class Go, class Fn>
+template <class V, class CI, int U, class G, class Go, class Pre, class Fn>
 __device__ __forceinline__ void sell_slices_g(int n, int s, int stride, const SellView &sv,
-                                              const V *__restrict__ val, G &&gat, Go &&go, Fn &&fn)
+                                              const V *__restrict__ val, G &&gat, Go &&go, Pre &&pre, Fn &&fn)
 {
     const bool plain = sv.plain & (sizeof(V) == 4 ? kSellPlain32 : kSellPlain64);
-    if constexpr (std::is_same<CI, int32_t>::value) {
-        if (sv.mask) {
-            if (sv.plain & kSellUniform) sell_slices_run<V, CI, U, false, true, true>(n, s, stride, sv, val, gat, go, fn);
-            else if (plain) sell_slices_run<V, CI, U, false, true, false>(n, s, stride, sv, val, gat, go, fn);
-            else sell_slices_run<V, CI, U, true, true, false>(n, s, stride, sv, val, gat, go, fn);
-            return;
+    if constexpr (std::is_same<CI, Stencil>::value) {
+        stencil_slices<V, U>(n, s, stride, sv, val, gat, go, pre, fn);
+    } else {
+        if constexpr (std::is_same<CI, int32_t>::value) {
+            if (sv.mask) {
+                if (plain) sell_slices_run<V, CI, U, false, true>(n, s, stride, sv, val, gat, go, pre, fn);
+                else sell_slices_run<V, CI, U, true, true>(n, s, stride, sv, val, gat, go, pre, fn);
+                return;
+            }
         }
+        if (plain) sell_slices_run<V, CI, U, false, false>(n, s, stride, sv, val, gat, go, pre, fn);
+        else sell_slices_run<V, CI, U, true, false>(n, s, stride, sv, val, gat, go, pre, fn);
     }
-    if (plain) sell_slices_run<V, CI, U, false, false, false>(n, s, stride, sv, val, gat, go, fn);
-    else sell_slices_run<V, CI, U, true, false, false>(n, s, stride, sv, val, gat, go, fn);
 }
 
 // The plain product: the gathered operand is x.
-template <class V, class CI, int U, class Go, class Fn>
+template <class V, class CI, int U, class Go, class Pre, class Fn>
 __device__ __forceinline__ void sell_slices(int n, int s, int stride, const SellView &sv,
                                             const V *__restrict__ val, const V *__restrict__ x,
-                                            Go &&go, Fn &&fn)
+                                            Go &&go, Pre &&pre, Fn &&fn)
 {
-    sell_slices_g<V, CI, U>(n, s, stride, sv, val, [x](int j) { return x[j]; }, go, fn);
+    sell_slices_g<V, CI, U>(n, s, stride, sv, val, GatherX<V>{x}, go, pre, fn);
 }
+
+// Own operands of rows whose epilogue needs none.
+struct NoOwn {
+    __device__ int operator()(int) const { return 0; }
+};
 
 // Standalone SELL SpMV; the grid has up to one wavefront per slice.
 template <class V, class CI, int U>
@@ -441,8 +560,18 @@ __global__ __launch_bounds__(kBlock) void k_spmv_sell(int n, SellView sv, const 
                                                       const V *__restrict__ x, V *__restrict__ y)
 {
     sell_slices<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
-                          gridDim.x * (kBlock / kWave), sv, val, x, [] { return true; },
-                          [&](int i, V s) { y[i] = s; });
+                          gridDim.x * (kBlock / kWave), sv, val, x, [] { return true; }, NoOwn{},
+                          [&](int i, V s, int) { y[i] = s; });
+}
+
+// Calls f with a value of the kernels' offset type for a layout: cw bytes per
+// offset, and its policy and layout bits.
+template <class F>
+inline void with_sell_ci(int cw, int plain, F &&f)
+{
+    if (plain & kSellUniform) f(Stencil{});
+    else if (cw == 2) f(int16_t{});
+    else f(int32_t{});
 }
 
 // Pairs per round UP the SELL kernels are built for, and the launch

@@ -90,9 +90,10 @@ __global__ __launch_bounds__(kBlock) void k_sr_spmv_sell(SrDesc a, int m)
     const bool run = gate_ok(g, kGateInner64);
     double wu = 0.0;
     sell_slices<double, CI, U>(d.n, sell_first((int)blockIdx.x), d.nblk * (kBlock / kWave), sv, d.sell_val, u,
-                               [&] { return run; }, [&](int r, double y) {
+                               [&] { return run; }, [u](int r) { return u[r]; },
+                               [&](int r, double y, double ur) {
                                    w[r] = y;
-                                   wu = fma(y, u[r], wu);
+                                   wu = fma(y, ur, wu);
                                });
     if (!run) return;
     wu = block_sum(wu, red);

@@ -106,9 +106,8 @@ def _outputs(spk, M, n):
 
 @pytest.mark.parametrize("case", ["lap2d_61", "lap3d_23", "box_13", "grid_1d_130", "empty_rows"])
 def test_uniform_values_same_bits(case):
-    """A matrix of one value per slice position stores those only (automatic
-    choice); every kernel family of the layout gives the bits of a value per
-    entry."""
+    """A matrix of one value per offset stores one list (automatic choice);
+    every kernel family of the layout gives the bits of a value per entry."""
     spk = need_gpu()
     A = {"lap2d_61": lambda: spkgen.laplace2d5(61, 0.3), "lap3d_23": lambda: spkgen.laplace3d7(23),
          "box_13": lambda: spkgen.diffusion3d27_lognormal(13, seed=1),
@@ -119,12 +118,13 @@ def test_uniform_values_same_bits(case):
         A = spkgen.CSR(A.n, A.rowptr, A.col, np.where(A.col == r, 27.0, -1.0 + 0.25 * (np.abs(A.col - r) == 1)))
     if case == "empty_rows":
         A = spkgen.CSR(A.n, A.rowptr, A.col, np.repeat(np.arange(A.n), np.diff(A.rowptr)) * 0 + 1.5)
-    widths, nlist = _shared_layout(A)
+    widths, _ = _shared_layout(A)
+    distinct = len(np.unique(A.col - np.repeat(np.arange(A.n), np.diff(A.rowptr))))
     res = []
     for param in (0, spk.SELL_SHARED, 16):
         M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
         spk.mat_set_kernel(M, spk.KERNEL_SELL, param)
-        assert M.info.stored_nnz == (nlist if param == 0 else 64 * sum(widths)) or param == 16
+        assert M.info.stored_nnz == (distinct if param == 0 else 64 * sum(widths)) or param == 16
         res.append(_outputs(spk, M, A.n))
         M.close()
     for other in res[1:]:
@@ -154,4 +154,30 @@ def test_uniform_values_need_every_entry(entry):
     spk.mat_mult(M, to_dev(x), y)
     yo = oracle.spmv(B, x)
     assert np.all(np.abs(y.cpu().numpy() - yo) <= 8 * 2.0 ** -53 * oracle.spmv_abs(B, x))
+    M.close()
+
+
+@pytest.mark.parametrize("distinct", [27, 28, 65])
+def test_uniform_values_offset_limit(distinct):
+    """27 distinct offsets in the whole matrix at most, however few each slice has."""
+    spk = need_gpu()
+    n = 64 * 70
+    rng = np.random.default_rng(distinct)
+    off = np.concatenate([[0], 1 + rng.choice(80, distinct - 1, replace=False) * 2])
+    rows = []
+    for i in range(n):  # slice s holds the diagonal and up to 23 of the others
+        have = np.unique(np.concatenate([[0], off[(i // 64 * 11 + np.arange(23)) % distinct]]))
+        rows.append([i + o for o in have if i + o < n])
+    rowptr = np.zeros(n + 1, np.int32)
+    rowptr[1:] = np.cumsum([len(r) for r in rows])
+    col = np.array([c for r in rows for c in r], np.int32)
+    r = np.repeat(np.arange(n), np.diff(rowptr))
+    A = spkgen.CSR(n, rowptr, col, np.where(col == r, 40.0, -1.0 - (col - r) / 128))
+    M = mat_on_gpu(spk, A)
+    widths, _ = _shared_layout(A)
+    assert M.info.lanes == 0 and M.info.stored_nnz == (distinct if distinct <= 27 else 64 * sum(widths))
+    x = rng.integers(-9, 10, n).astype(np.float64)
+    y = to_dev(np.full(n, np.nan))
+    spk.mat_mult(M, to_dev(x), y)
+    assert np.array_equal(y.cpu().numpy(), oracle.spmv(A, x))
     M.close()
