@@ -158,14 +158,111 @@ __device__ __forceinline__ int find_sys(const int32_t *blk_start, int nsys, int 
     return lo;
 }
 
+// Two registers' halves (D = 32) or rows of 16 lanes (D = 16) exchanged: lane
+// by lane, a then holds the lower and b the upper partner of each pair at
+// distance D, of x where that bit of the lane is clear and of y where it is
+// set.
+template <int D, class T>
+__device__ __forceinline__ void lane_swap(T x, T y, T &a, T &b)
+{
+    constexpr int W = sizeof(T) / 4;
+    union { T t; uint32_t w[W]; } ux, uy, ua, ub;
+    ux.t = x;
+    uy.t = y;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        if constexpr (D == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(ux.w[i], uy.w[i], false, false);
+            ua.w[i] = r[0];
+            ub.w[i] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane16_swap(ux.w[i], uy.w[i], false, false);
+            ua.w[i] = r[0];
+            ub.w[i] = r[1];
+        }
+    }
+    a = ua.t;
+    b = ub.t;
+}
+
+// The value D lanes on within a row of 16 (D < 16).
+template <int D, class T>
+__device__ __forceinline__ T row_ror(T v)
+{
+    constexpr int W = sizeof(T) / 4;
+    union { T t; uint32_t w[W]; } u;
+    u.t = v;
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+        u.w[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.w[i], 0x120 + D, 0xf, 0xf, true);
+    return u.t;
+}
+
+// One level of the butterfly: lane i's value plus lane i ^ D's.  Below 16 a
+// rotation by D is i ^ D once the values repeat every 2 D lanes, which the
+// levels 32, 16, 8, 4, 2, 1, taken in this order, give (at D = 8 a row is two
+// halves).
+template <int D, class T>
+__device__ __forceinline__ T wave_level(T v)
+{
+    if constexpr (D >= 16) {
+        T a, b;
+        lane_swap<D>(v, v, a, b);
+        return a + b;
+    } else {
+        return v + row_ror<D>(v);
+    }
+}
+
+// The levels 8, 4, 2, 1: sums of the rows of 16 lanes.
+template <class T>
+__device__ __forceinline__ T row_sum(T v)
+{
+    v = wave_level<8>(v);
+    v = wave_level<4>(v);
+    v = wave_level<2>(v);
+    return wave_level<1>(v);
+}
+
 // Butterfly sum over a wavefront; every lane ends with the same bits
 // (each level adds two values whose sum is commutative, hence identical).
+// Lane swaps and rotations instead of shuffles through the LDS pipe: a level
+// is three vector instructions instead of an LDS round trip.
 template <class T>
 __device__ __forceinline__ T wave_sum(T v)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    return row_sum(wave_level<16>(wave_level<32>(v)));
+}
+
+// Two butterfly sums at once, x's in the lower and y's in the upper half of
+// the lanes; four at once, w's, y's, x's and z's in rows 0 to 3.  The first
+// levels halve what a register needs, so the sums share the later ones; each
+// sum has wave_sum's bits.
+template <class T>
+__device__ __forceinline__ T wave_sum2(T x, T y)
+{
+    T a, b;
+    lane_swap<32>(x, y, a, b);
+    return row_sum(wave_level<16>(a + b));
+}
+
+template <class T>
+__device__ __forceinline__ T wave_sum4(T w, T x, T y, T z)
+{
+    T a, b, c, d, e, f;
+    lane_swap<32>(w, x, a, b);
+    lane_swap<32>(y, z, c, d);
+    lane_swap<16>(a + b, c + d, e, f);
+    return row_sum(e + f);
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    union { double d; int w[2]; } u;
+    u.d = v;
+    u.w[0] = __builtin_amdgcn_readlane(u.w[0], lane);
+    u.w[1] = __builtin_amdgcn_readlane(u.w[1], lane);
+    return u.d;
 }
 
 // Deterministic block sum: wave butterflies, then wave 0..3 in order.
