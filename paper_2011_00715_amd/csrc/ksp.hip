@@ -46,6 +46,9 @@ void free_workspace(spk_mat *A)
     hipFree(w->s);
     hipFree(w->srp);
     hipFree(w->sc);
+    hipFree(w->res_slots);
+    hipFree(w->res_gave_up);
+    hipHostFree(w->res_pgave_up);
     if (w->gsr) hipGraphExecDestroy(w->gsr);
     for (auto &e : w->pev)
         if (e) hipEventDestroy(e);
@@ -114,6 +117,17 @@ static bool fused_pays(const spk_mat *A, int bit)
     return !((six & bit) && !(seven & bit));
 }
 
+// Blocks of an FP64 solve's kernels.  The SELL partition rounds the tile count
+// down to a multiple of 8, so that a few blocks take two tiles; up to
+// kPcgBlocksSell tiles a block per tile serves as well, and then a partial sum
+// is one tile's wherever it is formed, which the one-launch iterations rely
+// on.  FP32 inner iterations keep the rounded partition: their sums' order
+// shows in the last digits of a mixed solve.
+static int fp64_blocks(const spk_mat *A)
+{
+    return A->kernel == SPK_KERNEL_SELL && A->sell_cw && A->ntiles <= kPcgBlocksSell ? A->ntiles : A->nblk;
+}
+
 static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
 {
     Workspace *w = A->ws;
@@ -125,7 +139,8 @@ static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
         SPK_TRY(dalloc(&w->ddesc, 1, w));
         SPK_TRY(dalloc(&w->blk_start, 2, w));
         SPK_TRY(dalloc(&w->st, 1, w));
-        SPK_TRY(dalloc(&w->partials, (int64_t)kNumPart * std::max(A->nblk, 1), w));
+        w->nblk64 = fp64_blocks(A);
+        SPK_TRY(dalloc(&w->partials, (int64_t)kNumPart * std::max({A->nblk, w->nblk64, 1}), w));
         SPK_TRY(dalloc(&w->r, A->n, w));
         SPK_TRY(dalloc(&w->z, A->n, w));
         SPK_TRY(dalloc(&w->p, A->n, w));
@@ -144,6 +159,12 @@ static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
             w->fused32 = fused_pays(A, kSellPlain32);
         }
         if (w->fused64) SPK_TRY(dalloc(&w->p2, A->n, w));
+        if (w->fused64 && w->nblk64 == A->ntiles && resident_fits(A)) {
+            SPK_TRY(dalloc(&w->res_slots, resident_slots(A), w));
+            SPK_TRY(dalloc(&w->res_gave_up, 1, w));
+            SPK_HIP(hipHostMalloc((void **)&w->res_pgave_up, sizeof(int32_t), hipHostMallocDefault));
+            w->resident = true;
+        }
         SPK_HIP(hipHostMalloc((void **)&w->pdesc, sizeof(SysDesc), hipHostMallocDefault));
         SPK_HIP(hipHostMalloc((void **)&w->pst, sizeof(SysState), hipHostMallocDefault));
         SPK_HIP(hipHostMalloc((void **)&w->pstatus, sizeof(int32_t) * 8, hipHostMallocDefault));
@@ -208,19 +229,21 @@ static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
 // product kernel alone, so it runs the three-kernel iteration: its
 // descriptor has no second p buffer (the results are the same bits).
 static bool use_fused(const Workspace *w, bool mixed) { return (mixed ? w->fused32 : w->fused64) && !w->prof; }
-static One batch_of(Workspace *w)
+static One batch_of(Workspace *w, bool mixed)
 {
     One b{w->hdesc};
+    if (!mixed) b.d.nblk = w->nblk64;
     if (!use_fused(w, false)) b.d.p2 = nullptr;
     if (!use_fused(w, true)) b.d.p2_32 = nullptr;
     return b;
 }
 
-// r = b - A x for the handle's kernel family.
-static int launch_resid(spk_mat *A, Workspace *w, int purpose, bool gated, hipStream_t s)
+// r = b - A x for the handle's kernel family (mixed: a mixed-precision
+// solve's partition).
+static int launch_resid(spk_mat *A, Workspace *w, bool mixed, int purpose, bool gated, hipStream_t s)
 {
-    const One b = batch_of(w);
-    const dim3 g(A->nblk), t(kBlock), one(1);
+    const One b = batch_of(w, mixed);
+    const dim3 g(b.d.nblk), t(kBlock), one(1);
     if (A->kernel == SPK_KERNEL_STREAM) {
         if (gated) hipLaunchKernelGGL((k_resid_stream<kGateResid, One>), g, t, 0, s, b);
         else hipLaunchKernelGGL((k_resid_stream<kGateNone, One>), g, t, 0, s, b);
@@ -263,8 +286,8 @@ static int prof_pair(Workspace *w, hipEvent_t *e0, hipEvent_t *e1)
 template <class V>
 static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
 {
-    const One b = batch_of(w);
-    const dim3 g(A->nblk), t(kBlock), one(1);
+    const One b = batch_of(w, Vecs<V>::mixed);
+    const dim3 g(b.d.nblk), t(kBlock), one(1);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (w->prof) {
         SPK_TRY(prof_pair(w, &e0, &e1));
@@ -312,8 +335,8 @@ static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
 template <class V, bool kStart>
 static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
 {
-    const One b = batch_of(w);
-    const dim3 g(A->nblk), t(kBlock);
+    const One b = batch_of(w, Vecs<V>::mixed);
+    const dim3 g(b.d.nblk), t(kBlock);
     with_sell(A, [&](auto ci, auto uc) {
         using CI = decltype(ci);
         constexpr int U = decltype(uc)::value;
@@ -328,11 +351,11 @@ static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
 static int enqueue_batch(spk_mat *A, Workspace *w, bool mixed, int K, hipStream_t s)
 {
     if (use_fused(w, mixed)) {
-        const One b = batch_of(w);
-        const dim3 g(A->nblk), t(kBlock);
+        const One b = batch_of(w, mixed);
+        const dim3 g(b.d.nblk), t(kBlock);
         if (mixed) {
             hipLaunchKernelGGL(k_update_x<One>, g, t, 0, s, b);
-            SPK_TRY(launch_resid(A, w, kResOuter, true, s));
+            SPK_TRY(launch_resid(A, w, true, kResOuter, true, s));
             hipLaunchKernelGGL(k_setup32<One>, g, t, 0, s, b);
             hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), t, 0, s, b);
             launch_fused<float, true>(A, w, s);
@@ -351,9 +374,9 @@ static int enqueue_batch(spk_mat *A, Workspace *w, bool mixed, int K, hipStream_
         return SPK_OK;
     }
     if (mixed) {
-        const One b = batch_of(w);
+        const One b = batch_of(w, true);
         hipLaunchKernelGGL(k_update_x<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
-        SPK_TRY(launch_resid(A, w, kResOuter, true, s));
+        SPK_TRY(launch_resid(A, w, true, kResOuter, true, s));
         hipLaunchKernelGGL(k_setup32<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
         hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), dim3(kBlock), 0, s, b);
         hipLaunchKernelGGL((k_pcg_p_continue<float, One>), dim3(A->nblk), dim3(kBlock), 0, s, b);
@@ -467,18 +490,32 @@ static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given
     const bool use_graph = o.graph_k > 0 && !w->prof;
     hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, s, w->st, o.rtol, o.atol, o.maxit, 0,
                        o.inner_rtol, o.inner_maxit, o.max_outer, hist_len);
-    SPK_TRY(launch_resid(A, w, kResSetup, false, s));
-    hipLaunchKernelGGL(k_setup64<One>, dim3(A->nblk), dim3(kBlock), 0, s, batch_of(w));
-    hipLaunchKernelGGL(k_fin_setup64<One>, dim3(1), dim3(kBlock), 0, s, batch_of(w));
+    const One b = batch_of(w, false);
+    const bool resident = w->resident && !w->prof;
+    SPK_TRY(launch_resid(A, w, false, kResSetup, false, s));
+    hipLaunchKernelGGL(k_setup64<One>, dim3(b.d.nblk), dim3(kBlock), 0, s, b);
+    hipLaunchKernelGGL(k_fin_setup64<One>, dim3(1), dim3(kBlock), 0, s, b);
     SPK_HIP(hipGetLastError());
     int restarts = 0;
     for (;;) {
+        bool ran = false;
+        if (resident) {
+            SPK_TRY(launch_resident(A, b.d, w->res_slots, w->res_gave_up, s, &ran));
+            if (ran)
+                SPK_HIP(hipMemcpyAsync(w->res_pgave_up, w->res_gave_up, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        }
+        if (!ran) {
+            SPK_TRY(read_state(w, s));
+            const int done_iter = w->pst->iter;
+            const int max_batches = (std::max(o.maxit - done_iter, 0) + K - 1) / K + 2;
+            if (w->pst->status == SPK_RUNNING) SPK_TRY(run_batches(A, w, false, K, use_graph, max_batches, s));
+        }
+        SPK_TRY(launch_resid(A, w, false, kResTrue, false, s));
         SPK_TRY(read_state(w, s));
-        const int done_iter = w->pst->iter;
-        const int max_batches = (std::max(o.maxit - done_iter, 0) + K - 1) / K + 2;
-        if (w->pst->status == SPK_RUNNING) SPK_TRY(run_batches(A, w, false, K, use_graph, max_batches, s));
-        SPK_TRY(launch_resid(A, w, kResTrue, false, s));
-        SPK_TRY(read_state(w, s));
+        if (ran && *w->res_pgave_up) {
+            set_error("the solve's blocks lost each other");
+            return SPK_EHIP;
+        }
         const SysState &S = *w->pst;
         const bool conv = S.status == SPK_CONVERGED_RTOL || S.status == SPK_CONVERGED_ATOL;
         if (conv && S.bnorm > 0 && S.iter > 0 && S.rnorm_true > S.thresh) {
@@ -488,8 +525,8 @@ static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given
             }
             ++restarts;
             hipLaunchKernelGGL(k_state_restart, dim3(1), dim3(64), 0, s, w->st);
-            hipLaunchKernelGGL(k_setup64<One>, dim3(A->nblk), dim3(kBlock), 0, s, batch_of(w));
-            hipLaunchKernelGGL(k_fin_setup64<One>, dim3(1), dim3(kBlock), 0, s, batch_of(w));
+            hipLaunchKernelGGL(k_setup64<One>, dim3(b.d.nblk), dim3(kBlock), 0, s, b);
+            hipLaunchKernelGGL(k_fin_setup64<One>, dim3(1), dim3(kBlock), 0, s, b);
             SPK_HIP(hipGetLastError());
             continue;
         }
@@ -524,7 +561,7 @@ static int solve_mixed(spk_mat *A, Workspace *w, const spk_ksp_opts &o, int hist
     SPK_HIP(hipGetLastError());
     const int max_batches = (o.maxit + K - 1) / K + 2 * (o.max_outer + 2);
     SPK_TRY(run_batches(A, w, true, K, use_graph, max_batches, s));
-    SPK_TRY(launch_resid(A, w, kResTrue, false, s));
+    SPK_TRY(launch_resid(A, w, true, kResTrue, false, s));
     SPK_TRY(read_state(w, s));
     const SysState &S = *w->pst;
     out->reason = S.status;
@@ -616,7 +653,7 @@ static int solve_sr(spk_mat *A, Workspace *w, const spk_ksp_opts &o, int hist_le
     const bool use_graph = o.graph_k > 0;
     hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, s, w->st, o.rtol, o.atol, o.maxit, 0,
                        o.inner_rtol, o.inner_maxit, o.max_outer, hist_len);
-    SPK_TRY(launch_resid(A, w, kResSetup, false, s));
+    SPK_TRY(launch_resid(A, w, true, kResSetup, false, s));
     SPK_TRY(sr_start(A, w, a, 0, s));
     if (use_graph && (!w->gsr || w->gsr_k != K)) {
         if (w->gsr) { hipGraphExecDestroy(w->gsr); w->gsr = nullptr; }
@@ -659,7 +696,7 @@ static int solve_sr(spk_mat *A, Workspace *w, const spk_ksp_opts &o, int hist_le
             }
             SPK_HIP(hipStreamSynchronize(s));
         }
-        SPK_TRY(launch_resid(A, w, kResTrue, false, s));
+        SPK_TRY(launch_resid(A, w, true, kResTrue, false, s));
         SPK_TRY(read_state(w, s));
         const SysState &S = *w->pst;
         const bool conv = S.status == SPK_CONVERGED_RTOL || S.status == SPK_CONVERGED_ATOL;

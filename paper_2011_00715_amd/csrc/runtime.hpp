@@ -45,6 +45,17 @@ inline int sell_load_policy(int64_t stored, int cw, int nslices, int n, int vect
     return bits;
 }
 
+// Blocks of the PCG kernels of one SELL system (product with its p.q
+// partials, update, p/x pass).  Every block of the update and p/x passes
+// sums all blocks' partials, so fewer, larger blocks cut that L2 traffic;
+// measured on the 7-point 128^3 / 27-point 160^3 systems against caps of
+// 512, 1536 and 2048 (same box, two rounds each): 1024 gave the fastest FP64
+// and FP32 iterations overall (FP64 66.3 -> 64.4 us and 288.4 -> 286.0 us
+// per iteration against 2048).  The other families keep 2048: their
+// products use the block count too, and the stream-tile SpMV of the
+// power-law matrix took 2693 us on 1024 blocks against 2138 us on 2048.
+constexpr int kPcgBlocksSell = 1024;
+
 // Solver workspace of one matrix (allocated on the first solve).
 struct Workspace {
     int n = 0;
@@ -80,6 +91,13 @@ struct Workspace {
     double *srp = nullptr;        // 2 sets x 3 partial arrays x nblk
     void *sc = nullptr;           // device scalars of the single-reduction recurrences
     int64_t bytes = 0;
+    int nblk64 = 0;               // blocks of an FP64 solve (fp64_blocks)
+    // iterations in one launch (small systems): the blocks' meeting slots and
+    // the flag of a wait that ran out, with a pinned copy
+    bool resident = false;
+    unsigned long long *res_slots = nullptr;
+    int32_t *res_gave_up = nullptr;
+    int32_t *res_pgave_up = nullptr;
     // profiled solves: one event pair around each iteration's product, in
     // launch order; `alive` is cleared for launches queued after the solve
     // had stopped
@@ -176,6 +194,11 @@ int launch_spmv(const spk_mat *A, const V *val, const V *x, V *y, hipStream_t s,
                 const SysState *gate_st, int gate_mode);
 
 void update_info(spk_mat *A);
+// iterations of small FP64 solves in one launch (resident.hip)
+bool resident_fits(const spk_mat *A);
+int64_t resident_slots(const spk_mat *A);
+int launch_resident(const spk_mat *A, const SysDesc &d, unsigned long long *slots, int32_t *gave_up, hipStream_t s,
+                    bool *done);
 constexpr double kRuDelta = 0.05;  // default refinement trigger with reliable updates
 double inner_rtol_of(const spk_ksp_opts &o);
 int ensure_f32(spk_mat *A, hipStream_t s);

@@ -401,3 +401,60 @@ def test_pcg_single_reduction_graph_direct_and_reasons():
     assert r.iterations == 0 and np.array_equal(x, xs)
     with pytest.raises(spk.SpkError):
         _solve(spk, M2, xs, single_reduction=1, precision=spk.PREC_MIXED)
+
+
+@pytest.mark.parametrize("offs,n", [([1], 1), ([1], 2), ([1], 64), ([1, 7], 257), ([1, 7], 2048), ([1, 7, 30], 2049),
+                                    ([1, 7, 30], 4095), ([1, 7, 30], 4096), ([1, 7, 30], 4097), ([1, 7], 4608),
+                                    ([1, 2, 7, 300], 4609), ([1, 2, 7, 300], 20481), ([1, 900], 65536),
+                                    ([1, 900], 262144), ([1, 900], 262145), ([1, 4000], 262100)])
+@pytest.mark.parametrize("layout", [0, 1, 16, 32])
+def test_pcg_one_launch_same_bits(offs, n, layout):
+    """Small FP64 systems iterate in one launch (one block up to 4096 rows, one
+    block per two tiles up to 2^18): solution, counts and history are those of
+    the launched iteration that a profiled solve runs, bit for bit; the oracle
+    agrees where it is quick."""
+    spk = need_gpu()
+    if layout == 0 and n <= 20481:  # constant coefficients: one value per offset
+        A = spkgen.laplace_grid((n,), 0.25)
+    else:
+        A = spkgen.banded_spd(n, [o for o in offs if o < n] or [1], seed=n, margin=0.1)
+    M = mat_on_gpu(spk, A)
+    try:
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, layout)
+    except spk.SpkError:
+        assert layout == 1  # a slice's list is too long beside its rows
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, 0)
+    b = spkgen.rhs_uniform(n, 4)
+    x, res, hist = _solve(spk, M, b, hist_len=200)
+    xp, rp, hp = _solve(spk, M, b, hist_len=200, profile=1)
+    assert res.reason == spk.CONVERGED_RTOL, res.as_dict()
+    assert np.array_equal(x, xp) and np.array_equal(hist, hp, equal_nan=True)
+    assert (res.iterations, res.restarts, res.rnorm) == (rp.iterations, rp.restarts, rp.rnorm)
+    if n <= 4608:
+        xo, ro, _ = oracle.pcg(A, b)
+        assert abs(res.iterations - ro["iterations"]) <= max(2, 0.01 * ro["iterations"])
+        assert np.linalg.norm(x - xo) <= 1e-5 * np.linalg.norm(xo)
+    M.close()
+
+
+@pytest.mark.parametrize("n", [700, 9000])
+def test_pcg_one_launch_stops(n):
+    """Every way to stop: iteration limits, an indefinite matrix, NaN, a zero
+    right-hand side, an unreachable tolerance (restarts)."""
+    spk = need_gpu()
+    A = spkgen.laplace_grid((n,), 0.05)
+    b = spkgen.rhs_uniform(n, 1)
+    r = np.repeat(np.arange(n), np.diff(A.rowptr))
+    indef = A.val.copy()
+    indef[(A.col == r) & (r == n // 2)] = -1.0
+    bad = b.copy()
+    bad[n // 3] = np.nan
+    for val, rhs, kw in ((A.val, b, {"maxit": 0}), (A.val, b, {"maxit": 1}), (A.val, b, {"maxit": 17}),
+                         (indef, b, {}), (A.val, bad, {}), (A.val, np.zeros(n), {}),
+                         (A.val, b, {"rtol": 1e-17, "maxit": 3000})):
+        M = mat_on_gpu(spk, spkgen.CSR(n, A.rowptr, A.col, val))
+        out = [_solve(spk, M, rhs, hist_len=64, profile=prof, **kw) for prof in (0, 1)]
+        (x, ra, ha), (y, rb, hb) = out
+        assert np.array_equal(x, y, equal_nan=True) and np.array_equal(ha, hb, equal_nan=True)
+        assert (ra.reason, ra.iterations, ra.restarts) == (rb.reason, rb.iterations, rb.restarts)
+        M.close()
