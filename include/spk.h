@@ -472,7 +472,8 @@ int spk_mg_profile(spk_mg *M, const double *b, double *x, int32_t reps, double *
 /* CG preconditioned by one cycle per iteration, FP64, with the stopping
  * rules, breakdown reasons, true-residual restarts and history of
  * spk_ksp_solve (precision must be SPK_PREC_FP64 and single_reduction 0).
- * graph_k iterations are captured per graph (0: no graph).  b, x: device
+ * one iteration is captured per graph (graph_k
+ * 0: no graph).  b, x: device
  * double[n] as in spk_ksp_solve.  Returns when the result is known. */
 int spk_ksp_solve_mg(spk_mg *M, const double *b, double *x, const spk_ksp_opts *opts,
                      spk_ksp_result *res, void *stream);

@@ -44,7 +44,7 @@ __global__ void k_row_stats(int n, int64_t nnz, const int32_t *__restrict__ rowp
     if (threadIdx.x < 6) tmax[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long a1 = 0, a2 = 0;
-    int amx = 0, amn = 0x7fffffff, abad = 0;
+    int amx = 0, amn = 0x7fffffff, abad = 0, bin0 = 0, cnt = 0;
     int at[6] = {0, 0, 0, 0, 0, 0};
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int64_t a = rowptr[i], e = rowptr[i + 1];
@@ -58,7 +58,12 @@ __global__ void k_row_stats(int n, int64_t nnz, const int32_t *__restrict__ rowp
         amx = max(amx, len);
         amn = min(amn, len);
         const int bin = len == 0 ? 0 : 32 - __clz(len);
-        atomicAdd(&hist[bin], 1);
+        if (bin != bin0) {  // a thread's rows mostly fall into one bin
+            if (cnt) atomicAdd(&hist[bin0], cnt);
+            bin0 = bin;
+            cnt = 0;
+        }
+        ++cnt;
 #pragma unroll
         for (int t = 0; t < 6; ++t) {
             const int R = t == 0 ? 256 : (t == 1 ? 128 : (t == 2 ? 64 : (t == 3 ? 32 : (t == 4 ? 16 : 8))));
@@ -69,13 +74,35 @@ __global__ void k_row_stats(int n, int64_t nnz, const int32_t *__restrict__ rowp
             }
         }
     }
-    atomicAdd(&s1, a1);
-    atomicAdd(&s2, a2);
-    atomicMax(&mx, amx);
-    atomicMin(&mn, amn);
-    atomicAdd(&bad, abad);
+    // one lane per wavefront: on one LDS address the atomics of a block's
+    // threads queue up (192 us of 7-point 128^3)
+    auto wsum = [](unsigned long long v) {
 #pragma unroll
-    for (int t = 0; t < 6; ++t) atomicMax(&tmax[t], at[t]);
+        for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+        return v;
+    };
+    auto wmax = [](int v) {
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
+        return v;
+    };
+    a1 = wsum(a1);
+    a2 = wsum(a2);
+    abad = (int)wsum((unsigned long long)abad);
+    amx = wmax(amx);
+    amn = -wmax(-amn);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) at[t] = wmax(at[t]);
+    if (cnt) atomicAdd(&hist[bin0], cnt);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&s1, a1);
+        atomicAdd(&s2, a2);
+        atomicMax(&mx, amx);
+        atomicMin(&mn, amn);
+        atomicAdd(&bad, abad);
+#pragma unroll
+        for (int t = 0; t < 6; ++t) atomicMax(&tmax[t], at[t]);
+    }
     __syncthreads();
     if (threadIdx.x < 33 && hist[threadIdx.x]) atomicAdd(&out->hist[threadIdx.x], hist[threadIdx.x]);
     if (threadIdx.x < 6) atomicMax(&out->tile_max[threadIdx.x], tmax[threadIdx.x]);

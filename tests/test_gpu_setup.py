@@ -181,3 +181,29 @@ def test_uniform_values_offset_limit(distinct):
     spk.mat_mult(M, to_dev(x), y)
     assert np.array_equal(y.cpu().numpy(), oracle.spmv(A, x))
     M.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 64, 65, 95, 343, 1000])
+def test_coarsest_inverse_blocks(n):
+    """The coarsest level alone (one level): the cycle is the dense inverse,
+    formed 32 columns a step; remainders of the steps and tiles, and the pivot
+    test in the first, a middle and the last step."""
+    import torch
+
+    spk = need_gpu()
+    A = spkgen.laplace_grid((n,), 0.3)
+    D = spkgen.to_dense(A)
+    b = spkgen.rhs_uniform(n, 5)
+    with mat_on_gpu(spk, A) as M, spk.mg_create(M, (n,), spk.mg_opts(max_levels=1, coarse_max=4096)) as H:
+        x = torch.full((n,), np.nan, dtype=torch.float64, device="cuda")
+        spk.mg_apply(H, to_dev(b), x)
+        # condition below 20: the inverse's error stays below n kappa u of the largest entry
+        assert np.max(np.abs(x.cpu().numpy() - np.linalg.solve(D, b))) <= n * 20 * 2.0 ** -50
+    r = np.repeat(np.arange(n), np.diff(A.rowptr))
+    for at in {0, n // 2, n - 1}:
+        val = A.val.copy()
+        val[(A.col == r) & (r == at)] = -0.5
+        with mat_on_gpu(spk, spkgen.CSR(n, A.rowptr, A.col, val)) as M:
+            with pytest.raises(spk.SpkError) as e:
+                spk.mg_create(M, (n,), spk.mg_opts(max_levels=1, coarse_max=4096))
+            assert e.value.status == spk.EINVAL
