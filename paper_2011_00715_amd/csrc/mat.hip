@@ -908,16 +908,22 @@ static int create_impl(int32_t n, int64_t nnz, const int32_t *rowptr, const int3
     A->stream_loads = (flags & SPK_MAT_STREAM) != 0;
     SPK_HIP(hipGetDevice(&A->device));
     const bool borrow = (flags & SPK_MAT_BORROW) != 0;
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t nzb = nnz > 0 ? (size_t)nnz : 1;
+    const size_t b_val = borrow ? 0 : up(sizeof(double) * nzb), b_col = borrow ? 0 : up(sizeof(int32_t) * nzb),
+                 b_ptr = borrow ? 0 : up(sizeof(int32_t) * ((size_t)n + 1)), b_inv = sizeof(double) * (n > 0 ? n : 1);
+    SPK_HIP(hipMalloc(&A->slab, b_val + b_col + b_ptr + b_inv));
+    char *slab = (char *)A->slab;
+    A->dinv = (double *)(slab + b_val + b_col + b_ptr);
     if (borrow) {
         A->own_csr = false;
         A->rowptr = const_cast<int32_t *>(rowptr);
         A->col = const_cast<int32_t *>(colind);
         A->val = const_cast<double *>(values);
     } else {
-        SPK_HIP(hipMalloc(&A->rowptr, sizeof(int32_t) * ((size_t)n + 1)));
-        SPK_HIP(hipMalloc(&A->col, sizeof(int32_t) * nzb));
-        SPK_HIP(hipMalloc(&A->val, sizeof(double) * nzb));
+        A->val = (double *)slab;
+        A->col = (int32_t *)(slab + b_val);
+        A->rowptr = (int32_t *)(slab + b_val + b_col);
         A->bytes += 4 * ((int64_t)n + 1) + 12 * nnz;
         const hipMemcpyKind kind = memtype == SPK_MEM_HOST ? hipMemcpyHostToDevice
                                                            : hipMemcpyDeviceToDevice;
@@ -951,7 +957,6 @@ static int create_impl(int32_t n, int64_t nnz, const int32_t *rowptr, const int3
             }
         }
     }
-    SPK_HIP(hipMalloc(&A->dinv, sizeof(double) * (n > 0 ? n : 1)));
     A->bytes += 8 * (int64_t)n;
 
     // statistics + structural checks (memory safety of every later kernel)
@@ -1268,13 +1273,8 @@ int spk_mat_destroy(spk_mat *A)
     hipStreamSynchronize(A->stream);
     free_workspace(A);
     free_multi(A);
-    if (A->own_csr) {
-        hipFree(A->rowptr);
-        hipFree(A->col);
-        hipFree(A->val);
-    }
+    hipFree(A->slab);
     hipFree(A->val32);
-    hipFree(A->dinv);
     hipFree(A->dinv32);
     hipFree(A->tile_row);
     hipFree(A->tile_k);

@@ -61,7 +61,12 @@ struct spk_mg {
     spk::MgLevel lev[spk::kMgMaxLevels];
     int f32 = 0;             // 1: the cycle runs in FP32 (values, vectors, arithmetic)
     void *cinv = nullptr;    // dense inverse of the coarsest matrix, row-major, cycle precision
-    // solve workspace (allocated on first solve)
+    // the levels' vectors, one allocation (null while their sizes are added up)
+    char *slab = nullptr;
+    int64_t slab_used = 0;
+    int solves = 0;
+    // solve workspace (allocated on first solve, one allocation)
+    char *ws = nullptr;
     double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *x = nullptr, *b = nullptr;
     double *tmp64 = nullptr; // FP64 SpMV output of the unfused families
     double *part = nullptr;  // 4 x kMgMaxPart partial sums
@@ -112,13 +117,11 @@ static int mg_alloc(spk_mg *M, T **p, int64_t count)
     return SPK_OK;
 }
 
-// A cycle vector of n entries (8 or 4 bytes each).
-static int mg_vec(spk_mg *M, void **p, int64_t n)
+// The next cycle vector of the slab: n entries (8 or 4 bytes each).
+static void mg_vec(spk_mg *M, void **p, int64_t n)
 {
-    const size_t b = (M->f32 ? 4 : 8) * (size_t)(n > 0 ? n : 1);
-    SPK_HIP(hipMalloc(p, b));
-    M->bytes += (int64_t)b;
-    return SPK_OK;
+    *p = M->slab ? M->slab + M->slab_used : nullptr;
+    M->slab_used += ((M->f32 ? 4 : 8) * (n > 0 ? n : 1) + 255) & ~(int64_t)255;
 }
 
 template <class V>
@@ -383,24 +386,33 @@ static int run_cycle(spk_mg *M, const CycleIo &io, const SysState *gate, hipStre
     return enqueue_cycle<double>(M, 0, false, false, false, gate, s, &io);
 }
 
-static int alloc_level_vectors(spk_mg *M, int l)
+static void place_level_vectors(spk_mg *M, int l)
 {
     MgLevel &L = M->lev[l];
     if (l > 0 || M->f32) {  // an FP64 cycle uses the call's arrays on level 0
-        SPK_TRY(mg_vec(M, &L.b, L.n));
-        SPK_TRY(mg_vec(M, &L.x, L.n));
+        mg_vec(M, &L.b, L.n);
+        mg_vec(M, &L.x, L.n);
     }
     if (l < M->nlev - 1) {
-        SPK_TRY(mg_vec(M, &L.r, L.n));
-        SPK_TRY(mg_vec(M, &L.d0, L.n));
-        SPK_TRY(mg_vec(M, &L.d1, L.n));
-        if (l > 0) SPK_TRY(mg_vec(M, &L.x2, L.n));
+        mg_vec(M, &L.r, L.n);
+        mg_vec(M, &L.d0, L.n);
+        mg_vec(M, &L.d1, L.n);
+        if (l > 0) mg_vec(M, &L.x2, L.n);
         // level 0's family may change later (spk_mat_set_kernel on the caller's matrix)
-        if (l == 0 || (L.A->kernel != SPK_KERNEL_SELL && L.A->kernel != SPK_KERNEL_STREAM))
-            SPK_TRY(mg_vec(M, &L.tmp, L.n));
+        if (l == 0 || (L.A->kernel != SPK_KERNEL_SELL && L.A->kernel != SPK_KERNEL_STREAM)) mg_vec(M, &L.tmp, L.n);
     } else if (l == 0) {
-        SPK_TRY(mg_vec(M, &L.tmp, L.n));
+        mg_vec(M, &L.tmp, L.n);
     }
+}
+
+static int alloc_level_vectors(spk_mg *M)
+{
+    for (int l = 0; l < M->nlev; ++l) place_level_vectors(M, l);
+    const int64_t need = M->slab_used;
+    M->slab_used = 0;
+    SPK_HIP(hipMalloc((void **)&M->slab, need > 0 ? need : 1));
+    M->bytes += need;
+    for (int l = 0; l < M->nlev; ++l) place_level_vectors(M, l);
     return SPK_OK;
 }
 
@@ -514,28 +526,12 @@ static void destroy_mg(spk_mg *M)
     hipStreamSynchronize(M->stream);
     for (int l = 0; l < M->nlev; ++l) {
         MgLevel &L = M->lev[l];
-        if (l > 0 || M->f32) {
-            hipFree(L.b);
-            hipFree(L.x);
-        }
         if (l > 0) spk_mat_destroy(L.A);
-        hipFree(L.r);
-        hipFree(L.d0);
-        hipFree(L.d1);
-        hipFree(L.x2);
-        hipFree(L.tmp);
     }
+    hipFree(M->slab);
     hipFree(M->cinv);
-    hipFree(M->r);
-    hipFree(M->z);
-    hipFree(M->p);
-    hipFree(M->q);
-    hipFree(M->x);
-    hipFree(M->b);
-    hipFree(M->tmp64);
-    hipFree(M->part);
+    hipFree(M->ws);
     hipFree(M->hist);
-    hipFree(M->st);
     hipHostFree(M->pst);
     hipHostFree(M->pstatus);
     for (auto &e : M->ev)
@@ -605,8 +601,8 @@ static int setup(spk_mg *M, spk_mat *A, const int32_t *shape, hipStream_t s)
             SPK_HIP(hipStreamSynchronize(s));
             L.A->info.has_f32 = 1;
         }
-        SPK_TRY(alloc_level_vectors(M, l));
     }
+    SPK_TRY(alloc_level_vectors(M));
     SPK_TRY(invert_coarsest(M, s));
     SPK_HIP(hipStreamCreateWithFlags(&M->cap, hipStreamNonBlocking));
     return SPK_OK;
@@ -617,15 +613,12 @@ static int get_solve_ws(spk_mg *M, int hist_len)
 {
     const int n = M->lev[0].n;
     if (!M->r) {
-        SPK_TRY(mg_alloc(M, &M->r, n));
-        SPK_TRY(mg_alloc(M, &M->z, n));
-        SPK_TRY(mg_alloc(M, &M->p, n));
-        SPK_TRY(mg_alloc(M, &M->q, n));
-        SPK_TRY(mg_alloc(M, &M->x, n));
-        SPK_TRY(mg_alloc(M, &M->b, n));
-        SPK_TRY(mg_alloc(M, &M->tmp64, n));
-        SPK_TRY(mg_alloc(M, &M->part, 4 * (int64_t)kMgMaxPart));
-        SPK_TRY(mg_alloc(M, &M->st, 1));
+        const int64_t nb = (8 * (int64_t)n + 255) & ~255ll;
+        SPK_TRY(mg_alloc(M, &M->ws, 7 * nb + 32 * (int64_t)kMgMaxPart + (int64_t)sizeof(SysState)));
+        double **vec[7] = {&M->r, &M->z, &M->p, &M->q, &M->x, &M->b, &M->tmp64};
+        for (int i = 0; i < 7; ++i) *vec[i] = (double *)(M->ws + i * nb);
+        M->part = (double *)(M->ws + 7 * nb);
+        M->st = (SysState *)(M->part + 4 * (int64_t)kMgMaxPart);
         SPK_HIP(hipHostMalloc((void **)&M->pst, sizeof(SysState), hipHostMallocDefault));
         SPK_HIP(hipHostMalloc((void **)&M->pstatus, sizeof(int32_t) * 8, hipHostMallocDefault));
         for (auto &e : M->ev) SPK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -781,7 +774,9 @@ static int solve(spk_mg *M, const double *b, double *x, const spk_ksp_opts &o, s
     // above 0: a longer graph only adds gated launches after the last
     // iteration (128^3: 3.89 ms a solve with 8, 3.44 with 1)
     const int K = 1;
-    const bool use_graph = o.graph_k > 0;
+    // a hierarchy's first solve launches its iterations: many live for one
+    // solve, and capturing a graph and destroying it take 2.5 ms there
+    const bool use_graph = o.graph_k > 0 && M->solves++ > 0;
     int restarts = 0;
     bool have_true = false;
     for (;;) {

@@ -117,6 +117,9 @@ struct spk_mat {
     int32_t n = 0;
     int64_t nnz = 0;
     int device = 0;
+    // owned CSR and D^-1, one allocation: past a few MB a hipMalloc takes 0.1 to
+    // 0.3 ms and a hipFree of used memory as much, whatever their size
+    void *slab = nullptr;
     int32_t *rowptr = nullptr;
     int32_t *col = nullptr;
     double *val = nullptr;
