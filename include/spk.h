@@ -472,9 +472,9 @@ int spk_mg_profile(spk_mg *M, const double *b, double *x, int32_t reps, double *
 /* CG preconditioned by one cycle per iteration, FP64, with the stopping
  * rules, breakdown reasons, true-residual restarts and history of
  * spk_ksp_solve (precision must be SPK_PREC_FP64 and single_reduction 0).
- * one iteration is captured per graph (graph_k
- * 0: no graph).  b, x: device
- * double[n] as in spk_ksp_solve.  Returns when the result is known. */
+ * From the second solve on a hierarchy on, an iteration is replayed from a
+ * graph (graph_k 0: never).  b, x: device double[n] as in spk_ksp_solve.
+ * Returns when the result is known. */
 int spk_ksp_solve_mg(spk_mg *M, const double *b, double *x, const spk_ksp_opts *opts,
                      spk_ksp_result *res, void *stream);
 int spk_mg_destroy(spk_mg *M);
