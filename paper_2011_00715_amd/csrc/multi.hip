@@ -12,7 +12,7 @@ namespace spk {
 struct MultiWs {
     int K = 0;
     int nblk = 0;
-    double *B = nullptr, *X = nullptr, *R = nullptr, *Z = nullptr, *P = nullptr, *Q = nullptr;
+    double *B = nullptr, *X = nullptr, *R = nullptr, *P = nullptr, *Q = nullptr;
     double *partials = nullptr;
     SysState *st = nullptr;
     SysState *pst = nullptr;  // pinned copy of the K states
@@ -36,7 +36,6 @@ void free_multi(spk_mat *A)
     hipFree(w->B);
     hipFree(w->X);
     hipFree(w->R);
-    hipFree(w->Z);
     hipFree(w->P);
     hipFree(w->Q);
     hipFree(w->partials);
@@ -95,6 +94,18 @@ static void with_multi(const spk_mat *A, int K, F &&f)
     }
 }
 
+// Calls f(integral_constant W) for the positions that the stencil walk keeps in
+// registers: the list's length where it is a short one of the usual stencils
+// (five, seven, nine points), else rounds of nine.
+template <class F>
+static void with_width(const spk_mat *A, F &&f)
+{
+    const int w = A->sell_plain >> kSellWidthShift;
+    if (w <= 5) f(std::integral_constant<int, 5>{});
+    else if (w <= 7) f(std::integral_constant<int, 7>{});
+    else f(std::integral_constant<int, 9>{});
+}
+
 static int get_multi(spk_mat *A, int K, MultiWs **out)
 {
     MultiWs *w = A->mws;
@@ -109,7 +120,7 @@ static int get_multi(spk_mat *A, int K, MultiWs **out)
         w->K = K;
         w->nblk = multi_nblk(A);
         const size_t nk = sizeof(double) * (size_t)std::max(A->n, 1) * K;
-        for (double **p : {&w->B, &w->X, &w->R, &w->Z, &w->P, &w->Q}) SPK_HIP(hipMalloc((void **)p, nk));
+        for (double **p : {&w->B, &w->X, &w->R, &w->P, &w->Q}) SPK_HIP(hipMalloc((void **)p, nk));
         SPK_HIP(hipMalloc((void **)&w->partials, sizeof(double) * kNumPart * K * std::max(multi_nblk(A), 1)));
         SPK_HIP(hipMalloc((void **)&w->st, sizeof(SysState) * K));
         SPK_HIP(hipMalloc((void **)&w->ctl, sizeof(MultiCtl)));
@@ -128,7 +139,6 @@ static MultiDesc solve_desc(const spk_mat *A, MultiWs *w)
     d.B = w->B;
     d.X = w->X;
     d.Rv = w->R;
-    d.Z = w->Z;
     d.P = w->P;
     d.Q = w->Q;
     d.partials = w->partials;
@@ -146,7 +156,11 @@ static void enqueue_multi_iter(const spk_mat *A, const MultiDesc &d, hipStream_t
     with_multi(A, d.K, [&](auto ct, auto kc) {
         using CI = decltype(ct);
         constexpr int K = decltype(kc)::value;
-        hipLaunchKernelGGL((k_m_spmm_pq<CI, K>), g, t, 0, s, d);
+        if constexpr (std::is_same<CI, Stencil>::value && K > 1)
+            with_width(A, [&](auto wc) {
+                hipLaunchKernelGGL((k_m_spmm_pq_stencil<K, decltype(wc)::value>), g, t, 0, s, d);
+            });
+        else hipLaunchKernelGGL((k_m_spmm_pq<CI, K>), g, t, 0, s, d);
         hipLaunchKernelGGL(k_m_fin_pq, cols, t, 0, s, d);
         hipLaunchKernelGGL((k_m_update<K>), g, t, 0, s, d);
         hipLaunchKernelGGL(k_m_fin_update, cols, t, 0, s, d);
@@ -238,9 +252,19 @@ int spk_mat_mult_multi(const spk_mat *A, int32_t k, const double *X, double *Y, 
     if (d.sell) d.nblk = std::max(1, std::min(ceil_div(ceil_div(A->n, kSell), kBlock / kWave), 16384));
     hipStream_t s = (hipStream_t)stream;
     A->stream = s;
+    const bool aligned = (((uintptr_t)X | (uintptr_t)Y) & 15) == 0;
     with_multi(A, k, [&](auto ct, auto kc) {
         using CI = decltype(ct);
         constexpr int K = decltype(kc)::value;
+        if constexpr (std::is_same<CI, Stencil>::value && K > 1) {
+            if (aligned) {
+                with_width(A, [&](auto wc) {
+                    hipLaunchKernelGGL((k_spmm_stencil<K, decltype(wc)::value>), dim3(d.nblk), dim3(kBlock), 0, s,
+                                       d, X, Y);
+                });
+                return;
+            }
+        }
         hipLaunchKernelGGL((k_spmm<CI, K>), dim3(d.nblk), dim3(kBlock), 0, s, d, X, Y);
     });
     SPK_HIP(hipGetLastError());

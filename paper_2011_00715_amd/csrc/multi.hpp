@@ -37,7 +37,7 @@ struct MultiDesc {
     SellView sv;
     const double *sell_val;
     const double *B;
-    double *X, *Rv, *Z, *P, *Q;  // n x K each
+    double *X, *Rv, *P, *Q;      // n x K each
     double *partials;            // [kNumPart][K][nblk]
     SysState *st;                // K states
     MultiCtl *ctl;
@@ -386,18 +386,33 @@ __device__ __forceinline__ void block_partials(double v[K], double *sh /* [4][K]
     }
 }
 
-// Block sums when lane t always holds column t % K (flat n x K element
-// walks with a stride that is a multiple of K): lanes of one column are
-// combined by the butterfly levels at distances >= K, then the waves in order.
+// Two elements of the flat n x K layout (one where K is 1): a lane's columns are
+// kCols * (t % (K / kCols)) and, for two, the next one, in every walk below.
 template <int K>
-__device__ __forceinline__ void block_partials_flat(double v, double *sh /* [4][K] */, double *part,
+struct Flat {
+    static constexpr int kCols = K > 1 ? 2 : 1;
+    static constexpr int kLanes = K / kCols;  // lanes per row
+    typedef double Elem __attribute__((ext_vector_type(kCols)));
+    static __device__ __forceinline__ int col(int t) { return t % kLanes * kCols; }
+};
+
+// Block sums per column of what the lanes hold for their columns: lanes of one
+// column are combined by the butterfly levels at distances >= kLanes, then the
+// waves in order.
+template <int K>
+__device__ __forceinline__ void block_partials_elem(typename Flat<K>::Elem v, double *sh /* [4][K] */, double *part,
                                                     int nblk, int j)
 {
-#pragma unroll
-    for (int off = kWave / 2; off >= K; off >>= 1) v += __shfl_xor(v, off, kWave);
+    constexpr int C = Flat<K>::kCols, L = Flat<K>::kLanes;
     const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int off = kWave / 2; off >= L; off >>= 1)
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] += __shfl_xor(v[c], off, kWave);
     __syncthreads();
-    if (lane < K) sh[w * K + lane] = v;
+    if (lane < L)
+#pragma unroll
+        for (int c = 0; c < C; ++c) sh[w * K + lane * C + c] = v[c];
     __syncthreads();
     if ((int)threadIdx.x < K) {
         const int q = threadIdx.x;
@@ -408,47 +423,134 @@ __device__ __forceinline__ void block_partials_flat(double v, double *sh /* [4][
     }
 }
 
-// Elements [rb K, re K) of the block's rows in the flat n x K layout, with
-// the lane's fixed column q = threadIdx.x % K; fn(e, i) for element e of row i.
-template <int K, class Fn>
-__device__ __forceinline__ void flat_walk(const MultiDesc &d, int j, Fn &&fn)
+// Elements [e0, e1) of the flat layout (multiples of K), kCols at a time with a
+// stride of kBlock lanes: ld(t, i) loads what lane-element t of row i needs,
+// st(t, v) uses it; a chunk's loads are issued before its stores.
+template <int K, class Ld, class St>
+__device__ __forceinline__ void flat_walk(int64_t e0, int64_t e1, Ld &&ld, St &&st)
 {
-    int t0, t1;
-    block_tiles(j, d.nblk, d.ntiles, t0, t1);
-    const int64_t e0 = (int64_t)t0 * d.R * K, e1 = (int64_t)min(t1 * d.R, d.n) * K;
-    constexpr int U = 4;
-    for (int64_t eb = e0 + threadIdx.x; eb < e1; eb += (int64_t)kBlock * U) {
+    constexpr int U = 4, C = Flat<K>::kCols;
+    using T = decltype(ld(int64_t(0), int64_t(0)));
+    const int64_t t0 = e0 / C, t1 = e1 / C;
+    for (int64_t tb = t0 + threadIdx.x; tb < t1; tb += (int64_t)kBlock * U) {
+        T v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t e = eb + (int64_t)u * kBlock;
-            if (e < e1) fn(e, (int)(e / K));
+            const int64_t t = min(tb + (int64_t)u * kBlock, t1 - 1);  // past the end: the last one, unused
+            v[u] = ld(t, t / Flat<K>::kLanes);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t t = tb + (int64_t)u * kBlock;
+            if (t < t1) st(t, v[u]);
         }
     }
 }
 
-// flat_walk with every load of a chunk issued before its stores: ld(e)
-// returns what element e needs, st(e, v) writes it back.  Used where a store
-// is conditional per lane, which otherwise keeps the compiler from moving
-// the next element's loads above it.
-template <int K, class Ld, class St>
-__device__ __forceinline__ void flat_walk_batched(const MultiDesc &d, int j, Ld &&ld, St &&st)
+// The flat range of block j's rows.
+__device__ __forceinline__ void flat_range(const MultiDesc &d, int j, int64_t &e0, int64_t &e1)
 {
     int t0, t1;
     block_tiles(j, d.nblk, d.ntiles, t0, t1);
-    const int64_t e0 = (int64_t)t0 * d.R * K, e1 = (int64_t)min(t1 * d.R, d.n) * K;
-    constexpr int U = 4;
-    using T = decltype(ld(int64_t(0)));
-    for (int64_t eb = e0 + threadIdx.x; eb < e1; eb += (int64_t)kBlock * U) {
-        T v[U];
+    e0 = (int64_t)t0 * d.R * d.K;
+    e1 = (int64_t)min(t1 * d.R, d.n) * d.K;
+}
+
+constexpr int kMultiAhead = 2;
+
+// Row walk for a matrix of one value per offset (K even): with the values in
+// scalar registers a row's product is the same for all its columns, so the
+// flat layout is walked like a vector, two elements a lane, and every gather is
+// one contiguous kilobyte per wavefront.  (A lane per row reads 8 K bytes of
+// each gathered row, a line per lane and instruction.)  A wave takes slices
+// s0, s0 + stride, ... of 64 rows, 64 lane-elements at a time (the order of the
+// staged walk, so sums over a lane's elements have its bits); fn(t, row, y, own)
+// gets lane-element t of the flat layout, own being what pre(t) loaded, once
+// go() holds.  X is 16-byte aligned.  The walk waits on the latency of its
+// rounds (16 waves a CU), so kMultiAhead pieces are loaded before the first is
+// used: with p.q on the 7-point 128^3 matrix, K = 8, 107.8 us with one, 95.7
+// with two, 100.7 with four (registers).  Neighbours a few rows away by lane
+// moves instead of loads: 127.6.
+template <int K, int W, class Go, class Pre, class Fn>
+__device__ __forceinline__ void multi_stencil(const MultiDesc &d, int s0, int stride, const double *__restrict__ X,
+                                              Go &&go, Pre &&pre, Fn &&fn)
+{
+    using E = typename Flat<K>::Elem;
+    constexpr int L = Flat<K>::kLanes;
+    constexpr int kRows = kWave / L;                       // rows of 64 lane-elements
+    constexpr int U = L > 1 ? kMultiAhead : 1;             // such pieces at a time
+    const int n = d.n, lane = threadIdx.x & (kWave - 1);
+    const int ns = (n + kSell - 1) / kSell;
+    const int w = d.sv.plain >> kSellWidthShift;
+    const uint32_t *__restrict__ masks = d.sv.mask;
+    // constant for the kernel's life: read by scalar loads; positions past the
+    // list repeat its last one, no mask has their bits
+    const auto *ou = as_constant(reinterpret_cast<const int32_t *>(d.sv.col));
+    const auto *uv = as_constant(d.sell_val);
+    const int64_t lo = ou[0], hi = ou[w - 1];
+    const E *__restrict__ Xe = reinterpret_cast<const E *>(X);
+    int ok[W];
+    double vk[W];
+    auto list = [&](int k0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = eb + (int64_t)u * kBlock;
-            if (e < e1) v[u] = ld(e);
+        for (int k = 0; k < W; ++k) {
+            ok[k] = ou[min(k0 + k, w - 1)];
+            vk[k] = uv[min(k0 + k, w - 1)];
         }
+    };
+    list(0);
+    int s = __builtin_amdgcn_readfirstlane(s0);
+    if (!go()) return;
+    for (; s < ns; s += stride) {
+        const int re = min((s + 1) * kSell, n);
+        for (int r0 = s * kSell; r0 < re; r0 += U * kRows) {
+            const bool in = r0 + lo >= 0 && r0 + (U * kRows - 1) + hi < n;
+            uint32_t m[U];
+            decltype(pre(int64_t(0))) own[U];
+            E acc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = eb + (int64_t)u * kBlock;
-            if (e < e1) st(e, v[u]);
+            for (int u = 0; u < U; ++u) {
+                const int row = r0 + u * kRows + lane / L;
+                m[u] = row < n ? masks[min(row, n - 1)] : 0u;
+                own[u] = pre(min((int64_t)(r0 + u * kRows) * L + lane, (int64_t)n * L - 1));
+                acc[u] = E(0.0);
+            }
+            for (int k0 = 0; k0 < w; k0 += W) {
+                E xv[U][W];
+                if (in) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int k = 0; k < W; ++k)
+                            xv[u][k] = (Xe + ((int64_t)(r0 + u * kRows) + ok[k]) * L)[(unsigned)lane];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int k = 0; k < W; ++k) {
+                            const int c = min(max(r0 + u * kRows + lane / L + ok[k], 0), n - 1);
+                            xv[u][k] = Xe[(int64_t)c * L + lane % L];
+                        }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < W; ++k)
+#pragma unroll
+                        for (int c = 0; c < Flat<K>::kCols; ++c) {
+                            const double t = fma(vk[k], xv[u][k][c], acc[u][c]);
+                            acc[u][c] = (m[u] >> k) & 1u ? t : acc[u][c];
+                        }
+                if (w <= W) break;
+#pragma unroll
+                for (int u = 0; u < U; ++u) m[u] >>= W;
+                list(k0 + W < w ? k0 + W : 0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int row = r0 + u * kRows + lane / L;
+                if (row < n) fn((int64_t)(r0 + u * kRows) * L + lane, row, acc[u], own[u]);
+            }
         }
     }
 }
@@ -471,6 +573,10 @@ __device__ __forceinline__ int xcd_runs(int l, int nblk, int R)
     const int x = l % kXcd, k = l / kXcd;
     return (k / R) * (kXcd * R) + x * R + k % R;
 }
+
+// Consecutive blocks per XCD of the stencil walk: 4, 16, 64 and a whole eighth
+// of the rows measured alike (101.6 to 104.1 us).
+constexpr int kStencilRun = 16;
 
 template <class CI, int K>
 __global__ __launch_bounds__(kBlock) void k_spmm(MultiDesc d, const double *__restrict__ X, double *__restrict__ Y)
@@ -498,6 +604,19 @@ __global__ __launch_bounds__(kBlock) void k_spmm(MultiDesc d, const double *__re
 #pragma unroll
         for (int q = 0; q < K; ++q) Y[(size_t)row * K + q] = acc[q];
     });
+}
+
+// The same for a matrix of one value per offset, K even, X and Y 16-byte aligned.
+template <int K, int W>
+__global__ __launch_bounds__(kBlock) void k_spmm_stencil(MultiDesc d, const double *__restrict__ X,
+                                                         double *__restrict__ Y)
+{
+    using E = typename Flat<K>::Elem;
+    const int l = xcd_runs((int)blockIdx.x, (int)gridDim.x, kStencilRun);
+    E *Ye = reinterpret_cast<E *>(Y);
+    multi_stencil<K, W>(d, l * (kBlock / kWave) + (int)threadIdx.x / kWave, (int)gridDim.x * (kBlock / kWave), X,
+                        [] { return true; }, [](int64_t) { return 0; },
+                        [&](int64_t t, int, E y, int) { __builtin_nontemporal_store(y, Ye + t); });
 }
 
 // ------------------------------------------------------------------ residual
@@ -576,29 +695,46 @@ static __global__ __launch_bounds__(kBlock) void k_m_fin_resid(MultiDesc d, int 
 }
 
 // ------------------------------------------------------------------ setup
-// Z = D^-1 R, P = Z for the running columns in mask, per-block r.z.
+// z = D^-1 r is formed where it is needed (the dots, p): reading r and D^-1 again
+// costs a K-th more than z would, and z is never stored (8 n K bytes an
+// iteration less).
+
+// P = Z for the running columns in mask, per-block r.z.
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_m_setup(MultiDesc d, int32_t mask)
 {
+    using E = typename Flat<K>::Elem;
+    constexpr int C = Flat<K>::kCols;
     __shared__ double sh[(kBlock / kWave) * K];
     int j;
     if (multi_block(d, j) < 0) return;
-    const int q = threadIdx.x % K;
-    const bool run = ((mask >> q) & 1) && d.st[q].status == SPK_RUNNING;
-    const double *__restrict__ Rv = d.Rv;
+    const int q = Flat<K>::col(threadIdx.x);
+    bool run[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) run[c] = ((mask >> (q + c)) & 1) && d.st[q + c].status == SPK_RUNNING;
+    const E *__restrict__ Re = reinterpret_cast<const E *>(d.Rv);
     const double *__restrict__ dinv = d.dinv;
-    double *__restrict__ Z = d.Z;
-    double *__restrict__ P = d.P;
-    double rz = 0.0;
-    if (run)
-        flat_walk<K>(d, j, [&](int64_t e, int i) {
-            const double ri = Rv[e];
-            const double zi = dinv[i] * ri;
-            Z[e] = zi;
-            P[e] = zi;
-            rz = fma(ri, zi, rz);
-        });
-    block_partials_flat<K>(rz, sh, d.partials + (size_t)kPartRz * K * d.nblk, d.nblk, j);
+    E *__restrict__ Pe = reinterpret_cast<E *>(d.P);
+    struct In {
+        E r, p;
+        double dinv;
+    };
+    E rz = E(0.0);
+    int64_t e0, e1;
+    flat_range(d, j, e0, e1);
+    flat_walk<K>(e0, e1, [&](int64_t t, int64_t i) { return In{Re[t], Pe[t], dinv[i]}; },
+                 [&](int64_t t, const In &v) {
+                     E p = v.p;
+#pragma unroll
+                     for (int c = 0; c < C; ++c)
+                         if (run[c]) {
+                             const double zi = v.dinv * v.r[c];
+                             p[c] = zi;
+                             rz[c] = fma(v.r[c], zi, rz[c]);
+                         }
+                     Pe[t] = p;
+                 });
+    block_partials_elem<K>(rz, sh, d.partials + (size_t)kPartRz * K * d.nblk, d.nblk, j);
 }
 
 static __global__ __launch_bounds__(kBlock) void k_m_fin_setup(MultiDesc d, int32_t mask)
@@ -652,21 +788,25 @@ __global__ __launch_bounds__(kBlock, K <= 8 ? 4 : 1) void k_m_spmm_pq(MultiDesc 
     const double *__restrict__ P = d.P;
     double *__restrict__ Q = d.Q;
     if (d.sell && K > 1) {
-        // flat pass: lane t always holds column t % K
-        double pqv = 0.0;
+        // flat pass, two elements a lane
+        using E = typename Flat<K>::Elem;
+        E pqv = E(0.0);
         const int lane = threadIdx.x & (kWave - 1);
-        const double *st = stage + (threadIdx.x / kWave) * kWave * K;
-        const double *pst = pstage + (threadIdx.x / kWave) * kWave * K;
+        const E *st = reinterpret_cast<const E *>(stage + (threadIdx.x / kWave) * kWave * K);
+        const E *pst = reinterpret_cast<const E *>(pstage + (threadIdx.x / kWave) * kWave * K);
         multi_sell_staged<CI, K, false>(d, l, P, stage + (threadIdx.x / kWave) * kWave * K,
                                         pstage + (threadIdx.x / kWave) * kWave * K,
                                         [&](int64_t e0, int cnt) {
-                                            for (int t = lane; t < cnt; t += kWave) {
-                                                const double v = st[t], pe = pst[t];
-                                                Q[e0 + t] = v;
-                                                pqv = fma(v, pe, pqv);
+                                            E *q = reinterpret_cast<E *>(Q + e0);
+                                            for (int t = lane; t < cnt / Flat<K>::kCols; t += kWave) {
+                                                const E v = st[t], pe = pst[t];
+                                                q[t] = v;
+#pragma unroll
+                                                for (int c = 0; c < Flat<K>::kCols; ++c)
+                                                    pqv[c] = fma(v[c], pe[c], pqv[c]);
                                             }
                                         });
-        block_partials_flat<K>(pqv, sh, d.partials + (size_t)kPartPq * K * d.nblk, d.nblk, j);
+        block_partials_elem<K>(pqv, sh, d.partials + (size_t)kPartPq * K * d.nblk, d.nblk, j);
         return;
     }
     double pq[K];
@@ -683,6 +823,31 @@ __global__ __launch_bounds__(kBlock, K <= 8 ? 4 : 1) void k_m_spmm_pq(MultiDesc 
         }
     });
     block_partials<K>(pq, sh, d.partials + (size_t)kPartPq * K * d.nblk, d.nblk, j);
+}
+
+// A for a matrix of one value per offset, K even: 103.8 us a row per lane ->
+// 95.7 on the 7-point 128^3 matrix with K = 8 (444 MB moved; P is fetched 2.3
+// times, the planes of the grid being 1 MB apart).
+template <int K, int W>
+__global__ __launch_bounds__(kBlock) void k_m_spmm_pq_stencil(MultiDesc d)
+{
+    using E = typename Flat<K>::Elem;
+    __shared__ double sh[(kBlock / kWave) * K];
+    if ((int)blockIdx.x >= d.nblk) return;
+    const int mask = d.ctl->mask;
+    const E *__restrict__ Pe = reinterpret_cast<const E *>(d.P);
+    E *__restrict__ Qe = reinterpret_cast<E *>(d.Q);
+    E pq = E(0.0);
+    const int l = xcd_runs((int)blockIdx.x, d.nblk, kStencilRun);
+    const int j = xcd_remap(l, d.nblk);  // the partial that the general kernel gives these slices
+    multi_stencil<K, W>(d, l * (kBlock / kWave) + (int)threadIdx.x / kWave, d.nblk * (kBlock / kWave), d.P,
+                        [&] { return mask != 0; }, [&](int64_t t) { return Pe[t]; },
+                        [&](int64_t t, int, E y, E p) {
+                            Qe[t] = y;
+#pragma unroll
+                            for (int c = 0; c < Flat<K>::kCols; ++c) pq[c] = fma(y[c], p[c], pq[c]);
+                        });
+    if (mask != 0) block_partials_elem<K>(pq, sh, d.partials + (size_t)kPartPq * K * d.nblk, d.nblk, j);
 }
 
 // F_A: eta = p.q and alpha per running column; eta <= 0 stops the column.
@@ -703,34 +868,51 @@ static __global__ __launch_bounds__(kBlock) void k_m_fin_pq(MultiDesc d)
     if (st->status != SPK_RUNNING) stop_column(d, q);
 }
 
-// B: R -= alpha Q, Z = D^-1 R for the running columns, per-block r.z, r.r.
+// B: R -= alpha Q for the running columns, per-block r.z and r.r (z = D^-1 r).
+// 128^3, K = 8: 98 us with z stored and one element a lane -> 73.6 (420 MB).
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_m_update(MultiDesc d)
 {
+    using E = typename Flat<K>::Elem;
+    constexpr int C = Flat<K>::kCols;
     __shared__ double sh[(kBlock / kWave) * K];
     int j;
     if (multi_block(d, j) < 0) return;
     const int mask = d.ctl->mask;
     if (mask == 0) return;
-    const int q = threadIdx.x % K;
-    const bool run = (mask >> q) & 1;
-    const double nal = run ? -d.st[q].alpha : 0.0;
-    const double *__restrict__ Q = d.Q;
+    const int q = Flat<K>::col(threadIdx.x);
+    bool run[C];
+    double nal[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        run[c] = (mask >> (q + c)) & 1;
+        nal[c] = run[c] ? -d.st[q + c].alpha : 0.0;
+    }
+    const E *__restrict__ Qe = reinterpret_cast<const E *>(d.Q);
     const double *__restrict__ dinv = d.dinv;
-    double *__restrict__ Rv = d.Rv;
-    double *__restrict__ Z = d.Z;
-    double rz = 0.0, rr = 0.0;
-    if (run)
-        flat_walk<K>(d, j, [&](int64_t e, int i) {
-            const double ri = fma(nal, Q[e], Rv[e]);
-            const double zi = dinv[i] * ri;
-            Rv[e] = ri;
-            Z[e] = zi;
-            rz = fma(ri, zi, rz);
-            rr = fma(ri, ri, rr);
-        });
-    block_partials_flat<K>(rz, sh, d.partials + (size_t)kPartRz * K * d.nblk, d.nblk, j);
-    block_partials_flat<K>(rr, sh, d.partials + (size_t)kPartRr * K * d.nblk, d.nblk, j);
+    E *__restrict__ Re = reinterpret_cast<E *>(d.Rv);
+    struct In {
+        E r, q;
+        double dinv;
+    };
+    E rz = E(0.0), rr = E(0.0);
+    int64_t e0, e1;
+    flat_range(d, j, e0, e1);
+    flat_walk<K>(e0, e1, [&](int64_t t, int64_t i) { return In{Re[t], Qe[t], dinv[i]}; },
+                 [&](int64_t t, const In &v) {
+                     E r = v.r;
+#pragma unroll
+                     for (int c = 0; c < C; ++c)
+                         if (run[c]) {  // a stopped column keeps its r
+                             const double ri = fma(nal[c], v.q[c], v.r[c]);
+                             r[c] = ri;
+                             rz[c] = fma(ri, v.dinv * ri, rz[c]);
+                             rr[c] = fma(ri, ri, rr[c]);
+                         }
+                     Re[t] = r;
+                 });
+    block_partials_elem<K>(rz, sh, d.partials + (size_t)kPartRz * K * d.nblk, d.nblk, j);
+    block_partials_elem<K>(rr, sh, d.partials + (size_t)kPartRr * K * d.nblk, d.nblk, j);
 }
 
 // F_B: per running column: iteration count, convergence, breakdowns, beta;
@@ -770,42 +952,48 @@ static __global__ __launch_bounds__(kBlock) void k_m_fin_update(MultiDesc d)
 // at most): block b takes the b-th chunk of the flat n x K range, a multiple
 // of 256 elements, in physical block order (a streaming pass gains nothing
 // from XCD-contiguous ranges; on the 128^3 k = 8 block, 1024 blocks with
-// those ranges took 131.5 us, 8192 in order 120.8).
+// those ranges took 131.5 us, 8192 in order 120.8; 111.4 with two elements a
+// lane and z formed here: 690 MB at 6.2 TB/s).
 constexpr int kMultiPxBlocks = 8192;
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_m_px(MultiDesc d)
 {
-    const int q = threadIdx.x % K;
-    const int cm = d.st[q].cmode;
-    if (cm == 0) return;  // no barrier follows
-    const double al = d.st[q].alpha, be = d.st[q].beta;
-    double *__restrict__ X = d.X;
-    double *__restrict__ P = d.P;
-    const double *__restrict__ Z = d.Z;
-    const int64_t nk = (int64_t)d.n * K;
-    const int64_t per = ((nk + gridDim.x - 1) / gridDim.x + kBlock - 1) / kBlock * kBlock;
-    const int64_t e0 = (int64_t)blockIdx.x * per, e1 = min(nk, e0 + per);
-    constexpr int U = 4;
-    for (int64_t eb = e0 + threadIdx.x; eb < e1; eb += (int64_t)kBlock * U) {
-        double p[U], x[U], z[U];
+    using E = typename Flat<K>::Elem;
+    constexpr int C = Flat<K>::kCols;
+    const int q = Flat<K>::col(threadIdx.x);
+    int cm[C], any = 0;
+    double al[C], be[C];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = eb + (int64_t)u * kBlock;
-            if (e < e1) {
-                p[u] = P[e];
-                x[u] = X[e];
-                z[u] = Z[e];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = eb + (int64_t)u * kBlock;
-            if (e < e1) {
-                X[e] = fma(al, p[u], x[u]);
-                if (cm == 2) P[e] = fma(be, p[u], z[u]);
-            }
-        }
+    for (int c = 0; c < C; ++c) {
+        cm[c] = d.st[q + c].cmode;
+        al[c] = d.st[q + c].alpha;
+        be[c] = d.st[q + c].beta;
+        any |= cm[c];
     }
+    if (any == 0) return;  // no barrier follows
+    E *__restrict__ Xe = reinterpret_cast<E *>(d.X);
+    E *__restrict__ Pe = reinterpret_cast<E *>(d.P);
+    const E *__restrict__ Re = reinterpret_cast<const E *>(d.Rv);
+    const double *__restrict__ dinv = d.dinv;
+    const int64_t nk = (int64_t)d.n * K;
+    constexpr int64_t kStep = (int64_t)kBlock * C;
+    const int64_t per = ((nk + gridDim.x - 1) / gridDim.x + kStep - 1) / kStep * kStep;
+    const int64_t e0 = min(nk, (int64_t)blockIdx.x * per), e1 = min(nk, e0 + per);
+    struct In {
+        E p, x, r;
+        double dinv;
+    };
+    flat_walk<K>(e0, e1, [&](int64_t t, int64_t i) { return In{Pe[t], Xe[t], Re[t], dinv[i]}; },
+                 [&](int64_t t, const In &v) {
+                     E x = v.x, p = v.p;
+#pragma unroll
+                     for (int c = 0; c < C; ++c) {
+                         if (cm[c]) x[c] = fma(al[c], v.p[c], v.x[c]);
+                         if (cm[c] == 2) p[c] = fma(be[c], v.p[c], v.dinv * v.r[c]);
+                     }
+                     Xe[t] = x;
+                     Pe[t] = p;
+                 });
 }
 
 // Per-column state for a new solve (FP64, one thread per column), all

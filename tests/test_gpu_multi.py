@@ -182,3 +182,48 @@ def test_multi_errors():
         spk.ksp_solve_multi(M, B4, X4, spk.ksp_opts(precision=spk.PREC_MIXED))
     with pytest.raises(spk.SpkError):
         spk.ksp_solve_multi(M, B4, B4)
+
+
+@pytest.mark.parametrize("k", [2, 4, 8, 16])
+@pytest.mark.parametrize("dims", [(3,), (15,), (17,), (63,), (64,), (65,), (129,), (33, 5), (9, 7, 5), "box", "wide"])
+def test_multi_one_value_per_offset_same_bits(dims, k):
+    """The flat walk of a matrix of one value per offset (lists of 3, 5, 7, 27
+    and 5 positions; edge and inner pieces, a remainder in each) gives the
+    bits of the walk of a value per entry: products, also of blocks that are
+    only 8-byte aligned, and solves with a zero, a converged and a far start."""
+    spk = need_gpu()
+    import torch
+
+    if dims == "box":
+        A = spkgen.diffusion3d27_lognormal(9, seed=1)
+        r = np.repeat(np.arange(A.n), np.diff(A.rowptr))
+        A = spkgen.CSR(A.n, A.rowptr, A.col, np.where(A.col == r, 27.0, -1.0))
+    elif dims == "wide":  # neighbours further off than a piece has rows
+        A = spkgen.laplace_grid((1000, 3), 0.5)
+    else:
+        A = spkgen.laplace_grid(dims, 0.5)
+    rng = np.random.default_rng(k)
+    X = _dev2(rng.standard_normal((A.n, k)))
+    res = []
+    for param in (0, 16):
+        M = mat_on_gpu(spk, A)
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, param)
+        out = []
+        for skip in (0, 1):
+            buf = torch.full((A.n * k + 1,), np.nan, dtype=torch.float64, device="cuda")
+            Y = buf[skip:A.n * k + skip].view(A.n, k)
+            xb = torch.empty_like(buf)
+            Xs = xb[skip:A.n * k + skip].view(A.n, k)
+            Xs.copy_(X)
+            spk.mat_mult_multi(M, Xs, Y)
+            out.append(Y.clone())
+        B = out[0].contiguous()
+        Z = torch.zeros_like(B)
+        Z[:, 0] = X[:, 0]
+        Z[:, k - 1] = 100.0
+        spk.ksp_solve_multi(M, B, Z)
+        out.append(Z)
+        res.append([o.cpu().numpy() for o in out])
+        M.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
