@@ -998,8 +998,8 @@ def bench_c4(args):
         "kernels": res,
         "bytes_f64": info.bytes_spmv_f64, "bytes_f32": info.bytes_spmv_f32,
         "note": "gbps = algorithmic CSR bytes (12 nnz + 4(n+1) + 16n; FP32 8 nnz + 4(n+1) + 8n) per "
-                "median launch time; the sliced family also moves 4(8n+1) row pointers and writes and "
-                "reads 8n partial products (format_bytes_f64)",
+                "median launch time; the sliced family also writes and reads nnz products (binned) or, by "
+                "lanes, moves 4(8n+1) row pointers and 8n partial products twice (format_bytes_f64)",
     }
     M.close()
     return out

@@ -102,9 +102,13 @@ enum {
                                in its own L2; a merge path over the stacked
                                slices, or lanes per slice row) into 8 partial
                                vectors that a second pass sums per row in
-                               slice order.  A copy of the matrix built at
-                               selection (12 nnz + 4 (8n + 1) bytes + 8n
-                               partials) */
+                               slice order.  Up to 512 bins of 16384 columns
+                               the merge path runs over bins instead: a first
+                               pass forms the products with a bin's x in LDS, a
+                               second sums them by row.  A copy of the matrix
+                               built at selection (12 nnz + 4 (8n + 1) bytes +
+                               8n partials; binned 20 nnz and 4 bytes for every
+                               bin of each 4096 entries and rows) */
     SPK_KERNEL_SELL_SIGMA = 6  /* SELL-C-sigma (opt-in): SELL-64 over the rows
                                   ordered by length, longest first, within
                                   windows of sigma rows, so that the rows of a

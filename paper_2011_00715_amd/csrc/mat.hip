@@ -437,6 +437,13 @@ void update_info(spk_mat *A)
         const int64_t extra = A->sell_idx_bytes + (A->sell_perm ? 4 * nn : 0) + (A->sell_ptr ? 4 * (ns + 1) : 0);
         I.format_bytes_spmv_f64 = 8 * A->sell_nnz + 16 * nn + extra;
         I.format_bytes_spmv_f32 = 4 * A->sell_nnz + 8 * nn + extra;
+    } else if (A->kernel == SPK_KERNEL_SLICED && A->xs_merge && A->bn_slab) {
+        // per entry the column within its bin, the value, the place in its tile
+        // and the product written and read; per tile its segments' starts
+        I.stored_nnz = nz;
+        const int64_t per = 4 * (nn + 1) + 8 * (int64_t)A->bn_tiles * A->bn_bins;
+        I.format_bytes_spmv_f64 = 28 * nz + 16 * nn + per;
+        I.format_bytes_spmv_f32 = 16 * nz + 8 * nn + per;
     } else if (A->kernel == SPK_KERNEL_SLICED && A->xs_ptr) {
         // stacked slices: 8n + 1 row pointers; the 8n partial products are
         // written once and read once by the summing pass
@@ -459,7 +466,7 @@ int ensure_f32(spk_mat *A, hipStream_t s)
         SPK_HIP(hipGetLastError());
         A->bytes += 4 * A->sell_nnz;
     }
-    if (A->xs_ptr) {
+    if (A->xs_ptr || A->bn_slab) {
         const int rc = ensure_sliced_f32(A, s);
         if (rc) return rc;
     }
@@ -489,11 +496,12 @@ static bool merge_fits(const spk_mat *A) { return (int64_t)A->n + A->nnz < 0x7ff
 // Row-length statistics -> kernel family (stream for short, even rows; vector
 // for long, even rows; merge-path for skewed lengths).
 // The sliced layout pays when x does not fit one XCD's 4 MB L2 and rows
-// reach across it (scattered columns).  With the merge path over the slices:
-// 1.15 ms against 2.02 ms (SELL) and 2.13 ms (merge) for 4M rows of 32
-// uniform random columns, 1.16 against 1.94 ms (merge) for the skewed
-// power-law C4 rows; lanes per slice row take 1.44 and 1.95 ms.  Banded
-// matrices keep their x window in L2 anyway.
+// reach across it (scattered columns).  For 4M skewed power-law rows of 32
+// entries on average 0.93 ms binned and 1.14 with the merge path over the
+// slices against 1.94 ms (merge); lanes per slice row take 1.95 ms.  Below the
+// line the product gains little (270 k rows of 32, FP64: 72 us against 65 of the
+// stream kernel; 450 k power-law rows: 104 against 116) for a copy of the matrix.
+// Banded matrices keep their x window in L2 anyway.
 static bool sliced_wanted(const spk_mat *A)
 {
     const double mean = A->n ? (double)A->stats.sum_len / A->n : 0.0;
@@ -559,7 +567,7 @@ static int setup_merge(spk_mat *A, hipStream_t s)
     SPK_HIP(hipMalloc(&A->carry_val, sizeof(double) * mt));
     A->bytes += (int64_t)mt * 20 + 8;
     hipLaunchKernelGGL(k_merge_partition, dim3(ceil_div(A->mtiles + 1, kBlock)), dim3(kBlock), 0, s,
-                       A->n, (int)A->nnz, A->rowptr, A->mtiles, A->tile_row, A->tile_k);
+                       A->n, (int)A->nnz, A->rowptr, A->mtiles, kMergeItems, A->tile_row, A->tile_k);
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
@@ -1022,8 +1030,7 @@ static int create_impl(int32_t n, int64_t nnz, const int32_t *rowptr, const int3
     }
     if (A->kernel != SPK_KERNEL_STREAM) A->R = 256;
     if (A->kernel == SPK_KERNEL_STREAM && A->R == 0) A->R = 32;
-    if (A->kernel == SPK_KERNEL_SLICED &&
-        (setup_sliced(A, s) != SPK_OK || (A->xs_merge && setup_sliced_merge(A, s) != SPK_OK))) {
+    if (A->kernel == SPK_KERNEL_SLICED && setup_sliced(A, A->xs_merge, s) != SPK_OK) {
         choose_kernel(A, true, false);  // no room for the copy: the unsliced family
         if (A->kernel != SPK_KERNEL_STREAM) A->R = 256;
     }
@@ -1174,13 +1181,9 @@ int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
             set_error("sliced parameter %d: 0, a power of two in [1, 64] or %d (merge path)", param, kMergeItems);
             return SPK_EINVAL;
         }
-        int rc = setup_sliced(A, s);
-        if (rc) return rc;
         const int merge = param == kMergeItems || (param == 0 && sliced_merge_fits(A));
-        if (merge) {
-            rc = setup_sliced_merge(A, s);
-            if (rc) return rc;
-        }
+        const int rc = setup_sliced(A, merge, s);
+        if (rc) return rc;
         A->kernel = SPK_KERNEL_SLICED;
         A->xs_merge = merge;
         A->lanes = lanes_ok ? param : sliced_lanes(A);
@@ -1197,7 +1200,7 @@ int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
         SPK_HIP(hipStreamSynchronize(s));
     }
     if (kernel == SPK_KERNEL_AUTO && A->kernel == SPK_KERNEL_SLICED) {
-        if (setup_sliced(A, s) != SPK_OK || (A->xs_merge && setup_sliced_merge(A, s) != SPK_OK)) {
+        if (setup_sliced(A, A->xs_merge, s) != SPK_OK) {
             choose_kernel(A, true, false);
             if (A->kernel == SPK_KERNEL_MERGE) {
                 const int r2 = setup_merge(A, s);

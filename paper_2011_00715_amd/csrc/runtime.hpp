@@ -172,6 +172,21 @@ struct spk_mat {
     int32_t *xs_tile_row = nullptr, *xs_tile_k = nullptr, *xs_carry_row = nullptr;
     int32_t *xs_slice_tile = nullptr;  // kSlices + 1 tile ranges
     void *xs_carry_val = nullptr;
+    // binned copy (the same family where it fits): entries by (column bin, row
+    // tile), one allocation
+    char *bn_slab = nullptr;
+    int bn_tiles = 0, bn_bins = 0, bn_pieces = 0;
+    int32_t *bn_tile_row = nullptr, *bn_tile_k = nullptr;  // bn_tiles + 1 each
+    int32_t *bn_start = nullptr;       // (bn_tiles + 1) x bn_bins: where a tile's segment of a bin starts
+    int4 *bn_piece = nullptr;          // bin and entry range of a block of the product pass
+    uint16_t *bn_col = nullptr;        // column within the bin
+    uint16_t *bn_dst = nullptr;        // place in the tile, by tile
+    double *bn_val = nullptr;
+    float *bn_val32 = nullptr;
+    void *bn_prod = nullptr;           // products (FP64 or FP32)
+    int32_t *bn_carry_row = nullptr;
+    void *bn_carry_val = nullptr;
+    int64_t bn_bytes = 0;
     spk::Workspace *ws = nullptr;
     spk::MultiWs *mws = nullptr;  // multi-right-hand-side solver workspace
     int64_t bytes = 0;
@@ -209,12 +224,12 @@ void free_multi(spk_mat *A);
 // column-sliced layout (xslice.hip)
 bool sliced_fits(const spk_mat *A);
 int sliced_lanes(const spk_mat *A);
-int setup_sliced(spk_mat *A, hipStream_t s);
+int setup_sliced(spk_mat *A, int merge, hipStream_t s);
 void free_sliced(spk_mat *A);
 int ensure_sliced_f32(spk_mat *A, hipStream_t s);
-int setup_sliced_merge(spk_mat *A, hipStream_t s);
 bool sliced_skewed(const spk_mat *A);
 bool sliced_merge_fits(const spk_mat *A);
+bool binned_fits(const spk_mat *A);
 template <class V>
 int launch_sliced(const spk_mat *A, const V *x, V *y, hipStream_t s, const SysState *gst, int gmode);
 template <class V>

@@ -640,13 +640,13 @@ __global__ void k_sell_fill(int n, const int32_t *__restrict__ rowptr,
 // ------------------------------------------------------------------ merge path
 // Split point of diagonal d on the merge of row ends (rowptr[i+1]) with
 // nonzero indices: (i, d - i) with i the number of completed rows.
-static __global__ void k_merge_partition(int n, int nnz, const int32_t *__restrict__ rowptr, int ntiles,
+static __global__ void k_merge_partition(int n, int nnz, const int32_t *__restrict__ rowptr, int ntiles, int per,
                                   int32_t *__restrict__ tile_row, int32_t *__restrict__ tile_k)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t > ntiles) return;
     const int64_t total = (int64_t)n + nnz;
-    const int64_t d64 = min((int64_t)t * kMergeItems, total);
+    const int64_t d64 = min((int64_t)t * per, total);
     const int d = (int)d64;
     int lo = d > nnz ? d - nnz : 0;
     int hi = d < n ? d : n;

@@ -580,3 +580,53 @@ def test_spmv_sell_shared_offsets():
     spk.mat_mult(M, to_dev(xi), y)
     assert np.array_equal(y.cpu().numpy(), oracle.spmv(U, xi))
     M.close()
+
+
+BIN, TILE = 16384, 4096  # columns of a bin, merge-path items (rows and entries) of a tile
+
+
+def _scattered(n, lens, seed):
+    """Rows of the given lengths, random columns (with repeats), small integers."""
+    rng = np.random.default_rng(seed)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    return spkgen.CSR(n, rowptr, col, rng.integers(-9, 10, rowptr[-1]).astype(np.float64))
+
+
+@pytest.mark.parametrize("case", ["one_row", "one_tile", "two_tiles", "bins_1", "bins_2", "bins_2_full", "bins_3",
+                                  "long_row", "empty_rows", "one_bin_used", "no_entries", "bins_512", "bins_513"])
+def test_binned_products(case):
+    """The sliced family's merge path by column bins and row tiles (beyond 512
+    bins: over the slices): exact on integers in FP64 and FP32, twice on the
+    same handle, for rows that end with a tile, go on over several or are
+    empty, and bins that are full, partly used or unused."""
+    spk = need_gpu()
+    import torch
+
+    n, lens = {"one_row": (1, [1]), "one_tile": (100, [TILE // 100 - 1] * 99 + [TILE - 100 - 99 * (TILE // 100 - 1)]),
+               "two_tiles": (100, [TILE // 100 - 1] * 99 + [TILE - 99 - 99 * (TILE // 100 - 1)]),
+               "bins_1": (BIN, 3), "bins_2": (BIN + 1, 3), "bins_2_full": (2 * BIN, 2), "bins_3": (2 * BIN + 3, 5),
+               "long_row": (BIN + 500, [1] * 300 + [5 * TILE + 7] + [2] * (BIN + 199)),
+               "empty_rows": (3 * TILE, [0] * (TILE + 5) + [40] * 3 + [0] * (2 * TILE - 8)),
+               "one_bin_used": (4 * BIN, 1), "no_entries": (300, 0), "bins_512": (512 * BIN, 1),
+               "bins_513": (512 * BIN + 1, 1)}[case]
+    lens = np.full(n, lens) if np.isscalar(lens) else np.array(lens)
+    assert lens.size == n
+    A = _scattered(n, lens, 7)
+    if case == "one_bin_used":
+        A = spkgen.CSR(n, A.rowptr, (2 * BIN + A.col % BIN).astype(np.int32), A.val)
+    M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+    assert spk.KERNEL_NAMES[M.info.kernel] == "sliced" and M.info.lanes == 2048
+    for seed in (1, 2):
+        x = np.random.default_rng(seed).integers(-50, 50, n).astype(np.float64)
+        ref = oracle.spmv(A, x)
+        y, y32 = to_dev(np.full(n, np.nan)), to_dev(np.full(n, np.nan, np.float32))
+        spk.mat_mult(M, to_dev(x), y)
+        spk.mat_mult_f32(M, to_dev(x.astype(np.float32)), y32)
+        assert np.array_equal(y.cpu().numpy(), ref)
+        assert np.array_equal(y32.cpu().numpy().astype(np.float64), ref)
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, 4)  # and the copy is given back
+    spk.mat_mult(M, to_dev(x), y)
+    assert np.array_equal(y.cpu().numpy(), ref)
+    M.close()
