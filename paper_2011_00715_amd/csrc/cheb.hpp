@@ -60,10 +60,12 @@ struct ChebOwn {
     double rcg;
 };
 
-template <class V>
+// kOneDiag: the matrix has one value per offset, so one D^-1.
+template <class V, bool kOneDiag = false>
 __device__ __forceinline__ ChebOwn<V> cheb_own(const ChebStep<V> &c, int i)
 {
-    return ChebOwn<V>{c.dk[i], c.x[i], c.r[i], c.dinv[i], c.part ? c.rcg[i] : 0.0};
+    return ChebOwn<V>{c.dk[i], c.x[i], c.r[i], kOneDiag ? (V)*as_constant(c.dinv) : c.dinv[i],
+                      c.part ? c.rcg[i] : 0.0};
 }
 
 // Row i of a step whose product is y.  Returns its term of rcg . z (0 when
@@ -113,23 +115,26 @@ __global__ __launch_bounds__(kBlock) void k_cheb_sell(int n, SellView sv, const 
     bool run = true;
     sell_slices<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
                           gridDim.x * (kBlock / kWave), sv, val, c.dk, [&] { return run = cheb_go(c.gate); },
-                          [&](int i) { return cheb_own(c, i); },
+                          [&](int i) { return cheb_own<V, std::is_same<CI, Stencil>::value>(c, i); },
                           [&](int i, V y, const ChebOwn<V> &o) { acc += cheb_row(c, i, y, o); });
     if (c.part && run) cheb_part(acc, c.part);
 }
 
-// d_0 = (D^-1 b) / theta of a start from zero.
-template <class V, class B>
+// d_0 = (D^-1 b) / theta of a start from zero; kOneDiag: D^-1 is `one`.
+template <class V, class B, bool kOneDiag>
 struct GatherD0 {
     const V *__restrict__ dinv;
     const B *__restrict__ b;
-    V it;
+    V it, one;
     struct Raw {
         V dinv;
         B b;
     };
-    __device__ Raw at(int j) const { return Raw{dinv[j], b[j]}; }
-    __device__ Raw sh(int64_t base, unsigned l) const { return Raw{(dinv + base)[l], (b + base)[l]}; }
+    __device__ Raw at(int j) const { return Raw{kOneDiag ? one : dinv[j], b[j]}; }
+    __device__ Raw sh(int64_t base, unsigned l) const
+    {
+        return Raw{kOneDiag ? one : (dinv + base)[l], (b + base)[l]};
+    }
     __device__ V of(const Raw &r) const
     {
 #pragma clang fp contract(off)
@@ -142,14 +147,16 @@ template <class V, class B, class CI, int U>
 __global__ __launch_bounds__(kBlock) void k_cheb_sell_zero(int n, SellView sv, const V *__restrict__ val,
                                                            ChebStep<V> c, const B *__restrict__ b)
 {
-    const GatherD0<V, B> d0{c.dinv, b, c.inv_theta};
+    constexpr bool kOneDiag = std::is_same<CI, Stencil>::value;
+    const V one = kOneDiag ? (V)*as_constant(c.dinv) : V(0);
+    const GatherD0<V, B, kOneDiag> d0{c.dinv, b, c.inv_theta, one};
     double acc = 0.0;
     bool run = true;
     sell_slices_g<V, CI, U>(n, blockIdx.x * (kBlock / kWave) + (int)threadIdx.x / kWave,
                             gridDim.x * (kBlock / kWave), sv, val, d0, [&] { return run = cheb_go(c.gate); },
                             [&](int i) {
 #pragma clang fp contract(off)
-                                const V bi = (V)b[i], di = c.dinv[i];
+                                const V bi = (V)b[i], di = kOneDiag ? one : c.dinv[i];
                                 return ChebOwn<V>{di * bi * c.inv_theta, V(0), bi, di, c.part ? c.rcg[i] : 0.0};
                             },
                             [&](int i, V y, const ChebOwn<V> &o) {

@@ -331,6 +331,16 @@ static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
     return SPK_OK;
 }
 
+// B of the fused iteration.
+template <class V>
+static void launch_update(spk_mat *A, Workspace *w, hipStream_t s)
+{
+    const One b = batch_of(w, Vecs<V>::mixed);
+    const dim3 g(b.d.nblk), t(kBlock);
+    if (one_diag(A)) hipLaunchKernelGGL((k_pcg_update<V, One, true>), g, t, 0, s, b);
+    else hipLaunchKernelGGL((k_pcg_update<V, One>), g, t, 0, s, b);
+}
+
 // F of the fused iteration (the C part, then the next product).
 template <class V, bool kStart>
 static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
@@ -360,13 +370,13 @@ static int enqueue_batch(spk_mat *A, Workspace *w, bool mixed, int K, hipStream_
             hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), t, 0, s, b);
             launch_fused<float, true>(A, w, s);
             for (int k = 0; k < K; ++k) {
-                hipLaunchKernelGGL((k_pcg_update<float, One>), g, t, 0, s, b);
+                launch_update<float>(A, w, s);
                 launch_fused<float, false>(A, w, s);
             }
         } else {
             launch_fused<double, true>(A, w, s);
             for (int k = 0; k < K; ++k) {
-                hipLaunchKernelGGL((k_pcg_update<double, One>), g, t, 0, s, b);
+                launch_update<double>(A, w, s);
                 launch_fused<double, false>(A, w, s);
             }
         }

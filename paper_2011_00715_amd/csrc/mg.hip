@@ -286,7 +286,8 @@ static int smoother_start(spk_mg *M, int l, bool x0_nonzero, const CycleIo *io, 
     const V *dinv = dinv_of<V>(A);
     const dim3 gn(grid_n(n)), tb(kBlock);
     if (x0_nonzero)
-        SPK_TRY(launch_rows<V>(A, x, RowResid<V>{b, r, d0, dinv, inv_theta}, nullptr, nullptr, gate, (V *)L.tmp, s));
+        SPK_TRY(launch_rows<V>(A, x, RowResid<V>{b, r, d0, dinv, inv_theta, one_diag(A) ? 0 : -1}, nullptr, nullptr,
+                               gate, (V *)L.tmp, s));
     else if (f32 && l == 0)  // the FP64 right-hand side, rounded and kept
         hipLaunchKernelGGL((k_cheb_init<V, double>), gn, tb, 0, s, n, io->b64, (const V *)nullptr, x, r, d0, dinv,
                            inv_theta, gate, b);
@@ -973,7 +974,6 @@ int spk_mg_profile(spk_mg *M, const double *b, double *x, int32_t reps, double *
     hipStream_t s = (hipStream_t)stream;
     M->stream = s;
     for (int l = 0; l < M->nlev; ++l) level_ms[l] = 0.0;
-    MgLevel &L0 = M->lev[0];
     int rc = SPK_OK;
     for (int r = 0; r < reps && rc == SPK_OK; ++r) {
         MgTimer t;

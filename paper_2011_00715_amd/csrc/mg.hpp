@@ -430,10 +430,11 @@ struct RowResid {
     V *r, *d0;
     const V *dinv;
     V inv_theta;
+    int each;  // -1: D^-1 per row; 0: the matrix has one
     struct Own {
         V b, dinv;
     };
-    __device__ Own own(int i) const { return Own{b[i], dinv[i]}; }
+    __device__ Own own(int i) const { return Own{b[i], dinv[i & each]}; }
     __device__ double operator()(int i, V y, const Own &o) const
     {
         const V ri = o.b - y;

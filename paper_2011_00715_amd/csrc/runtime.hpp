@@ -205,6 +205,14 @@ inline void with_sell(const spk_mat *A, F &&f)
                  [&](auto ci) { with_sell_u(A->sell_u, [&](auto uc) { f(ci, uc); }); });
 }
 
+// The kernels walk a matrix of one value per offset: its rows hold at most one
+// entry per column, and where a diagonal is needed (every row has a nonzero
+// one) it is one number, and so is its inverse in dinv.
+inline bool one_diag(const spk_mat *A)
+{
+    return A->kernel == SPK_KERNEL_SELL && A->sell_cw && (A->sell_plain & kSellUniform);
+}
+
 // y = A x with the handle's kernel (V = double or float); optional gate for
 // launches inside captured solver graphs.
 template <class V>

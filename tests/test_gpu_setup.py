@@ -132,6 +132,34 @@ def test_uniform_values_same_bits(case):
             assert np.array_equal(a, b, equal_nan=True)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("case", ["lap2d_521", "lap3d_67"])
+def test_one_diagonal_same_bits(case, precision):
+    """Solves too large for one launch: a matrix of one value per offset forms
+    z = D^-1 r where it is used, with the bits of a stored D^-1 and z; stopped
+    early, started from a guess, and over refinements that keep or restart the
+    direction."""
+    spk = need_gpu()
+    import torch
+
+    A = {"lap2d_521": lambda: spkgen.laplace2d5(521, 0.3), "lap3d_67": lambda: spkgen.laplace3d7(67)}[case]()
+    assert A.n > 262144
+    b = to_dev(spkgen.rhs_uniform(A.n, 3))
+    prec = {"fp64": spk.PREC_FP64, "mixed": spk.PREC_MIXED}[precision]
+    res = []
+    for param in (0, 16):
+        M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, param)
+        for kw in ({}, {"maxit": 13}, {"rtol": 1e-12}):
+            x = b * 0.125
+            r = spk.ksp_solve(M, b, x, spk.ksp_opts(precision=prec, **kw))
+            res.append((r.reason, r.iterations, x.cpu().numpy()))
+        M.close()
+    for a, c in zip(res[:3], res[3:]):
+        assert a[:2] == c[:2]
+        assert np.array_equal(a[2], c[2])
+
+
 @pytest.mark.parametrize("entry", ["first", "last", "sign_of_zero"])
 def test_uniform_values_need_every_entry(entry):
     """One entry that differs, in its sign bit alone too, keeps a value per entry."""
