@@ -78,7 +78,8 @@ static int dalloc(T **p, int64_t count, Workspace *w)
 // its partials, ~4.6 us) instead of the persistent grid when each lane of
 // the persistent grid would stream more than this many SELL entries:
 // 160^3 27-point makes 210 (FP64 iteration 313 -> 306 us, FP32 inner
-// 181 -> 177 us with the wide product), the 7-point matrices of 150^3 and
+// 181 -> 177 us with the wide product; 229 us now that the lists are read by
+// scalar loads and the vector passes are wider), the 7-point matrices of 150^3 and
 // 160^3 45 and 55 (FP32 inner iterations 65 -> 70 and 79 -> 83 us slower),
 // 128^3 28.
 constexpr int64_t kWideEntriesPerLane = 96;

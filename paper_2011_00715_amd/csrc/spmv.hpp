@@ -307,38 +307,14 @@ struct GatherX {
 // gat gives the gathered operands: x[j] for a plain product; the fused PCG
 // kernels form p = z + beta p there.
 //
-// SH (shared offsets, CI = int32): the offsets come from the slice's list
-// (wave-uniform, scalar loads), rlen is the row's position mask, and gathered
-// columns are clamped into [0, n) for the positions the row does not use.
-template <class V, class CI, int UP, bool NT, bool SH, class G>
+template <class V, class CI, int UP, bool NT, class G>
 __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ val, G &&gat,
-                                      int32_t b, int slen, int rlen, int lane, int row, int n)
+                                      int32_t b, int slen, int rlen, int lane, int row)
 {
-    static_assert(!SH || std::is_same<CI, int32_t>::value, "shared offsets are int32");
     using CP = typename Pair2<CI>::type;
     using VP = typename Pair2<V>::type;
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
-    const int32_t *__restrict__ ou =
-        reinterpret_cast<const int32_t *>(sv.col) + (__builtin_amdgcn_readfirstlane(b) >> 6);
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
-    auto offsets = [&](int p) -> CP {
-        if constexpr (SH) {
-            CP c;
-            c.x = ou[2 * p];
-            c.y = ou[2 * p + 1];
-            return c;
-        } else {
-            return sell_ld<NT>(cp + (size_t)p * kSell);
-        }
-    };
-    auto column = [&](int off) -> int {
-        if constexpr (SH) return min(max(row + off, 0), n - 1);
-        else return row + off;
-    };
-    auto real = [&](int k) -> bool {
-        if constexpr (SH) return ((unsigned)rlen >> k) & 1u;
-        else return k < rlen;
-    };
     const int np = slen >> 1;
     // the odd last entry is loaded first and gathered with the first round,
     // so an odd width costs no extra memory round trip; it is added last
@@ -349,8 +325,7 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
     Raw xt{};
     if (odd) {
         const size_t t = (size_t)b + (size_t)np * (2 * kSell) + lane;
-        if constexpr (SH) ct = ou[2 * np];
-        else ct = sell_ld<NT>(reinterpret_cast<const CI *>(sv.col) + t);
+        ct = sell_ld<NT>(reinterpret_cast<const CI *>(sv.col) + t);
         at = sell_ld<NT>(val + t);
     }
     V acc = V(0);
@@ -360,28 +335,28 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
             const int p = p0 + u < np ? p0 + u : np - 1;
-            c[u] = offsets(p);
+            c[u] = sell_ld<NT>(cp + (size_t)p * kSell);
             a[u] = sell_ld<NT>(vp + (size_t)p * kSell);
         }
         Raw xv[2 * UP];
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
-            xv[2 * u] = gat.at(column((int)c[u].x));
-            xv[2 * u + 1] = gat.at(column((int)c[u].y));
+            xv[2 * u] = gat.at(row + (int)c[u].x);
+            xv[2 * u + 1] = gat.at(row + (int)c[u].y);
         }
-        if (p0 == 0 && odd) xt = gat.at(column((int)ct));
+        if (p0 == 0 && odd) xt = gat.at(row + (int)ct);
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
             const int k = 2 * (p0 + u);
             if (p0 + u < np) {
-                if (real(k)) acc = fma(a[u].x, gat.of(xv[2 * u]), acc);
-                if (real(k + 1)) acc = fma(a[u].y, gat.of(xv[2 * u + 1]), acc);
+                if (k < rlen) acc = fma(a[u].x, gat.of(xv[2 * u]), acc);
+                if (k + 1 < rlen) acc = fma(a[u].y, gat.of(xv[2 * u + 1]), acc);
             }
         }
     }
     if (odd) {
-        if (np == 0) xt = gat.at(column((int)ct));
-        if (real(slen - 1)) acc = fma(at, gat.of(xt), acc);
+        if (np == 0) xt = gat.at(row + (int)ct);
+        if (slen - 1 < rlen) acc = fma(at, gat.of(xt), acc);
     }
     return acc;
 }
@@ -395,18 +370,16 @@ __device__ __forceinline__ V sell_row(const SellView &sv, const V *__restrict__ 
 // flight at any moment are adjacent in memory (one DRAM stream front rather
 // than one per block).  The first slice's header is loaded before go() is
 // asked whether to run (go holds no barrier: waves may own different counts).
-template <class V, class CI, int U, bool NT, bool SH, class G, class Go, class Pre, class Fn>
+template <class V, class CI, int U, bool NT, class G, class Go, class Pre, class Fn>
 __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const SellView &sv,
                                                 const V *__restrict__ val, G &&gat, Go &&go, Pre &&pre, Fn &&fn)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int ns = (n + kSell - 1) / kSell;
     // position j = 64 s + lane of the layout holds matrix row perm[j]
-    // (SELL-C-sigma) or row j; its length is in len or len16 (its position
-    // mask in mask with shared offsets)
+    // (SELL-C-sigma) or row j; its length is in len or len16
     auto head = [&](int j, int &rlen, int &row) {
-        if constexpr (SH) rlen = j < n ? (int)sv.mask[j] : 0;
-        else rlen = j < n ? (sv.len16 ? (int)sv.len16[j] : (int)sv.len[j]) : 0;
+        rlen = j < n ? (sv.len16 ? (int)sv.len16[j] : (int)sv.len[j]) : 0;
         row = j < n && sv.perm ? sv.perm[j] : j;
     };
     int32_t b = 0, e = 0;
@@ -420,7 +393,7 @@ __device__ __forceinline__ void sell_slices_run(int n, int s, int stride, const 
     while (s < ns) {
         const int slen = (e - b) / kSell;
         if (s * kSell + lane < n) {
-            const V y = sell_row<V, CI, U, NT, SH>(sv, val, gat, b, slen, rlen, lane, row, n);
+            const V y = sell_row<V, CI, U, NT>(sv, val, gat, b, slen, rlen, lane, row);
             fn(row, y, pre(row));
         }
         s += stride;
@@ -436,6 +409,98 @@ template <class T>
 __device__ __forceinline__ const __attribute__((address_space(4))) T *as_constant(const T *p)
 {
     return (const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
+// The same walk for offsets shared per slice: list and slice pointers are read
+// by scalar loads, a row's mask says which positions it uses, and inside the
+// matrix a gather is a scalar base and the lane, with no vector arithmetic per
+// entry (elsewhere its column is clamped into [0, n) for the positions that a
+// row does not use).  The general walk read the list into vector registers, one
+// more round trip before the gathers, and spent about eight vector instructions
+// an entry on columns: wide product of the 27-point 160^3 system 189 -> 175 us
+// (0.94 GB, all 27 entries of a row in flight; 183, 200, 190 us with 14, 18, 10
+// of them, 239 with the registers held to four waves).
+template <class V, int UP, bool NT, class G, class Go, class Pre, class Fn>
+__device__ __forceinline__ void shared_slices(int n, int s0, int stride, const SellView &sv,
+                                              const V *__restrict__ val, G &&gat, Go &&go, Pre &&pre, Fn &&fn)
+{
+    using VP = typename Pair2<V>::type;
+    using Raw = typename std::remove_reference_t<G>::Raw;
+    const unsigned lane = threadIdx.x & (kWave - 1);
+    const int ns = (n + kSell - 1) / kSell;
+    const auto *ptr = as_constant(sv.ptr);
+    const auto *lists = as_constant(reinterpret_cast<const int32_t *>(sv.col));
+    auto masks = [&](int t) -> uint32_t {
+        const int j = t * kSell + (int)lane;
+        return j < n ? sv.mask[j] : 0u;
+    };
+    int s = __builtin_amdgcn_readfirstlane(s0);
+    int32_t b = 0, e = 0;
+    uint32_t m = 0;
+    if (s < ns) {
+        b = ptr[s];
+        e = ptr[s + 1];
+        m = masks(s);
+    }
+    if (!go()) return;
+    while (s < ns) {
+        const int r0 = s * kSell, row = r0 + (int)lane;
+        const int slen = (e - b) / kSell, np = slen >> 1;
+        const bool odd = slen & 1;
+        const auto *o = lists + b / kSell;
+        const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
+        // the list ascends
+        const bool in = slen > 0 && r0 + o[0] >= 0 && (int64_t)r0 + (kSell - 1) + o[slen - 1] < n;
+        auto gather = [&](int off) -> Raw { return gat.at(min(max(row + off, 0), n - 1)); };
+        // the odd last entry is gathered with the first round and added last
+        V at = V(0);
+        Raw xt{};
+        int ot = 0;
+        if (odd) {
+            ot = o[slen - 1];
+            at = sell_ld<NT>(val + b + (size_t)np * (2 * kSell) + lane);
+        }
+        V acc = V(0);
+        for (int p0 = 0; p0 < np; p0 += UP) {
+            VP a[UP];
+            int c[2 * UP];
+#pragma unroll
+            for (int u = 0; u < UP; ++u) {
+                const int p = min(p0 + u, np - 1);
+                c[2 * u] = o[2 * p];
+                c[2 * u + 1] = o[2 * p + 1];
+                a[u] = sell_ld<NT>(vp + (size_t)p * kSell);
+            }
+            Raw xv[2 * UP];
+            if (in) {
+#pragma unroll
+                for (int u = 0; u < 2 * UP; ++u) xv[u] = gat.sh((int64_t)r0 + c[u], lane);
+                if (p0 == 0 && odd) xt = gat.sh((int64_t)r0 + ot, lane);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 2 * UP; ++u) xv[u] = gather(c[u]);
+                if (p0 == 0 && odd) xt = gather(ot);
+            }
+#pragma unroll
+            for (int u = 0; u < UP; ++u) {
+                const int k = 2 * (p0 + u);
+                if (p0 + u < np) {
+                    if ((m >> k) & 1u) acc = fma(a[u].x, gat.of(xv[2 * u]), acc);
+                    if ((m >> (k + 1)) & 1u) acc = fma(a[u].y, gat.of(xv[2 * u + 1]), acc);
+                }
+            }
+        }
+        if (odd) {
+            if (np == 0) xt = gather(ot);
+            if ((m >> (slen - 1)) & 1u) acc = fma(at, gat.of(xt), acc);
+        }
+        if (row < n) fn(row, acc, pre(row));
+        s += stride;
+        if (s >= ns) break;
+        b = ptr[s];
+        e = ptr[s + 1];
+        m = masks(s);
+    }
 }
 
 // The same walk for a matrix of one value per offset.  With 4 bytes of matrix
@@ -530,13 +595,13 @@ __device__ __forceinline__ void sell_slices_g(int n, int s, int stride, const Se
     } else {
         if constexpr (std::is_same<CI, int32_t>::value) {
             if (sv.mask) {
-                if (plain) sell_slices_run<V, CI, U, false, true>(n, s, stride, sv, val, gat, go, pre, fn);
-                else sell_slices_run<V, CI, U, true, true>(n, s, stride, sv, val, gat, go, pre, fn);
+                if (plain) shared_slices<V, U, false>(n, s, stride, sv, val, gat, go, pre, fn);
+                else shared_slices<V, U, true>(n, s, stride, sv, val, gat, go, pre, fn);
                 return;
             }
         }
-        if (plain) sell_slices_run<V, CI, U, false, false>(n, s, stride, sv, val, gat, go, pre, fn);
-        else sell_slices_run<V, CI, U, true, false>(n, s, stride, sv, val, gat, go, pre, fn);
+        if (plain) sell_slices_run<V, CI, U, false>(n, s, stride, sv, val, gat, go, pre, fn);
+        else sell_slices_run<V, CI, U, true>(n, s, stride, sv, val, gat, go, pre, fn);
     }
 }
 

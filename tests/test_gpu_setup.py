@@ -235,3 +235,59 @@ def test_coarsest_inverse_blocks(n):
             with pytest.raises(spk.SpkError) as e:
                 spk.mg_create(M, (n,), spk.mg_opts(max_levels=1, coarse_max=4096))
             assert e.value.status == spk.EINVAL
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 200, 1031])
+@pytest.mark.parametrize("offsets", [(0,), (-1, 0), (-3, -1, 0, 2), (-130, -64, -1, 0, 1, 64), "first_and_last", "32"])
+def test_shared_offsets_walk_same_bits(offsets, n):
+    """Lists of one to 32 positions, odd and even, with slices whose gathers
+    all fall inside the matrix, partly do, or that are empty: the bits of the
+    walk with an offset per entry, in FP64 and FP32, and where the product is
+    fused with others."""
+    spk = need_gpu()
+    import torch
+
+    if offsets == "first_and_last":
+        offsets = (1 - n, 0, n - 1) if n > 1 else (0,)
+    elif offsets == "32":
+        offsets = tuple(range(-17, 15))
+    rng = np.random.default_rng(n)
+    rows, cols = [], []
+    for o in sorted(offsets):
+        i = np.arange(max(0, -o), min(n, n - o))
+        rows.append(i)
+        cols.append(i + o)
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    keep = (rows // 64 != 1) | (n > 1000)  # an empty slice in the middle
+    rows, cols = rows[keep], cols[keep]
+    order = np.lexsort((cols, rows))
+    rows, cols = rows[order], cols[order]
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    val = np.where(rows == cols, 70.0, 0.0) + rng.standard_normal(rows.size)
+    A = spkgen.CSR(n, rowptr, cols.astype(np.int32), val)
+    x = to_dev(rng.standard_normal(n))
+    lens = np.diff(rowptr)
+    longest = sum(lens[i:i + 64].max() for i in range(0, n, 64))
+    if 16 * sum(_shared_layout(A)[0]) > 17 * longest:  # grows the storage by more than a sixteenth
+        M = mat_on_gpu(spk, A)
+        with pytest.raises(spk.SpkError):
+            spk.mat_set_kernel(M, spk.KERNEL_SELL, spk.SELL_SHARED)
+        return
+    res = []
+    for param in (spk.SELL_SHARED, 32):
+        M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+        spk.mat_set_kernel(M, spk.KERNEL_SELL, param)
+        y, y32 = torch.full_like(x, np.nan), torch.full_like(x.float(), np.nan)
+        spk.mat_mult(M, x, y)
+        spk.mat_mult_f32(M, x.float(), y32)
+        out = [y, y32]
+        if M.info.zero_diag_rows == 0:
+            s = torch.full_like(x, np.nan)
+            spk.pc_chebyshev(M, x, s, 3, 0.2, 2.0)
+            z = torch.zeros_like(x)
+            spk.ksp_solve(M, x, z, spk.ksp_opts(maxit=5, precision=spk.PREC_MIXED))
+            out += [s, z]
+        res.append([o.cpu().numpy() for o in out])
+        M.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b, equal_nan=True)
