@@ -200,27 +200,45 @@ __global__ void k_fill0(int64_t m, double *__restrict__ a)
         a[i] = 0.0;
 }
 
-__global__ void k_axpy(int n, double alpha, const double *__restrict__ x, double *__restrict__ y)
+// out = f(a, b) element by element, kPairs: two a lane (16-byte aligned
+// operands; an odd last element is the last lane's alone).  One launch lane per
+// element or pair.  1.9 M elements (cached): axpy 9.6 -> 8.4 us,
+// aypx 8.7 -> 7.5, the pointwise product 9.4 -> 8.2.
+template <bool kPairs, class F>
+__global__ __launch_bounds__(kBlock) void k_map(int n, const double *a, const double *b, double *out, F f)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = fma(alpha, x[i], y[i]);
+    typedef double D2 __attribute__((ext_vector_type(2)));
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if constexpr (kPairs) {
+        if (2 * t + 1 < n) {
+            const D2 x = reinterpret_cast<const D2 *>(a)[t], y = reinterpret_cast<const D2 *>(b)[t];
+            reinterpret_cast<D2 *>(out)[t] = D2{f(x[0], y[0]), f(x[1], y[1])};
+        } else if (2 * t < n) {
+            out[2 * t] = f(a[2 * t], b[2 * t]);
+        }
+    } else {
+        for (int64_t i = t; i < n; i += (int64_t)gridDim.x * blockDim.x) out[i] = f(a[i], b[i]);
+    }
 }
 
-__global__ void k_aypx(int n, double beta, const double *__restrict__ x, double *__restrict__ y)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = fma(beta, y[i], x[i]);
-}
-
-__global__ void k_pmul(int n, const double *__restrict__ d, const double *__restrict__ r,
-                       double *__restrict__ z)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        z[i] = d[i] * r[i];
-}
+struct Axpy {
+    double alpha;
+    __device__ double operator()(double x, double y) const { return fma(alpha, x, y); }
+};
+struct Aypx {
+    double beta;
+    __device__ double operator()(double x, double y) const { return fma(beta, y, x); }
+};
+struct Mul {
+    __device__ double operator()(double d, double r) const { return d * r; }
+};
 
 // Single-pass dots: per-block partials of x.y (and x.w) over a contiguous
-// chunk per block; k_dot_fin sums them in a fixed order.
+// chunk per block; k_dot_fin sums them in a fixed order.  A lane's next
+// kDotAhead elements are loaded before the first is added: a chunk is a few
+// steps long, and one load a step waited out the memory's latency each time
+// (1.9 M elements, cached: 8.7 -> 7.2 to 8.0 us).
+constexpr int kDotAhead = 4;
 __global__ __launch_bounds__(kBlock) void k_dot(int n, const double *__restrict__ x,
                                                 const double *__restrict__ y,
                                                 const double *__restrict__ w,
@@ -233,10 +251,24 @@ __global__ __launch_bounds__(kBlock) void k_dot(int n, const double *__restrict_
     const int rb = (int)min((int64_t)n, j * chunk);
     const int re = (int)min((int64_t)n, (j + 1) * chunk);
     double a = 0.0, b = 0.0;
-    for (int i = rb + (int)threadIdx.x; i < re; i += kBlock) {
-        const double xi = x[i];
-        a = fma(xi, y[i], a);
-        if (w) b = fma(xi, w[i], b);
+    for (int64_t i0 = rb + (int)threadIdx.x; i0 < re; i0 += kDotAhead * kBlock) {
+        double xv[kDotAhead], yv[kDotAhead], wv[kDotAhead];
+#pragma unroll
+        for (int u = 0; u < kDotAhead; ++u) {
+            const int64_t i = min(i0 + u * kBlock, (int64_t)re - 1);  // past the end: the last one, unused
+            xv[u] = x[i];
+            yv[u] = y[i];
+        }
+        if (w) {
+#pragma unroll
+            for (int u = 0; u < kDotAhead; ++u) wv[u] = w[min(i0 + u * kBlock, (int64_t)re - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kDotAhead; ++u) {
+            if (i0 + u * kBlock >= re) break;
+            a = fma(xv[u], yv[u], a);
+            if (w) b = fma(xv[u], wv[u], b);
+        }
     }
     a = block_sum(a, red);
     if (w) b = block_sum(b, red);
@@ -379,6 +411,23 @@ static int grid_stream(int64_t m)
     if (g > (1 << 22)) g = 1 << 22;
     if (g < 1) g = 1;
     return (int)g;
+}
+
+// Pairs where the operands (at most three vectors) stay in the Infinity Cache;
+// streamed from HBM one element a lane is the faster by 2 % (2^27 elements: 537
+// against 549 us).
+constexpr int kPairsMax = 1 << 23;
+
+template <class F>
+static void launch_map(int n, const double *a, const double *b, double *out, F f, void *stream)
+{
+    const int64_t pairs = ((int64_t)n + 1) / 2;
+    if (n <= kPairsMax && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)out) & 15) == 0)
+        hipLaunchKernelGGL((k_map<true, F>), dim3((unsigned)((pairs + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                           (hipStream_t)stream, n, a, b, out, f);
+    else
+        hipLaunchKernelGGL((k_map<false, F>), dim3(grid_stream(n)), dim3(kBlock), 0, (hipStream_t)stream, n, a, b, out,
+                           f);
 }
 
 static int grid_for(int64_t m)
@@ -1262,8 +1311,7 @@ int spk_pc_jacobi_apply(const spk_mat *A, const double *r, double *z, void *stre
         return SPK_EZERODIAG;
     }
     A->stream = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_pmul, dim3(grid_stream(A->n)), dim3(kBlock), 0, (hipStream_t)stream, A->n,
-                       A->dinv, r, z);
+    launch_map(A->n, (const double *)A->dinv, r, z, Mul{}, stream);
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
@@ -1294,7 +1342,7 @@ int spk_vec_axpy(int32_t n, double alpha, const double *x, double *y, void *stre
 {
     if (n < 0 || (n > 0 && (!x || !y))) { set_error("bad argument"); return SPK_EINVAL; }
     if (n == 0) return SPK_OK;
-    hipLaunchKernelGGL(k_axpy, dim3(grid_stream(n)), dim3(kBlock), 0, (hipStream_t)stream, n, alpha, x, y);
+    launch_map(n, x, y, y, Axpy{alpha}, stream);
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
@@ -1303,7 +1351,7 @@ int spk_vec_aypx(int32_t n, double beta, const double *x, double *y, void *strea
 {
     if (n < 0 || (n > 0 && (!x || !y))) { set_error("bad argument"); return SPK_EINVAL; }
     if (n == 0) return SPK_OK;
-    hipLaunchKernelGGL(k_aypx, dim3(grid_stream(n)), dim3(kBlock), 0, (hipStream_t)stream, n, beta, x, y);
+    launch_map(n, x, y, y, Aypx{beta}, stream);
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }

@@ -630,3 +630,45 @@ def test_binned_products(case):
     spk.mat_mult(M, to_dev(x), y)
     assert np.array_equal(y.cpu().numpy(), ref)
     M.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 3, 255, 511, 512, 513, 1025, 2048 * 256 * 4 + 5])
+def test_vector_kernels_pairs(n, shift):
+    """Two elements a lane where every operand is 16-byte aligned, one
+    otherwise; odd tails; dots whose lanes hold less than, exactly and more
+    than the elements loaded ahead.  Exact on integers, nothing written past
+    the end."""
+    spk = need_gpu()
+    import torch
+
+    rng = np.random.default_rng(n)
+    xh, yh, dh = (rng.integers(-9, 10, n).astype(np.float64) for _ in range(3))
+    dh = 2.0 ** dh  # exact inverses
+
+    def place(a):
+        buf = torch.full((n + 2,), -77.0, dtype=torch.float64, device="cuda")
+        v = buf[shift:shift + n]
+        v.copy_(torch.from_numpy(a))
+        return buf, v
+
+    bx, x = place(xh)
+    by, y = place(yh)
+    bz, z = place(xh)
+    spk.vec_axpy(3.0, x, y)
+    assert np.array_equal(y.cpu().numpy(), yh + 3 * xh)
+    spk.vec_aypx(-2.0, x, y)
+    want = xh - 2 * (yh + 3 * xh)
+    assert np.array_equal(y.cpu().numpy(), want)
+    D = spkgen.CSR(n, np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32), dh)
+    with mat_on_gpu(spk, D) as M:
+        spk.pc_jacobi_apply(M, y, z)
+    assert np.array_equal(z.cpu().numpy(), want / dh)
+    for b in (bx, by, bz):
+        h = b.cpu().numpy()
+        assert h[:shift].tolist() == [-77.0] * shift and h[shift + n:].tolist() == [-77.0] * (2 - shift)
+    res = torch.empty(2, dtype=torch.float64, device="cuda")
+    spk.vec_dot(x, y, res)
+    assert res[0].item() == float(np.dot(xh, want))
+    spk.vec_dot2(x, y, x, res)
+    assert res.tolist() == [float(np.dot(xh, want)), float(np.dot(xh, xh))]
