@@ -350,7 +350,9 @@ static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
     const dim3 g(b.d.nblk), t(kBlock);
     with_sell(A, [&](auto ci, auto uc) {
         using CI = decltype(ci);
-        constexpr int U = decltype(uc)::value;
+        // a start runs once a sequence: one size of round will do for it (the
+        // list for a whole matrix has to fit its round)
+        constexpr int U = kStart && !std::is_same<CI, Stencil>::value ? 4 : decltype(uc)::value;
         hipLaunchKernelGGL((k_pcg_fused_sell<V, CI, U, kStart, One>), g, t, 0, s, b);
     });
 }
