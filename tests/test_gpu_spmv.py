@@ -594,7 +594,7 @@ def _scattered(n, lens, seed):
 
 
 @pytest.mark.parametrize("case", ["one_row", "one_tile", "two_tiles", "bins_1", "bins_2", "bins_2_full", "bins_3",
-                                  "long_row", "empty_rows", "one_bin_used", "no_entries", "bins_512", "bins_513"])
+                                  "long_row", "longest_row", "empty_rows", "one_bin_used", "no_entries", "bins_512", "bins_513"])
 def test_binned_products(case):
     """The sliced family's merge path by column bins and row tiles (beyond 512
     bins: over the slices): exact on integers in FP64 and FP32, twice on the
@@ -607,6 +607,7 @@ def test_binned_products(case):
                "two_tiles": (100, [TILE // 100 - 1] * 99 + [TILE - 99 - 99 * (TILE // 100 - 1)]),
                "bins_1": (BIN, 3), "bins_2": (BIN + 1, 3), "bins_2_full": (2 * BIN, 2), "bins_3": (2 * BIN + 3, 5),
                "long_row": (BIN + 500, [1] * 300 + [5 * TILE + 7] + [2] * (BIN + 199)),
+               "longest_row": (TILE, [1] * 5 + [25 * TILE] + [1] * (TILE - 7) + [8 * TILE]),
                "empty_rows": (3 * TILE, [0] * (TILE + 5) + [40] * 3 + [0] * (2 * TILE - 8)),
                "one_bin_used": (4 * BIN, 1), "no_entries": (300, 0), "bins_512": (512 * BIN, 1),
                "bins_513": (512 * BIN + 1, 1)}[case]
