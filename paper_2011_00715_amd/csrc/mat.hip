@@ -1158,6 +1158,7 @@ int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
 {
     if (!A) { set_error("A is NULL"); return SPK_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
+    ++A->layout_gen;
     // solver graphs and partials depend on the partition: release them after
     // the handle's earlier work has finished
     free_workspace(A);

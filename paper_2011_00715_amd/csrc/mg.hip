@@ -78,8 +78,7 @@ struct spk_mg {
     hipStream_t cap = nullptr;
     hipGraphExec_t g = nullptr;
     int gk = 0;
-    int g_kernel = -1;      // level-0 SpMV family the graph was captured with
-    const void *g_sell = nullptr;
+    uint64_t g_layout = 0;  // level 0's layout the graph was captured with (spk_mat::layout_gen)
     spk::MgTimer *timer = nullptr;  // set while a profiled cycle is enqueued
     int64_t bytes = 0;
     hipStream_t stream = nullptr;   // stream of the latest call that queued work
@@ -663,7 +662,7 @@ static int enqueue_iteration(spk_mg *M, hipStream_t s)
 static int get_graph(spk_mg *M, int K)
 {
     const spk_mat *A0 = M->lev[0].A;
-    if (M->g && M->gk == K && M->g_kernel == A0->kernel && M->g_sell == (const void *)A0->sell_val) return SPK_OK;
+    if (M->g && M->gk == K && M->g_layout == A0->layout_gen) return SPK_OK;
     if (M->g) {
         hipGraphExecDestroy(M->g);
         M->g = nullptr;
@@ -685,8 +684,7 @@ static int get_graph(spk_mg *M, int K)
         return hip_fail(e2, "hipGraphInstantiate", __FILE__, __LINE__);
     }
     M->gk = K;
-    M->g_kernel = A0->kernel;
-    M->g_sell = A0->sell_val;
+    M->g_layout = A0->layout_gen;
     return SPK_OK;
 }
 

@@ -127,6 +127,9 @@ struct spk_mat {
     double *dinv = nullptr;
     float *dinv32 = nullptr;
     bool own_csr = true;
+    // counts spk_mat_set_kernel calls: each may free, build or switch layouts, so
+    // a graph captured elsewhere (a hierarchy's) holds only while it stands
+    uint64_t layout_gen = 0;
     spk::RowStats stats{};
     spk_mat_info info{};
     // SpMV selection

@@ -267,3 +267,35 @@ def test_fp32_cycle_fine_families(kernel):
     x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
     spk.mg_apply(G, to_dev(b), x)
     _close(x.cpu().numpy(), oracle.mg_cycle(h, b), 1e-4, kernel)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solve_follows_the_fine_layout(precision):
+    """Level 0 may change its SpMV layout between solves: every solve on the
+    hierarchy, the replayed ones among them, runs on the layout of the moment
+    and gives the bits of a new hierarchy's first solve on it."""
+    spk = need_gpu()
+    import torch
+
+    A = spkgen.diffusion3d27_lognormal(15, seed=3)
+    opts = spk.mg_opts(coarse_max=64, precision=spk.PREC_MIXED if precision == "mixed" else spk.PREC_FP64)
+    b = to_dev(spkgen.rhs_uniform(A.n, 4))
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    M = mat_on_gpu(spk, A)
+    G = spk.mg_create(M, (15, 15, 15), opts)
+    for kernel, param in ((spk.KERNEL_SLICED, 2048), (spk.KERNEL_SLICED, 4), (spk.KERNEL_SLICED, 2048),
+                          (spk.KERNEL_SELL, 16), (spk.KERNEL_SELL, 32), (spk.KERNEL_SELL, spk.SELL_SHARED),
+                          (spk.KERNEL_SELL_SIGMA, 256), (spk.KERNEL_STREAM, 8), (spk.KERNEL_AUTO, 0)):
+        spk.mat_set_kernel(M, kernel, param)
+        fresh = mat_on_gpu(spk, A)
+        spk.mat_set_kernel(fresh, kernel, param)
+        with spk.mg_create(fresh, (15, 15, 15), opts) as F:
+            ref = torch.zeros_like(x)
+            want = spk.ksp_solve_mg(F, b, ref).iterations
+        fresh.close()
+        for again in range(3):
+            x.zero_()
+            assert spk.ksp_solve_mg(G, b, x).iterations == want, (kernel, param, again)
+            assert torch.equal(x, ref), (kernel, param, again)
+    G.close()
+    M.close()
