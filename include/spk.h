@@ -370,6 +370,12 @@ typedef struct {
  * FP64 iterative refinement (residual, update and test in FP64).
  * Queued on `stream`; returns when the result is known (waits for the
  * stream about once per graph_k iterations, with two batches in flight).
+ * FP64 solves of small matrices run all iterations in one launch whose blocks
+ * wait for each other.  Where something else keeps some of them off the GPU
+ * for seconds, the solve begins again with separate launches (the same bits)
+ * and the handle keeps to those until spk_mat_set_kernel.  The environment's
+ * SPK_RESIDENT_POLLS, read when the handle's workspace is made, sets after
+ * how many polls a wait gives up (testing).
  * opts may be NULL (defaults).  res must not be NULL.
  */
 int spk_ksp_solve(spk_mat *A, const double *b, double *x, const spk_ksp_opts *opts,

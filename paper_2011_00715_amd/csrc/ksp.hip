@@ -164,6 +164,7 @@ static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
             SPK_TRY(dalloc(&w->res_slots, resident_slots(A), w));
             SPK_TRY(dalloc(&w->res_gave_up, 1, w));
             SPK_HIP(hipHostMalloc((void **)&w->res_pgave_up, sizeof(int32_t), hipHostMallocDefault));
+            w->res_polls = resident_polls();
             w->resident = true;
         }
         SPK_HIP(hipHostMalloc((void **)&w->pdesc, sizeof(SysDesc), hipHostMallocDefault));
@@ -494,17 +495,20 @@ struct SolveOut {
     double rnorm0 = 0, rnorm = 0, bnorm = 0, rnorm_true = 0;
 };
 
-// FP64 Jacobi-PCG on w->x (already initialised).
-static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given_residual,
+// FP64 Jacobi-PCG on w->x (already initialised; zero unless x_given).
+static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given,
                    int hist_len, hipStream_t s, SolveOut *out)
 {
-    (void)x_given_residual;
     const int K = w->prof ? 1 : o.graph_k > 0 ? o.graph_k : 8;
     const bool use_graph = o.graph_k > 0 && !w->prof;
     hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, s, w->st, o.rtol, o.atol, o.maxit, 0,
                        o.inner_rtol, o.inner_maxit, o.max_outer, hist_len);
     const One b = batch_of(w, false);
-    const bool resident = w->resident && !w->prof;
+    bool resident = w->resident && !w->prof;
+    // should the blocks lose each other, the solve begins again: its start waits
+    // in q, which the one launch does not use
+    if (resident && x_given)
+        SPK_HIP(hipMemcpyAsync(w->q, w->x, sizeof(double) * A->n, hipMemcpyDeviceToDevice, s));
     SPK_TRY(launch_resid(A, w, false, kResSetup, false, s));
     hipLaunchKernelGGL(k_setup64<One>, dim3(b.d.nblk), dim3(kBlock), 0, s, b);
     hipLaunchKernelGGL(k_fin_setup64<One>, dim3(1), dim3(kBlock), 0, s, b);
@@ -513,9 +517,11 @@ static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given
     for (;;) {
         bool ran = false;
         if (resident) {
-            SPK_TRY(launch_resident(A, b.d, w->res_slots, w->res_gave_up, s, &ran));
+            SPK_TRY(launch_resident(A, b.d, w->res_slots, w->res_gave_up, w->res_polls, s, &ran));
             if (ran)
                 SPK_HIP(hipMemcpyAsync(w->res_pgave_up, w->res_gave_up, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            else
+                resident = false;  // the batches use q
         }
         if (!ran) {
             SPK_TRY(read_state(w, s));
@@ -526,8 +532,12 @@ static int solve64(spk_mat *A, Workspace *w, const spk_ksp_opts &o, bool x_given
         SPK_TRY(launch_resid(A, w, false, kResTrue, false, s));
         SPK_TRY(read_state(w, s));
         if (ran && *w->res_pgave_up) {
-            set_error("the solve's blocks lost each other");
-            return SPK_EHIP;
+            // not all blocks ran at once (something else holds the GPU): the same
+            // solve by separate launches, here and from now on with this workspace
+            w->resident = false;
+            if (x_given) SPK_HIP(hipMemcpyAsync(w->x, w->q, sizeof(double) * A->n, hipMemcpyDeviceToDevice, s));
+            else fill_zero(w->x, A->n, s);
+            return solve64(A, w, o, x_given, hist_len, s, out);
         }
         const SysState &S = *w->pst;
         const bool conv = S.status == SPK_CONVERGED_RTOL || S.status == SPK_CONVERGED_ATOL;
@@ -994,7 +1004,7 @@ int spk_ksp_solve(spk_mat *A, const double *b, double *x, const spk_ksp_opts *op
     } else if (o.single_reduction) {
         SPK_TRY(solve_sr(A, w, o, o.hist_len, s, &out));
     } else {
-        SPK_TRY(solve64(A, w, o, false, o.hist_len, s, &out));
+        SPK_TRY(solve64(A, w, o, o.x0_nonzero != 0, o.hist_len, s, &out));
     }
     SPK_HIP(hipMemcpyAsync(x, w->x, sizeof(double) * A->n, hipMemcpyDeviceToDevice, s));
     if (o.hist_len > 0 && !fallback)

@@ -1,5 +1,6 @@
 // Launch of the one-launch PCG iterations (resident.hpp).
 #include <algorithm>
+#include <cstdlib>
 
 #include "resident.hpp"
 #include "runtime.hpp"
@@ -45,14 +46,21 @@ static hipError_t launch(const spk_mat *A, ResidentArgs a, int nslots, hipStream
                                       dim3(kResMany), args, 0u, s);
 }
 
+int resident_polls()
+{
+    const char *e = getenv("SPK_RESIDENT_POLLS");
+    return e ? std::max(atoi(e), 0) : kResPolls;
+}
+
 // Runs the iterations of the FP64 solve whose descriptor is d (p2 set, one
 // tile per block) on the stream; *done says whether it was launched (the
 // caller iterates otherwise).  gave_up (device) is nonzero afterwards if the
-// blocks lost each other.
-int launch_resident(const spk_mat *A, const SysDesc &d, unsigned long long *slots, int32_t *gave_up, hipStream_t s,
-                    bool *done)
+// blocks lost each other; x, r and the state then hold nothing of use.
+// d.q is not touched.
+int launch_resident(const spk_mat *A, const SysDesc &d, unsigned long long *slots, int32_t *gave_up, int polls,
+                    hipStream_t s, bool *done)
 {
-    const ResidentArgs a{d, slots, gave_up};
+    const ResidentArgs a{d, slots, gave_up, polls};
     hipError_t e = hipErrorInvalidValue;
     with_sell_ci(A->sell_cw, A->sell_plain, [&](auto ci) {
         using CI = decltype(ci);

@@ -55,13 +55,15 @@ constexpr int kResRing = 3;
 // An empty slot: a NaN that a published sum never is (NaNs are published as
 // the canonical one).
 constexpr unsigned long long kResEmpty = 0x7ff4dead00c0ffeeull;
-// Polls of a slot before a block gives up (seconds): every wait ends.
-constexpr int kResSpins = 1 << 21;
+// Polls of a slot before a block gives up (seconds): every wait ends, also where
+// something else holds the CUs that the other blocks need.
+constexpr int kResPolls = 1 << 21;
 
 struct ResidentArgs {
     SysDesc d;
     unsigned long long *slots;  // [kResRing][2][nblk + kResGroups], all kResEmpty on entry
     int32_t *gave_up;           // set when a wait ran out
+    int polls;                  // of a slot, before a block gives up
 };
 
 template <class T>
@@ -273,9 +275,13 @@ __global__ __launch_bounds__(kResOne) void k_pcg_resident_one(ResidentArgs a)
 // every block reading every tile, all blocks' polls met on the few memory
 // channels that hold the slots: 152 k rows took 18.6 us an iteration with
 // blocks of one tile, 10.2 with blocks of four.
+// A block whose wait runs out leaves for good, and so do those that wait for it
+// at this meeting or the next.  At a solve's last meeting some may leave and
+// others finish: x, r and the state are then of no use.
 struct Meeting {
     unsigned long long *slots;
     int32_t *gave_up;
+    int polls;
     double *ws;     // [2][kResMany / kWave]
     double *group;  // [2][kResGroups]
     int nblk, turn = 0;
@@ -289,13 +295,13 @@ struct Meeting {
     // Waits for P slots, stride apart, of which this lane has the first cnt;
     // all of a round's loads are in flight together.
     template <int P>
-    static __device__ __forceinline__ void wait_slots(unsigned long long *p, int stride, int cnt,
-                                                      unsigned long long (&v)[P], bool &ok)
+    __device__ __forceinline__ void wait_slots(unsigned long long *p, int stride, int cnt,
+                                               unsigned long long (&v)[P], bool &ok) const
     {
 #pragma unroll
         for (int u = 0; u < P; ++u) v[u] = u < cnt ? ld_agent(p + (size_t)u * stride) : 0;
         bool all = false;
-        for (int k = 0; k < kResSpins; ++k) {
+        for (int k = 0; k < polls; ++k) {
             all = true;
 #pragma unroll
             for (int u = 0; u < P; ++u) all &= v[u] != kResEmpty;
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(kResMany, kResPerCu * kResMany / kWave / 4) void k_
         dinv = d.dinv[row];
     }
     const SellView sv{d.sell_ptr, d.sell_col, d.sell_len, d.sell_plain, d.sell_len16, d.sell_perm, d.sell_mask};
-    Meeting meet{a.slots, a.gave_up, ws, group, nblk};
+    Meeting meet{a.slots, a.gave_up, a.polls, ws, group, nblk};
     ResScalars c;
     c.rho = ss.rho;
     c.rn = ss.rnorm;

@@ -92,12 +92,14 @@ struct Workspace {
     void *sc = nullptr;           // device scalars of the single-reduction recurrences
     int64_t bytes = 0;
     int nblk64 = 0;               // blocks of an FP64 solve (fp64_blocks)
-    // iterations in one launch (small systems): the blocks' meeting slots and
-    // the flag of a wait that ran out, with a pinned copy
+    // iterations in one launch (small systems; off once its blocks have lost
+    // each other): the blocks' meeting slots and the flag of a wait that ran out,
+    // with a pinned copy
     bool resident = false;
     unsigned long long *res_slots = nullptr;
     int32_t *res_gave_up = nullptr;
     int32_t *res_pgave_up = nullptr;
+    int res_polls = 0;
     // profiled solves: one event pair around each iteration's product, in
     // launch order; `alive` is cleared for launches queued after the solve
     // had stopped
@@ -226,8 +228,9 @@ void update_info(spk_mat *A);
 // iterations of small FP64 solves in one launch (resident.hip)
 bool resident_fits(const spk_mat *A);
 int64_t resident_slots(const spk_mat *A);
-int launch_resident(const spk_mat *A, const SysDesc &d, unsigned long long *slots, int32_t *gave_up, hipStream_t s,
-                    bool *done);
+int resident_polls();
+int launch_resident(const spk_mat *A, const SysDesc &d, unsigned long long *slots, int32_t *gave_up, int polls,
+                    hipStream_t s, bool *done);
 constexpr double kRuDelta = 0.05;  // default refinement trigger with reliable updates
 double inner_rtol_of(const spk_ksp_opts &o);
 int ensure_f32(spk_mat *A, hipStream_t s);

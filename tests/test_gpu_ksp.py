@@ -458,3 +458,30 @@ def test_pcg_one_launch_stops(n):
         assert np.array_equal(x, y, equal_nan=True) and np.array_equal(ha, hb, equal_nan=True)
         assert (ra.reason, ra.iterations, ra.restarts) == (rb.reason, rb.iterations, rb.restarts)
         M.close()
+
+
+@pytest.mark.parametrize("polls", [0, 1, 4, 64])
+@pytest.mark.parametrize("n,start", [(4097, False), (20481, True), (262144, False)])
+def test_pcg_one_launch_gives_up(monkeypatch, n, start, polls):
+    """Blocks that lose each other, at the first poll or anywhere later, cost
+    the solve time and nothing else: counts, history and solution are those of
+    the launched iteration bit for bit, and so are the next solve's."""
+    spk = need_gpu()
+    monkeypatch.setenv("SPK_RESIDENT_POLLS", str(polls))
+    A = spkgen.laplace_grid((n,), 0.25)
+    M = mat_on_gpu(spk, A)
+    spk.mat_set_kernel(M, spk.KERNEL_SELL, 0)
+    for seed in (4, 5):
+        b = spkgen.rhs_uniform(n, seed)
+        x0 = spkgen.rhs_uniform(n, seed + 10) if start else None
+        x, res, hist = _solve(spk, M, b, hist_len=64, x0=x0)
+        xp, rp, hp = _solve(spk, M, b, hist_len=64, x0=x0, profile=1)
+        assert res.reason == spk.CONVERGED_RTOL, res.as_dict()
+        assert np.array_equal(x, xp) and np.array_equal(hist, hp, equal_nan=True)
+        assert (res.iterations, res.restarts, res.rnorm) == (rp.iterations, rp.restarts, rp.rnorm)
+    # the iteration limits, and a tolerance that cannot be met
+    for kw in ({"maxit": 0}, {"rtol": 1e-17, "maxit": 300}):
+        x, res, _ = _solve(spk, M, b, **kw)
+        xp, rp, _ = _solve(spk, M, b, profile=1, **kw)
+        assert np.array_equal(x, xp) and (res.reason, res.iterations) == (rp.reason, rp.iterations)
+    M.close()
