@@ -28,6 +28,9 @@ void set_error(const char *fmt, ...)
 
 int hip_fail(hipError_t e, const char *what, const char *file, int line)
 {
+    // the runtime keeps an error until it is read: left there, the launch checks
+    // of a fallback, or of the program's own kernels, would report it again
+    (void)hipGetLastError();
     set_error("%s failed: %s (%s:%d)", what, hipGetErrorString(e), file, line);
     return e == hipErrorOutOfMemory ? SPK_ENOMEM : SPK_EHIP;
 }

@@ -747,7 +747,9 @@ int spk_server_create(const spk_server_opts *opts, void *stream, spk_server **ou
     S->s = (hipStream_t)stream;
     int rc = SPK_OK;
     auto chk = [&](hipError_t e, const char *what) {
-        if (e != hipSuccess && rc == SPK_OK) rc = hip_fail(e, what, __FILE__, __LINE__);
+        if (e == hipSuccess) return;
+        if (rc == SPK_OK) rc = hip_fail(e, what, __FILE__, __LINE__);
+        else (void)hipGetLastError();  // the first error is reported; this one is read too
     };
     chk(hipGetDevice(&S->dev), "hipGetDevice");
     chk(hipMalloc(&S->arena_base, o.hbm_budget_bytes), "arena hipMalloc");
@@ -788,6 +790,7 @@ int spk_server_create(const spk_server_opts *opts, void *stream, spk_server **ou
             S->pin_arena.init(o.pinned_bytes);
             touch_pages(S->pin_base, o.pinned_bytes);
         } else {
+            (void)hipGetLastError();
             S->pin_base = nullptr;
         }
     }

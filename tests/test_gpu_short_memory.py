@@ -1,0 +1,116 @@
+"""Calls whose allocations fail: what has another layout to take takes it and
+works, what has not returns an error, and either way neither the handle nor
+the program's own HIP calls are left with it.
+
+A child process loads a stand-in for hipMalloc (short_memory.c) that lets
+chosen requests fail in the runtime itself."""
+
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from gpu_util import need_gpu
+
+pytestmark = pytest.mark.gpu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path[:0] = [sys.argv[2], sys.argv[3]]
+import numpy as np
+import torch
+import spkgen, oracle
+from paper_2011_00715_amd import spk
+from gpu_util import mat_on_gpu, to_dev
+from test_gpu_spmv import _scattered
+hip = [l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64.so" in l][0]
+shim.short_memory_real(ctypes.cast(ctypes.CDLL(hip).hipMalloc, ctypes.c_void_p))
+torch.ones(1, device="cuda").add_(1)
+
+def short(lo, hi=1 << 50, count=1):
+    shim.short_memory(ctypes.c_size_t(lo), ctypes.c_size_t(hi), count)
+
+def failed():
+    left = shim.short_memory_left()
+    shim.short_memory(ctypes.c_size_t(1), ctypes.c_size_t(0), 0)
+    assert left == 0, "no request of this size was made"
+
+def works(M, A, f32=False):
+    torch.ones(1, device="cuda").add_(1)  # raises if an error was left behind
+    x = np.random.default_rng(1).integers(-50, 50, A.n).astype(np.float64)
+    ref = oracle.spmv(A, x)
+    y = to_dev(np.full(A.n, np.nan))
+    spk.mat_mult(M, to_dev(x), y)
+    assert np.array_equal(y.cpu().numpy(), ref)
+    if f32:
+        y = to_dev(np.full(A.n, np.nan, np.float32))
+        spk.mat_mult_f32(M, to_dev(x.astype(np.float32)), y)
+        assert np.array_equal(y.cpu().numpy(), ref.astype(np.float32))
+"""
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    need_gpu()
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if not cc:
+        pytest.skip("no C compiler")
+    so = str(tmp_path_factory.mktemp("shim") / "short_memory.so")
+    subprocess.run([cc, "-shared", "-fPIC", "-O1", os.path.join(HERE, "short_memory.c"), "-o", so], check=True)
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-u", "-c", PRELUDE + code + "\nprint('done')", so, os.path.dirname(HERE),
+                            HERE], capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout + r.stderr
+
+    return run
+
+
+def test_no_room_for_the_binned_copy(child):
+    """The sliced family keeps to the slices, on request and by itself."""
+    child("""
+n = 40000
+A = _scattered(n, [5] * (n - 1) + [3000], 7)
+M = mat_on_gpu(spk, A)
+short(20 * A.nnz)
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+failed()
+assert spk.KERNEL_NAMES[M.info.kernel] == "sliced" and M.info.lanes == 2048
+works(M, A)
+M.close()
+
+n = 1 << 19
+A = _scattered(n, [8] * (n - 1) + [4000], 3)
+M = mat_on_gpu(spk, A)
+assert spk.KERNEL_NAMES[M.info.kernel] == "sliced"
+M.close()
+short(20 * A.nnz)
+M = mat_on_gpu(spk, A)
+failed()
+assert spk.KERNEL_NAMES[M.info.kernel] == "sliced"
+works(M, A)
+M.close()
+""")
+
+
+def test_an_error_is_not_left_behind(child):
+    """A handle refused for want of memory leaves the program's own launches alone."""
+    child("""
+A = spkgen.laplace3d7(24)
+csr = to_dev(A.rowptr), to_dev(A.col), to_dev(A.val)
+M = mat_on_gpu(spk, A)
+for lo, call in ((8 * A.nnz, lambda: spk.mat_create_csr(*csr)), (1, lambda: spk.server_create())):
+    short(lo)
+    try:
+        call()
+        raise SystemExit("created without memory")
+    except spk.SpkError as e:
+        assert e.status == spk.ENOMEM, e
+    failed()
+    works(M, A)
+""")
