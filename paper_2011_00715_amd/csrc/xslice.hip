@@ -236,7 +236,9 @@ static int setup_binned(spk_mat *A, hipStream_t s)
         free_binned(A);
         return hip_fail(e, "binned layout", __FILE__, __LINE__);
     }
-    return A->val32 ? ensure_sliced_f32(A, s) : SPK_OK;
+    const int rc = A->val32 ? ensure_sliced_f32(A, s) : SPK_OK;
+    if (rc != SPK_OK) free_binned(A);  // no half a copy beside what the caller takes instead
+    return rc;
 }
 
 static int setup_slices(spk_mat *A, hipStream_t s)
@@ -278,6 +280,7 @@ static int setup_slices(spk_mat *A, hipStream_t s)
     hipFree(cnt);
     hipFree(bsum);
     if (A->val32) rc = ensure_sliced_f32(A, s);
+    if (rc != SPK_OK) free_slices(A);
     return rc;
 }
 

@@ -6,25 +6,27 @@
 typedef int (*malloc_fn)(void **, size_t);
 static malloc_fn real;
 static size_t fail_lo = 1, fail_hi = 0;
-static int fail_left = 0;
+static unsigned fail_mask = 0;
 
 void short_memory_real(malloc_fn f) { real = f; }
 
-/* The next `count` requests of lo to hi bytes fail. */
-void short_memory(size_t lo, size_t hi, int count)
+/* Of the next requests of lo to hi bytes, the i-th (from 0) fails where bit i of `mask` is set. */
+void short_memory(size_t lo, size_t hi, unsigned mask)
 {
     fail_lo = lo;
     fail_hi = hi;
-    fail_left = count;
+    fail_mask = mask;
 }
 
-int short_memory_left(void) { return fail_left; }
+/* The requests of the mask that have not come yet. */
+unsigned short_memory_left(void) { return fail_mask; }
 
 int hipMalloc(void **p, size_t bytes)
 {
-    if (fail_left > 0 && bytes >= fail_lo && bytes <= fail_hi) {
-        --fail_left;
-        return real(p, (size_t)1 << 60); /* more than any device has: the runtime's own error */
+    if (bytes >= fail_lo && bytes <= fail_hi) {
+        const int fail = fail_mask & 1;
+        fail_mask >>= 1;
+        if (fail) return real(p, (size_t)1 << 60); /* more than any device has: the runtime's own error */
     }
     return real(p, bytes);
 }

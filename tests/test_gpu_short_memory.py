@@ -32,8 +32,8 @@ hip = [l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64.so" in l][
 shim.short_memory_real(ctypes.cast(ctypes.CDLL(hip).hipMalloc, ctypes.c_void_p))
 torch.ones(1, device="cuda").add_(1)
 
-def short(lo, hi=1 << 50, count=1):
-    shim.short_memory(ctypes.c_size_t(lo), ctypes.c_size_t(hi), count)
+def short(lo, hi=1 << 50, mask=1):
+    shim.short_memory(ctypes.c_size_t(lo), ctypes.c_size_t(hi), mask)
 
 def failed():
     left = shim.short_memory_left()
@@ -113,4 +113,27 @@ for lo, call in ((8 * A.nnz, lambda: spk.mat_create_csr(*csr)), (1, lambda: spk.
         assert e.status == spk.ENOMEM, e
     failed()
     works(M, A)
+""")
+
+
+def test_no_room_for_fp32_values(child):
+    """A copy goes where its FP32 values do not fit: nothing is kept that no
+    product uses."""
+    child("""
+n = 40000
+A = _scattered(n, [5] * (n - 1) + [3000], 7)
+M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+before = M.info.device_bytes
+short(4 * A.nnz, 4 * A.nnz + 8, mask=0b101)  # the binned FP32 values, not the slices' columns, their FP32 values
+try:
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+    raise SystemExit("found room")
+except spk.SpkError as e:
+    assert e.status == spk.ENOMEM, e
+failed()
+spk.mat_set_kernel(M, spk.KERNEL_VECTOR, 8)
+assert M.info.device_bytes == before
+works(M, A, True)
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+works(M, A, True)
 """)
