@@ -191,7 +191,7 @@ struct spk_mat {
     void *bn_prod = nullptr;           // products (FP64 or FP32)
     int32_t *bn_carry_row = nullptr;
     void *bn_carry_val = nullptr;
-    int64_t bn_bytes = 0;
+    int64_t xs_bytes = 0, bn_bytes = 0;  // what the two copies count in `bytes`
     spk::Workspace *ws = nullptr;
     spk::MultiWs *mws = nullptr;  // multi-right-hand-side solver workspace
     int64_t bytes = 0;

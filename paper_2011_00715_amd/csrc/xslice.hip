@@ -104,7 +104,6 @@ static int setup_sliced_merge(spk_mat *A, hipStream_t s)
 static void free_binned(spk_mat *A)
 {
     hipFree(A->bn_slab);
-    if (A->bn_val32) A->bytes -= 4 * (A->nnz + 2);
     hipFree(A->bn_val32);
     A->bytes -= A->bn_bytes;
     A->bn_slab = nullptr;
@@ -116,10 +115,8 @@ static void free_binned(spk_mat *A)
 static void free_slices(spk_mat *A)
 {
     free_sliced_merge(A);
-    if (A->xs_ptr) {
-        A->bytes -= 4 * ((int64_t)kSlices * A->n + 1) + 12 * A->nnz + 8 * (int64_t)kSlices * A->n;
-        if (A->xs_val32) A->bytes -= 4 * A->nnz;
-    }
+    A->bytes -= A->xs_bytes;
+    A->xs_bytes = 0;
     hipFree(A->xs_ptr);
     hipFree(A->xs_col);
     hipFree(A->xs_val);
@@ -144,15 +141,17 @@ int ensure_sliced_f32(spk_mat *A, hipStream_t s)
         SPK_HIP(hipMalloc(&A->bn_val32, sizeof(float) * ((size_t)A->nnz + 2)));
         hipLaunchKernelGGL(k_xs_f32, dim3(grid_rows(A->nnz)), dim3(kBlock), 0, s, A->nnz, (const double *)A->bn_val,
                            A->bn_val32);
-        SPK_HIP(hipGetLastError());
         A->bytes += 4 * (A->nnz + 2);
+        A->bn_bytes += 4 * (A->nnz + 2);
+        SPK_HIP(hipGetLastError());
     }
     if (!A->xs_ptr || A->xs_val32 || A->nnz == 0) return SPK_OK;
     SPK_HIP(hipMalloc(&A->xs_val32, sizeof(float) * (size_t)A->nnz));
     hipLaunchKernelGGL(k_xs_f32, dim3(grid_rows(A->nnz)), dim3(kBlock), 0, s, A->nnz, (const double *)A->xs_val,
                        A->xs_val32);
-    SPK_HIP(hipGetLastError());
     A->bytes += 4 * A->nnz;
+    A->xs_bytes += 4 * A->nnz;
+    SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
 
@@ -256,7 +255,7 @@ static int setup_slices(spk_mat *A, hipStream_t s)
     auto fail = [&](hipError_t e, const char *what) {
         hipFree(cnt);
         hipFree(bsum);
-        free_sliced(A);
+        free_slices(A);
         return hip_fail(e, what, __FILE__, __LINE__);
     };
     hipError_t e = hipMalloc(&cnt, sizeof(int32_t) * (size_t)rows);
@@ -266,7 +265,8 @@ static int setup_slices(spk_mat *A, hipStream_t s)
     if (e == hipSuccess) e = hipMalloc(&A->xs_val, sizeof(double) * (size_t)std::max<int64_t>(A->nnz, 1));
     if (e == hipSuccess) e = hipMalloc(&A->xs_part, sizeof(double) * (size_t)rows);
     if (e != hipSuccess) return fail(e, "hipMalloc");
-    A->bytes += 4 * ((int64_t)rows + 1) + 12 * A->nnz + 8 * (int64_t)rows;
+    A->xs_bytes = 4 * ((int64_t)rows + 1) + 12 * A->nnz + 8 * (int64_t)rows;
+    A->bytes += A->xs_bytes;
     hipLaunchKernelGGL(k_xs_count, dim3(grid_rows(n)), dim3(kBlock), 0, s, n, (const int32_t *)A->rowptr,
                        (const int32_t *)A->col, cnt);
     e = scan_exclusive(rows, cnt, A->xs_ptr, bsum, s);
@@ -296,6 +296,12 @@ int setup_sliced(spk_mat *A, int merge, hipStream_t s)
         return SPK_OK;
     }
     int rc = setup_slices(A, s);
+    if (rc == SPK_ENOMEM && A->bn_slab) {
+        // the binned copy makes room, and comes back where that is not enough
+        free_binned(A);
+        rc = setup_slices(A, s);
+        if (rc != SPK_OK) (void)setup_binned(A, s);
+    }
     if (rc == SPK_OK && merge) rc = setup_sliced_merge(A, s);
     if (rc == SPK_OK) free_binned(A);
     return rc;

@@ -137,3 +137,36 @@ works(M, A, True)
 spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
 works(M, A, True)
 """)
+
+
+def test_no_room_for_two_copies(child):
+    """From the binned copy to the slices: it makes room for them, and is there
+    again where they do not fit even so."""
+    child("""
+n = 40000
+A = _scattered(n, [5] * (n - 1) + [3000], 7)
+M = mat_on_gpu(spk, A)
+before = M.info.device_bytes
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+binned = M.info.device_bytes
+short(8 * A.nnz, mask=1)  # the slices' values, once
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 4)
+failed()
+assert M.info.lanes == 4
+works(M, A)
+slices = M.info.device_bytes
+assert slices == before + 12 * A.nnz + 4 * (8 * n + 1) + 8 * 8 * n
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+assert M.info.device_bytes == binned
+short(8 * A.nnz, mask=0b11)  # twice
+try:
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, 4)
+    raise SystemExit("found room")
+except spk.SpkError as e:
+    assert e.status == spk.ENOMEM, e
+failed()
+assert M.info.lanes == 2048
+works(M, A)
+spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+assert M.info.device_bytes == binned
+""")
