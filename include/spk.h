@@ -234,7 +234,8 @@ int spk_mat_create_csr(int32_t n, int64_t nnz, const int32_t *rowptr,
  * Waits for the handle's earlier work (the stream of its latest call), then
  * builds the layout the family needs on `stream` and returns once it is
  * built (it synchronises `stream` only).  Invalidates cached solver graphs
- * and releases the solver workspaces, which the next solve re-creates. */
+ * and releases the solver workspaces, which the next solve re-creates.  A
+ * refused request leaves the family and layout as they were. */
 int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream);
 
 /* y = A x (Sec. 4: MatMult on an AIJ matrix).  x, y: device double[n],

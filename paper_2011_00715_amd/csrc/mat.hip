@@ -1157,16 +1157,8 @@ int spk_mat_create_csr(int32_t n, int64_t nnz, const int32_t *rowptr, const int3
     return SPK_OK;
 }
 
-int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
+static int set_kernel(spk_mat *A, int kernel, int32_t param, hipStream_t s)
 {
-    if (!A) { set_error("A is NULL"); return SPK_EINVAL; }
-    hipStream_t s = (hipStream_t)stream;
-    ++A->layout_gen;
-    // solver graphs and partials depend on the partition: release them after
-    // the handle's earlier work has finished
-    free_workspace(A);
-    free_multi(A);
-    A->stream = s;
     switch (kernel) {
     case SPK_KERNEL_AUTO: choose_kernel(A); break;
     case SPK_KERNEL_STREAM: {
@@ -1276,9 +1268,58 @@ int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
             }
         }
     }
+    return SPK_OK;
+}
+
+// After a refused set_kernel: the family and layout of before it (`was`), or,
+// where that layout is gone and does not fit any more, a family without one.
+struct KernelChoice {
+    int kernel, R, lanes, xs_merge, sell_req, sell_sigma;
+};
+static void keep_kernel(spk_mat *A, const KernelChoice &was, hipStream_t s)
+{
+    A->kernel = was.kernel;
+    A->R = was.R;
+    A->lanes = was.lanes;
+    A->xs_merge = was.xs_merge;
+    bool there = true;
+    if (was.kernel == SPK_KERNEL_SELL) {
+        // (built again if the request took it down)
+        there = setup_sell(A, s, was.sell_req, was.sell_sigma) == SPK_OK &&
+                (!A->val32 || (ensure_f32(A, s) == SPK_OK && hipStreamSynchronize(s) == hipSuccess));
+    } else if (was.kernel == SPK_KERNEL_SLICED) {
+        there = A->xs_merge ? A->bn_slab || A->xs_tiles : A->xs_ptr != nullptr;
+    }
+    if (!there || A->sell_req < 0) free_sell(A);  // half a layout
+    if (there) return;
+    choose_kernel(A, false, false);
+    if (A->kernel == SPK_KERNEL_MERGE && setup_merge(A, s) != SPK_OK) {
+        A->kernel = SPK_KERNEL_VECTOR;  // the one that needs no memory at all
+        A->lanes = 32;
+    }
+}
+
+int spk_mat_set_kernel(spk_mat *A, int kernel, int32_t param, void *stream)
+{
+    if (!A) { set_error("A is NULL"); return SPK_EINVAL; }
+    hipStream_t s = (hipStream_t)stream;
+    ++A->layout_gen;
+    // solver graphs and partials depend on the partition: release them after
+    // the handle's earlier work has finished
+    free_workspace(A);
+    free_multi(A);
+    A->stream = s;
+    const KernelChoice was{A->kernel, A->R, A->lanes, A->xs_merge, A->sell_req, A->sell_sigma};
+    const int rc = set_kernel(A, kernel, param, s);
+    if (rc != SPK_OK) {
+        char why[sizeof g_err];
+        memcpy(why, g_err, sizeof why);
+        keep_kernel(A, was, s);
+        memcpy(g_err, why, sizeof why);
+    }
     apply_partition(A);
     update_info(A);
-    return SPK_OK;
+    return rc;
 }
 
 int spk_mat_mult(const spk_mat *A, const double *x, double *y, void *stream)

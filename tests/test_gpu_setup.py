@@ -291,3 +291,52 @@ def test_shared_offsets_walk_same_bits(offsets, n):
         M.close()
     for a, b in zip(*res):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+def _shuffled(n, seed):
+    """A diagonally dominant tridiagonal matrix, rows and columns permuted alike:
+    few entries a row, far more than 32 offsets a slice."""
+    A = spkgen.laplace_grid((n,), 0.25)
+    to = np.random.default_rng(seed).permutation(n)
+    row, col = to[np.repeat(np.arange(n), np.diff(A.rowptr))], to[A.col]
+    order = np.lexsort((col, row))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))]).astype(np.int32)
+    return spkgen.CSR(n, rowptr, col[order].astype(np.int32), A.val[order])
+
+
+@pytest.mark.parametrize("kernel,param", [("AUTO", 0), ("SELL", 16), ("SELL", 32), ("SELL_SIGMA", 256), ("STREAM", 8),
+                                          ("VECTOR", 4), ("MERGE", 0), ("SLICED", 4), ("SLICED", 2048)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_refused_kernel_changes_nothing(kernel, param, flags):
+    """Offsets that slices cannot share are found out while building: the
+    handle goes on with the layout it had, bit for bit, in every call."""
+    spk = need_gpu()
+    import torch
+
+    A = _shuffled(3000, 5)
+    ref, M = (mat_on_gpu(spk, A, flags=flags) for _ in range(2))
+    for m in (ref, M):
+        spk.mat_set_kernel(m, getattr(spk, "KERNEL_" + kernel), param)
+    for k, p in ((spk.KERNEL_SELL, spk.SELL_SHARED), (spk.KERNEL_VECTOR, 3), (spk.KERNEL_SELL_SIGMA, 100), (99, 0)):
+        with pytest.raises(spk.SpkError) as e:
+            spk.mat_set_kernel(M, k, p)
+        assert e.value.status == spk.EINVAL
+    M.info = spk.mat_get_info(M)
+    assert (M.info.kernel, M.info.lanes, M.info.stored_nnz) == (
+        ref.info.kernel, ref.info.lanes, ref.info.stored_nnz)
+    assert M.info.device_bytes <= ref.info.device_bytes  # a SELL copy that is not in use goes
+    if M.info.kernel == spk.KERNEL_SELL:
+        assert M.info.device_bytes == ref.info.device_bytes
+    b = to_dev(spkgen.rhs_uniform(A.n, 1))
+
+    def outputs(m):
+        y, x, z = (torch.zeros_like(b) for _ in range(3))
+        spk.mat_mult(m, b, y)
+        spk.ksp_solve(m, b, x, spk.ksp_opts(precision=spk.PREC_MIXED if flags else spk.PREC_FP64))
+        spk.pc_chebyshev(m, b, z, 3)
+        return y, x, z
+
+    for got, want in zip(outputs(M), outputs(ref)):
+        assert torch.equal(got, want)
+    ref.close()
+    M.close()
