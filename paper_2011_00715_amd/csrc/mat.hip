@@ -613,10 +613,19 @@ static int setup_merge(spk_mat *A, hipStream_t s)
     const int64_t items = (int64_t)A->n + A->nnz;
     A->mtiles = (int)((items + kMergeItems - 1) / kMergeItems);
     const int mt = A->mtiles > 0 ? A->mtiles : 1;
-    SPK_HIP(hipMalloc(&A->tile_row, sizeof(int32_t) * (mt + 1)));
-    SPK_HIP(hipMalloc(&A->tile_k, sizeof(int32_t) * (mt + 1)));
-    SPK_HIP(hipMalloc(&A->carry_row, sizeof(int32_t) * mt));
-    SPK_HIP(hipMalloc(&A->carry_val, sizeof(double) * mt));
+    hipError_t e = hipMalloc(&A->tile_row, sizeof(int32_t) * (mt + 1));
+    if (e == hipSuccess) e = hipMalloc(&A->tile_k, sizeof(int32_t) * (mt + 1));
+    if (e == hipSuccess) e = hipMalloc(&A->carry_row, sizeof(int32_t) * mt);
+    if (e == hipSuccess) e = hipMalloc(&A->carry_val, sizeof(double) * mt);
+    if (e != hipSuccess) {  // all four or none: tile_row says that they are there
+        hipFree(A->tile_row);
+        hipFree(A->tile_k);
+        hipFree(A->carry_row);
+        hipFree(A->carry_val);
+        A->tile_row = A->tile_k = A->carry_row = nullptr;
+        A->carry_val = nullptr;
+        return hip_fail(e, "merge path", __FILE__, __LINE__);
+    }
     A->bytes += (int64_t)mt * 20 + 8;
     hipLaunchKernelGGL(k_merge_partition, dim3(ceil_div(A->mtiles + 1, kBlock)), dim3(kBlock), 0, s,
                        A->n, (int)A->nnz, A->rowptr, A->mtiles, kMergeItems, A->tile_row, A->tile_k);
@@ -1095,8 +1104,8 @@ static int create_impl(int32_t n, int64_t nnz, const int32_t *rowptr, const int3
         rc = setup_sell(A, s, 0);
         if (rc) {
             if (getenv("SPK_FORCE_KERNEL")) return rc;
-            free_sell(A);  // the layout did not fit: take the next family
-            choose_kernel(A, false);
+            free_sell(A);  // the layout did not fit: take the next family that needs no copy
+            choose_kernel(A, false, false);
             if (A->kernel != SPK_KERNEL_STREAM) A->R = 256;
             apply_partition(A);
             if (A->kernel == SPK_KERNEL_MERGE) {
@@ -1260,7 +1269,7 @@ static int set_kernel(spk_mat *A, int kernel, int32_t param, hipStream_t s)
         if (rc == SPK_OK) rc = hipStreamSynchronize(s) == hipSuccess ? SPK_OK : SPK_EHIP;
         if (rc) {
             free_sell(A);
-            choose_kernel(A, false);
+            choose_kernel(A, false, false);
             if (A->kernel == SPK_KERNEL_MERGE) {
                 const int r2 = setup_merge(A, s);
                 if (r2) return r2;

@@ -170,3 +170,54 @@ works(M, A)
 spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
 assert M.info.device_bytes == binned
 """)
+
+
+def test_no_room_for_any_copy(child):
+    """Without room for its layout a matrix takes a family that needs none, at
+    creation and where a refused request took the layout down; the merge path
+    does without half of its tiles."""
+    child("""
+n = 1 << 19
+A = _scattered(n, [8] * (n - 1) + [40], 3)
+csr = to_dev(A.rowptr), to_dev(A.col), to_dev(A.val)
+short(8 * A.nnz, mask=0b1110)  # not the CSR arrays; the binned copy, the slices, SELL
+M = spk.mat_create_csr(*csr)
+failed()
+assert spk.KERNEL_NAMES[M.info.kernel] in ("stream", "vector", "merge"), spk.KERNEL_NAMES[M.info.kernel]
+works(M, A)
+M.close()
+
+n = 3000
+A = _scattered(n, [3] * n, 4)
+M = mat_on_gpu(spk, A)
+spk.mat_set_kernel(M, spk.KERNEL_SELL, 16)
+short(8 * A.nnz)  # the layout that would come back
+try:
+    spk.mat_set_kernel(M, spk.KERNEL_SELL, spk.SELL_SHARED)
+    raise SystemExit("shared")
+except spk.SpkError as e:
+    assert e.status == spk.EINVAL, e
+failed()
+M.info = spk.mat_get_info(M)
+assert spk.KERNEL_NAMES[M.info.kernel] in ("stream", "vector", "merge")
+works(M, A)
+spk.mat_set_kernel(M, spk.KERNEL_VECTOR, 4)
+tiles = (A.n + A.nnz + 2047) // 2048
+for mask in (1, 2, 4, 8):
+    N = mat_on_gpu(spk, A)
+    spk.mat_set_kernel(N, spk.KERNEL_VECTOR, 4)
+    before = N.info.device_bytes
+    short(4 * tiles, 8 * tiles, mask=mask)
+    try:
+        spk.mat_set_kernel(N, spk.KERNEL_MERGE, 0)
+        raise SystemExit("found room")
+    except spk.SpkError as e:
+        assert e.status == spk.ENOMEM, e
+    failed()
+    N.info = spk.mat_get_info(N)
+    assert spk.KERNEL_NAMES[N.info.kernel] == "vector" and N.info.device_bytes == before
+    works(N, A)
+    spk.mat_set_kernel(N, spk.KERNEL_MERGE, 0)
+    works(N, A)
+    N.close()
+""")
