@@ -129,7 +129,7 @@ static int fp64_blocks(const spk_mat *A)
     return A->kernel == SPK_KERNEL_SELL && A->sell_cw && A->ntiles <= kPcgBlocksSell ? A->ntiles : A->nblk;
 }
 
-static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
+static int make_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
 {
     Workspace *w = A->ws;
     if (!w) {
@@ -223,6 +223,15 @@ static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
     }
     *out = w;
     return SPK_OK;
+}
+
+// The handle's workspace; whole, or none: one that lacks an array would pass
+// for ready at the next call.
+static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
+{
+    const int rc = make_workspace(A, mixed, out, s);
+    if (rc != SPK_OK) free_workspace(A);
+    return rc;
 }
 
 // Every pointer of the descriptor is owned by the workspace (b is copied in),
@@ -665,9 +674,9 @@ static int sr_start(spk_mat *A, Workspace *w, const SrDesc &a, int b, hipStream_
 static int solve_sr(spk_mat *A, Workspace *w, const spk_ksp_opts &o, int hist_len, hipStream_t s,
                     SolveOut *out)
 {
-    if (!w->s) {
-        SPK_HIP(hipMalloc((void **)&w->s, sizeof(double) * std::max(A->n, 1)));
-        SPK_HIP(hipMalloc((void **)&w->srp, sizeof(double) * 6 * std::max(A->nblk, 1)));
+    if (!w->sc) {  // the last of the three
+        if (!w->s) SPK_HIP(hipMalloc((void **)&w->s, sizeof(double) * std::max(A->n, 1)));
+        if (!w->srp) SPK_HIP(hipMalloc((void **)&w->srp, sizeof(double) * 6 * std::max(A->nblk, 1)));
         SPK_HIP(hipMalloc(&w->sc, sizeof(SrScal)));
         w->bytes += 8 * (int64_t)std::max(A->n, 1) + 48 * (int64_t)std::max(A->nblk, 1) + sizeof(SrScal);
     }
@@ -970,9 +979,11 @@ int spk_ksp_solve(spk_mat *A, const double *b, double *x, const spk_ksp_opts *op
         if (w->gmix) { hipGraphExecDestroy(w->gmix); w->gmix = nullptr; }
         if (w->gsr) { hipGraphExecDestroy(w->gsr); w->gsr = nullptr; }
         if (w->hist) hipFree(w->hist);
-        w->hist = nullptr;
+        w->bytes -= 8 * (int64_t)w->hist_cap;
+        w->hist = w->hdesc.hist = nullptr;
+        w->hist_cap = 0;
         SPK_HIP(hipMalloc(&w->hist, sizeof(double) * o.hist_len));
-        w->bytes += 8 * (int64_t)(o.hist_len - w->hist_cap);
+        w->bytes += 8 * (int64_t)o.hist_len;
         w->hist_cap = o.hist_len;
         w->hdesc.hist = w->hist;
     }

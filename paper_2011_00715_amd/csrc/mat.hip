@@ -523,8 +523,9 @@ int ensure_f32(spk_mat *A, hipStream_t s)
         if (rc) return rc;
     }
     if (A->val32 || A->n == 0) return SPK_OK;
+    // val32 says that both are there
+    if (!A->dinv32) SPK_HIP(hipMalloc(&A->dinv32, sizeof(float) * A->n));
     SPK_HIP(hipMalloc(&A->val32, sizeof(float) * (A->nnz > 0 ? A->nnz : 1)));
-    SPK_HIP(hipMalloc(&A->dinv32, sizeof(float) * A->n));
     A->bytes += 4 * A->nnz + 4 * (int64_t)A->n;
     if (A->nnz > 0)
         hipLaunchKernelGGL(k_to_f32, dim3(grid_for(A->nnz)), dim3(kBlock), 0, s, A->nnz, A->val,

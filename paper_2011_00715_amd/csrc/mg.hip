@@ -613,26 +613,29 @@ static int get_solve_ws(spk_mg *M, int hist_len)
 {
     const int n = M->lev[0].n;
     if (!M->r) {
+        // what the vectors' allocation makes ready comes first
+        if (!M->pst) SPK_HIP(hipHostMalloc((void **)&M->pst, sizeof(SysState), hipHostMallocDefault));
+        if (!M->pstatus) SPK_HIP(hipHostMalloc((void **)&M->pstatus, sizeof(int32_t) * 8, hipHostMallocDefault));
+        for (auto &e : M->ev)
+            if (!e) SPK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         const int64_t nb = (8 * (int64_t)n + 255) & ~255ll;
         SPK_TRY(mg_alloc(M, &M->ws, 7 * nb + 32 * (int64_t)kMgMaxPart + (int64_t)sizeof(SysState)));
         double **vec[7] = {&M->r, &M->z, &M->p, &M->q, &M->x, &M->b, &M->tmp64};
         for (int i = 0; i < 7; ++i) *vec[i] = (double *)(M->ws + i * nb);
         M->part = (double *)(M->ws + 7 * nb);
         M->st = (SysState *)(M->part + 4 * (int64_t)kMgMaxPart);
-        SPK_HIP(hipHostMalloc((void **)&M->pst, sizeof(SysState), hipHostMallocDefault));
-        SPK_HIP(hipHostMalloc((void **)&M->pstatus, sizeof(int32_t) * 8, hipHostMallocDefault));
-        for (auto &e : M->ev) SPK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     const int need = std::max(hist_len, 1);
     if (need > M->hist_cap) {
-        hipFree(M->hist);
-        M->hist = nullptr;
-        SPK_TRY(mg_alloc(M, &M->hist, need));
-        M->hist_cap = need;
         if (M->g) {  // the graph holds the old history pointer
             hipGraphExecDestroy(M->g);
             M->g = nullptr;
         }
+        hipFree(M->hist);
+        M->hist = nullptr;
+        M->hist_cap = 0;
+        SPK_TRY(mg_alloc(M, &M->hist, need));
+        M->hist_cap = need;
     }
     return SPK_OK;
 }

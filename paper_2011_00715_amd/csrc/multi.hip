@@ -106,7 +106,7 @@ static void with_width(const spk_mat *A, F &&f)
     else f(std::integral_constant<int, 9>{});
 }
 
-static int get_multi(spk_mat *A, int K, MultiWs **out)
+static int make_multi(spk_mat *A, int K, MultiWs **out)
 {
     MultiWs *w = A->mws;
     if (w && (w->K != K || w->nblk != multi_nblk(A))) {
@@ -131,6 +131,14 @@ static int get_multi(spk_mat *A, int K, MultiWs **out)
     }
     *out = w;
     return SPK_OK;
+}
+
+// Whole, or none.
+static int get_multi(spk_mat *A, int K, MultiWs **out)
+{
+    const int rc = make_multi(A, K, out);
+    if (rc != SPK_OK) free_multi(A);
+    return rc;
 }
 
 static MultiDesc solve_desc(const spk_mat *A, MultiWs *w)

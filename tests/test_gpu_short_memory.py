@@ -221,3 +221,56 @@ for mask in (1, 2, 4, 8):
     works(N, A)
     N.close()
 """)
+
+
+@pytest.mark.parametrize("what", ["solve", "mixed", "single", "multi", "mg", "history"])
+def test_no_room_for_a_workspace(child, what):
+    """A solve that gets only some of its arrays is refused, and the next one
+    has them all: each of the first requests fails once in its turn."""
+    child(f"what = {what!r}" + """
+A = spkgen.laplace3d7(24)
+b = to_dev(spkgen.rhs_uniform(A.n, 0))
+B = to_dev(np.stack([spkgen.rhs_uniform(A.n, s) for s in range(4)], 1))
+X = torch.zeros_like(B) if what == "multi" else torch.zeros_like(b)
+
+def solve(M, G, hist=None):
+    X.zero_()
+    if what == "multi":
+        spk.ksp_solve_multi(M, B, X)
+    elif what == "mg":
+        spk.ksp_solve_mg(G, b, X, hist=hist)
+    else:
+        spk.ksp_solve(M, b, X, spk.ksp_opts(precision=spk.PREC_MIXED if what == "mixed" else spk.PREC_FP64,
+                                            single_reduction=int(what == "single")), hist=hist)
+    return X.clone()
+
+def start():
+    M = mat_on_gpu(spk, A)
+    return M, spk.mg_create(M, (24, 24, 24)) if what == "mg" else None
+
+M, G = start()
+want = solve(M, G)
+del M, G
+refused = 0
+for i in range(30):
+    M, G = start()
+    if what == "history":  # a longer one than the handle has
+        solve(M, G, np.zeros(8))
+    short(1, mask=1 << i)
+    try:
+        got = solve(M, G, np.zeros(64) if what == "history" else None)
+        short(1, mask=0)
+        assert torch.equal(got, want)
+        break  # that many requests are not made
+    except spk.SpkError as e:
+        assert e.status == spk.ENOMEM, e
+        refused += 1
+    failed()
+    for again in range(2):
+        hist = np.full(8, np.nan)
+        assert torch.equal(solve(M, G, hist if what in ("history", "mg") else None), want), (i, again)
+        assert what not in ("history", "mg") or np.isfinite(hist[0])
+    if G: G.close()
+    M.close()
+assert refused >= (1 if what in ("history", "mg") else 3) and i < 29
+""")
