@@ -15,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libspk.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["mat.hip", "ksp.hip", "server.hip", "multi.hip", "mg.hip", "xslice.hip", "resident.hip"]
+SOURCES = ["cheb.hip", "cheb32.hip", "iter64.hip", "iter32.hip", "ksp.hip", "mat.hip", "server.hip", "multi.hip",
+           "mg.hip", "xslice.hip", "resident.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

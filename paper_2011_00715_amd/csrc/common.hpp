@@ -116,6 +116,12 @@ int hip_fail(hipError_t e, const char *what, const char *file, int line);
         if (e_ != hipSuccess) return ::spk::hip_fail(e_, #call, __FILE__, __LINE__); \
     } while (0)
 
+#define SPK_TRY(x)                  \
+    do {                            \
+        const int rc_ = (x);        \
+        if (rc_ != SPK_OK) return rc_; \
+    } while (0)
+
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // Logical blocks for a system of `ntiles` tiles, at most `maxb`: a multiple of

@@ -7,10 +7,8 @@
 
 #include <algorithm>
 
-#include "cheb.hpp"
-#include "krylov.hpp"
+#include "iterate.hpp"
 #include "sr.hpp"
-#include "runtime.hpp"
 
 namespace spk {
 
@@ -67,12 +65,6 @@ static int dalloc(T **p, int64_t count, Workspace *w)
     w->bytes += (int64_t)b;
     return SPK_OK;
 }
-
-#define SPK_TRY(x)                  \
-    do {                            \
-        const int rc_ = (x);        \
-        if (rc_ != SPK_OK) return rc_; \
-    } while (0)
 
 // The PCG product runs one wavefront per slice (plus the one-block fold of
 // its partials, ~4.6 us) instead of the persistent grid when each lane of
@@ -227,26 +219,11 @@ static int make_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s
 
 // The handle's workspace; whole, or none: one that lacks an array would pass
 // for ready at the next call.
-static int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
+int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s)
 {
     const int rc = make_workspace(A, mixed, out, s);
     if (rc != SPK_OK) free_workspace(A);
     return rc;
-}
-
-// Every pointer of the descriptor is owned by the workspace (b is copied in),
-// so the descriptor travels by value in the kernel arguments and captured
-// graphs stay valid from one solve to the next.  A profiled solve times the
-// product kernel alone, so it runs the three-kernel iteration: its
-// descriptor has no second p buffer (the results are the same bits).
-static bool use_fused(const Workspace *w, bool mixed) { return (mixed ? w->fused32 : w->fused64) && !w->prof; }
-static One batch_of(Workspace *w, bool mixed)
-{
-    One b{w->hdesc};
-    if (!mixed) b.d.nblk = w->nblk64;
-    if (!use_fused(w, false)) b.d.p2 = nullptr;
-    if (!use_fused(w, true)) b.d.p2_32 = nullptr;
-    return b;
 }
 
 // r = b - A x for the handle's kernel family (mixed: a mixed-precision
@@ -277,138 +254,18 @@ static int launch_resid(spk_mat *A, Workspace *w, bool mixed, int purpose, bool 
     return SPK_OK;
 }
 
-// The next event pair of a profiled solve (created on first use).
-static int prof_pair(Workspace *w, hipEvent_t *e0, hipEvent_t *e1)
-{
-    const size_t k = 2 * (size_t)w->pev_used;
-    while (w->pev.size() < k + 2) {
-        hipEvent_t e = nullptr;
-        SPK_HIP(hipEventCreate(&e));
-        w->pev.push_back(e);
-    }
-    if (w->alive.size() < (size_t)w->pev_used + 1) w->alive.resize(w->pev_used + 1);
-    w->alive[w->pev_used] = 1;
-    *e0 = w->pev[k];
-    *e1 = w->pev[k + 1];
-    ++w->pev_used;
-    return SPK_OK;
-}
-
-template <class V>
-static int enqueue_iteration(spk_mat *A, Workspace *w, hipStream_t s)
-{
-    const One b = batch_of(w, Vecs<V>::mixed);
-    const dim3 g(b.d.nblk), t(kBlock), one(1);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (w->prof) {
-        SPK_TRY(prof_pair(w, &e0, &e1));
-        SPK_HIP(hipEventRecord(e0, s));
-    }
-    if (A->kernel == SPK_KERNEL_STREAM) {
-        hipLaunchKernelGGL((k_pcg_spmv_stream<V, One>), g, t, 0, s, b);
-    } else if (A->kernel == SPK_KERNEL_SELL && w->wpart) {
-        const dim3 gw(w->nwpart);
-        with_sell(A, [&](auto ci, auto uc) {
-            using CI = decltype(ci);
-            constexpr int U = decltype(uc)::value;
-            // (a list for the whole matrix streams too little for the rule)
-            if constexpr (!std::is_same<CI, Stencil>::value)
-                hipLaunchKernelGGL((k_pcg_spmv_sell_wide<V, CI, U>), gw, t, 0, s, b, w->wpart);
-        });
-        // the pair times the slice kernel, which moves the bytes; the fold
-        // of its per-block partials (one block, a few microseconds) is outside
-        if (e1) {
-            SPK_HIP(hipEventRecord(e1, s));
-            e1 = nullptr;
-        }
-        hipLaunchKernelGGL((k_fin_pq<V>), one, dim3(kFinPqThreads), 0, s, b, (const double *)w->wpart, w->nwpart);
-    } else if (A->kernel == SPK_KERNEL_SELL) {
-        with_sell(A, [&](auto ci, auto uc) {
-            using CI = decltype(ci);
-            constexpr int U = decltype(uc)::value;
-            hipLaunchKernelGGL((k_pcg_spmv_sell<V, CI, U, One>), g, t, 0, s, b);
-        });
-    } else {
-        const V *val = std::is_same<V, double>::value ? (const V *)A->val : (const V *)A->val32;
-        V *p = std::is_same<V, double>::value ? (V *)w->p : (V *)w->p32;
-        V *q = std::is_same<V, double>::value ? (V *)w->q : (V *)w->q32;
-        SPK_TRY(launch_spmv<V>(A, val, p, q, s, w->st, Vecs<V>::gate));
-        hipLaunchKernelGGL((k_pcg_pq<V, One>), g, t, 0, s, b);
-    }
-    if (e1) SPK_HIP(hipEventRecord(e1, s));
-    hipLaunchKernelGGL((k_pcg_update<V, One>), g, t, 0, s, b);
-    hipLaunchKernelGGL((k_pcg_px<V, One>), g, t, 0, s, b);
-    SPK_HIP(hipGetLastError());
-    return SPK_OK;
-}
-
-// B of the fused iteration.
-template <class V>
-static void launch_update(spk_mat *A, Workspace *w, hipStream_t s)
-{
-    const One b = batch_of(w, Vecs<V>::mixed);
-    const dim3 g(b.d.nblk), t(kBlock);
-    if (one_diag(A)) hipLaunchKernelGGL((k_pcg_update<V, One, true>), g, t, 0, s, b);
-    else hipLaunchKernelGGL((k_pcg_update<V, One>), g, t, 0, s, b);
-}
-
-// F of the fused iteration (the C part, then the next product).
-template <class V, bool kStart>
-static void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
-{
-    const One b = batch_of(w, Vecs<V>::mixed);
-    const dim3 g(b.d.nblk), t(kBlock);
-    with_sell(A, [&](auto ci, auto uc) {
-        using CI = decltype(ci);
-        // a start runs once a sequence: one size of round will do for it (the
-        // list for a whole matrix has to fit its round)
-        constexpr int U = kStart && !std::is_same<CI, Stencil>::value ? 4 : decltype(uc)::value;
-        hipLaunchKernelGGL((k_pcg_fused_sell<V, CI, U, kStart, One>), g, t, 0, s, b);
-    });
-}
-
 // One batch of K iterations (mixed: preceded by the refinement kernels).
-// Fused: a start kernel (a no-op unless a setup finalizer just ran) and K
-// times B, F; F of the batch's last iteration holds its decision, which the
-// next batch's refinement kernels (gated on the phase it sets) follow.
+// Fused: F of the batch's last iteration holds its decision, which the next
+// batch's refinement kernels (gated on the phase it sets) follow.
 static int enqueue_batch(spk_mat *A, Workspace *w, bool mixed, int K, hipStream_t s)
 {
-    if (use_fused(w, mixed)) {
-        const One b = batch_of(w, mixed);
-        const dim3 g(b.d.nblk), t(kBlock);
-        if (mixed) {
-            hipLaunchKernelGGL(k_update_x<One>, g, t, 0, s, b);
-            SPK_TRY(launch_resid(A, w, true, kResOuter, true, s));
-            hipLaunchKernelGGL(k_setup32<One>, g, t, 0, s, b);
-            hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), t, 0, s, b);
-            launch_fused<float, true>(A, w, s);
-            for (int k = 0; k < K; ++k) {
-                launch_update<float>(A, w, s);
-                launch_fused<float, false>(A, w, s);
-            }
-        } else {
-            launch_fused<double, true>(A, w, s);
-            for (int k = 0; k < K; ++k) {
-                launch_update<double>(A, w, s);
-                launch_fused<double, false>(A, w, s);
-            }
-        }
-        SPK_HIP(hipGetLastError());
-        return SPK_OK;
-    }
-    if (mixed) {
-        const One b = batch_of(w, true);
-        hipLaunchKernelGGL(k_update_x<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
-        SPK_TRY(launch_resid(A, w, true, kResOuter, true, s));
-        hipLaunchKernelGGL(k_setup32<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
-        hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), dim3(kBlock), 0, s, b);
-        hipLaunchKernelGGL((k_pcg_p_continue<float, One>), dim3(A->nblk), dim3(kBlock), 0, s, b);
-        for (int k = 0; k < K; ++k) SPK_TRY(enqueue_iteration<float>(A, w, s));
-    } else {
-        for (int k = 0; k < K; ++k) SPK_TRY(enqueue_iteration<double>(A, w, s));
-    }
-    SPK_HIP(hipGetLastError());
-    return SPK_OK;
+    if (!mixed) return launch_iterations<double>(A, w, K, s);
+    const One b = batch_of(w, true);
+    hipLaunchKernelGGL(k_update_x<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
+    SPK_TRY(launch_resid(A, w, true, kResOuter, true, s));
+    hipLaunchKernelGGL(k_setup32<One>, dim3(A->nblk), dim3(kBlock), 0, s, b);
+    hipLaunchKernelGGL(k_fin_setup32<One>, dim3(1), dim3(kBlock), 0, s, b);
+    return launch_iterations<float>(A, w, K, s);
 }
 
 static int get_graph(spk_mat *A, Workspace *w, bool mixed, int K, hipGraphExec_t *out)
@@ -771,149 +628,11 @@ static void fill_zero(double *p, int64_t n, hipStream_t s)
     hipLaunchKernelGGL(k_zero64, dim3((int)g), dim3(kBlock), 0, s, n, p);
 }
 
-static int grid_n(int64_t n)
-{
-    int64_t g = (n + kBlock - 1) / kBlock;
-    if (g > kMaxBlocksSingle) g = kMaxBlocksSingle;
-    return (int)(g < 1 ? 1 : g);
-}
-
-// One Chebyshev step: fused SpMV + update for the SELL and stream families,
-// SpMV into tmp then the update pass for the others (V = double, or float
-// with the handle's FP32 values).
-template <class V>
-int cheb_step(spk_mat *A, const ChebStep<V> &c, V *tmp, hipStream_t s, int *np)
-{
-    constexpr bool f64 = std::is_same<V, double>::value;
-    const dim3 g(A->nblk), t(kBlock);
-    if ((c.b || c.b64) && !cheb_zero_fused(A)) {
-        set_error("internal: Chebyshev start from zero without a SELL layout");
-        return SPK_EINVAL;
-    }
-    if (A->kernel == SPK_KERNEL_SELL) {
-        const SellView sv{A->sell_ptr, A->sell_col, A->sell_len, A->sell_plain, A->sell_len16, A->sell_perm, A->sell_mask};
-        // up to one wavefront per slice (no partial sums to keep per block)
-        const dim3 gs(std::max(1, std::min(ceil_div(ceil_div(A->n, kSell), kBlock / kWave), 16384)));
-        const int n = A->n;
-        const V *sval = f64 ? (const V *)A->sell_val : (const V *)A->sell_val32;
-        if (!sval) { set_error("internal: no SELL values of this precision"); return SPK_EINVAL; }
-        auto from_zero = [&](auto *b) {
-            using B = std::remove_const_t<std::remove_pointer_t<decltype(b)>>;
-            with_sell(A, [&](auto ci, auto uc) {
-                using CI = decltype(ci);
-                constexpr int U = decltype(uc)::value;
-                hipLaunchKernelGGL((k_cheb_sell_zero<V, B, CI, U>), gs, t, 0, s, n, sv, sval, c, b);
-            });
-        };
-        if (c.b64) from_zero(c.b64);
-        else if (c.b) from_zero(c.b);
-        else
-            with_sell(A, [&](auto ci, auto uc) {
-                using CI = decltype(ci);
-                constexpr int U = decltype(uc)::value;
-                hipLaunchKernelGGL((k_cheb_sell<V, CI, U>), gs, t, 0, s, n, sv, sval, c);
-            });
-        if (np) *np = (int)gs.x;
-    } else if (A->kernel == SPK_KERNEL_STREAM) {
-        const V *val = f64 ? (const V *)A->val : (const V *)A->val32;
-        hipLaunchKernelGGL((k_cheb_stream<V>), g, t, 0, s, A->n, A->R, A->ntiles, A->nblk, A->rowptr, A->col, val,
-                           c);
-        if (np) *np = A->nblk;
-    } else {
-        const V *val = f64 ? (const V *)A->val : (const V *)A->val32;
-        SPK_TRY(launch_spmv<V>(A, val, c.dk, tmp, s, c.gate, c.gate ? kGateInner64 : kGateNone));
-        hipLaunchKernelGGL((k_cheb_update<V>), dim3(grid_n(A->n)), t, 0, s, A->n, (const V *)tmp, c);
-        if (np) *np = grid_n(A->n);
-    }
-    SPK_HIP(hipGetLastError());
-    return SPK_OK;
-}
-
-template int cheb_step<double>(spk_mat *, const ChebStep<double> &, double *, hipStream_t, int *);
-template int cheb_step<float>(spk_mat *, const ChebStep<float> &, float *, hipStream_t, int *);
-
 }  // namespace spk
 
 using namespace spk;
 
 extern "C" {
-
-int spk_pc_chebyshev(const spk_mat *Ac, const double *b, double *x, double *r_out, int32_t steps,
-                     double emin, double emax, int32_t x0_nonzero, void *stream)
-{
-    spk_mat *A = const_cast<spk_mat *>(Ac);
-    if (!A) { set_error("A is NULL"); return SPK_EINVAL; }
-    const int64_t n = A->n;
-    if (n > 0 && (!b || !x)) { set_error("NULL b or x"); return SPK_EINVAL; }
-    if (steps < 0) { set_error("steps = %d < 0", steps); return SPK_EINVAL; }
-    auto overlap = [n](const double *a, const double *c) { return a && c && a < c + n && c < a + n; };
-    if (n > 0 && (overlap(b, x) || overlap(r_out, x) || overlap(r_out, b))) {
-        set_error("b, x and r_out must not overlap");
-        return SPK_EINVAL;
-    }
-    if (A->stats.zero_diag) {
-        set_error("%d rows without a nonzero diagonal", A->stats.zero_diag);
-        return SPK_EZERODIAG;
-    }
-    if (!(emax > 0.0)) emax = A->info.gershgorin;
-    if (!(emin > 0.0)) emin = emax / 10.0;
-    if (!(emin > 0.0) || !(emax > emin) || !std::isfinite(emax)) {
-        set_error("spectral interval [%g, %g]: need 0 < emin < emax", emin, emax);
-        return SPK_EINVAL;
-    }
-    if (n == 0) return SPK_OK;
-    hipStream_t s = (hipStream_t)stream;
-    A->stream = s;
-    Workspace *w = nullptr;
-    SPK_TRY(get_workspace(A, false, &w, s));
-    const double theta = 0.5 * (emax + emin), delta = 0.5 * (emax - emin), sigma = theta / delta;
-    double *r = r_out ? r_out : w->r;
-    double *dbuf[2] = {w->z, w->p};
-    double *tmp = w->q;
-    if (steps == 1 && !r_out && !x0_nonzero) {
-        hipLaunchKernelGGL((k_cheb_one<double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n, b,
-                           (const double *)A->dinv, 1.0 / theta, x);
-        SPK_HIP(hipGetLastError());
-        return SPK_OK;
-    }
-    // from zero on SELL the first step forms its own start
-    const bool zero_fused = !x0_nonzero && steps >= 1 && cheb_zero_fused(A);
-    if (!zero_fused) {
-        if (x0_nonzero) SPK_TRY(launch_spmv<double>(A, A->val, x, tmp, s, nullptr, kGateNone));
-        hipLaunchKernelGGL((k_cheb_init<double, double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n, b,
-                           x0_nonzero ? (const double *)tmp : nullptr, x, r, dbuf[0], (const double *)A->dinv,
-                           1.0 / theta, (const SysState *)nullptr, (double *)nullptr);
-        SPK_HIP(hipGetLastError());
-    }
-    if (steps == 1 && !r_out) {
-        hipLaunchKernelGGL((k_cheb_last<double>), dim3(grid_n(n)), dim3(kBlock), 0, s, (int)n,
-                           (const double *)dbuf[0], x, (const SysState *)nullptr);
-        SPK_HIP(hipGetLastError());
-        return SPK_OK;
-    }
-    double rho = 1.0 / sigma;
-    // without a residual the last step is only x += d: the pass before adds it
-    const int passes = r_out ? steps : steps - 1;
-    for (int k = 0; k < passes; ++k) {
-        const double rho_next = 1.0 / (2.0 * sigma - rho);
-        ChebStep<double> c;
-        c.dk = dbuf[k & 1];
-        c.dn = k == steps - 1 ? nullptr : dbuf[(k + 1) & 1];
-        c.r = r;
-        c.x = x;
-        c.dinv = A->dinv;
-        c.c1 = rho_next * rho;
-        c.c2 = 2.0 * rho_next / delta;
-        if (k == 0 && zero_fused) {
-            c.b = b;
-            c.inv_theta = 1.0 / theta;
-        }
-        c.close = !r_out && k == passes - 1;
-        SPK_TRY(cheb_step(A, c, tmp, s));
-        rho = rho_next;
-    }
-    return SPK_OK;
-}
 
 void spk_ksp_opts_default(spk_ksp_opts *o)
 {

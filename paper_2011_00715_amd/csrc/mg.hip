@@ -86,12 +86,6 @@ struct spk_mg {
 
 namespace spk {
 
-#define SPK_TRY(x)                     \
-    do {                               \
-        const int rc_ = (x);           \
-        if (rc_ != SPK_OK) return rc_; \
-    } while (0)
-
 enum { kPartRzMg = 0, kPartPqMg = 1, kPartRrMg = 2, kPartBbMg = 3 };
 
 // Levels up to this many rows fold the prolongation into the post-smoother's

@@ -225,6 +225,11 @@ int launch_spmv(const spk_mat *A, const V *val, const V *x, V *y, hipStream_t s,
                 const SysState *gate_st, int gate_mode);
 
 void update_info(spk_mat *A);
+// the handle's solver workspace (ksp.hip)
+int get_workspace(spk_mat *A, bool mixed, Workspace **out, hipStream_t s);
+// K iterations in FP64 (V = double) or of a mixed solve's inner CG (float)
+template <class V>
+int launch_iterations(spk_mat *A, Workspace *w, int K, hipStream_t s);
 // iterations of small FP64 solves in one launch (resident.hip)
 bool resident_fits(const spk_mat *A);
 int64_t resident_slots(const spk_mat *A);

@@ -83,3 +83,13 @@ def test_multigrid_host_validation_without_gpu(lib):
     assert spk._lib.spk_ksp_solve_mg(None, None, None, None, ctypes.byref(res), None) == spk.EINVAL
     assert spk._lib.spk_mg_apply(None, None, None, None) == spk.EINVAL
     assert spk._lib.spk_mg_destroy(None) == spk.OK
+
+
+def test_code_is_loaded_in_parts(lib):
+    """The first launch of a kernel loads all code of its source file, some
+    3 ms a megabyte: no file's code grows past 2 MB."""
+    with open(LIB, "rb") as f:
+        code = f.read()
+    at = [m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", code)]
+    sizes = [b - a for a, b in zip(at, at[1:])]
+    assert len(at) >= 8 and max(sizes) <= 2 << 20, sizes
