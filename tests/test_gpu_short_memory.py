@@ -274,3 +274,34 @@ for i in range(30):
     M.close()
 assert refused >= (1 if what in ("history", "mg") else 3) and i < 29
 """)
+
+
+def test_smoothing_in_one_pass_needs_no_memory(child):
+    """Smoothing from zero that is a single pass over the matrix allocates
+    nothing; more steps take the workspace."""
+    child("""
+A = spkgen.laplace3d7(24)
+b = to_dev(spkgen.rhs_uniform(A.n, 0))
+outs = []
+for armed in (False, True):
+    M = mat_on_gpu(spk, A)
+    if not armed:
+        spk.ksp_solve(M, b, torch.zeros_like(b))  # the workspace is there
+    x, y, z, r = (torch.full_like(b, float("nan")) for _ in range(4))
+    short(1, mask=int(armed))
+    spk.pc_chebyshev(M, b, x, 1)
+    spk.pc_chebyshev(M, b, y, 2)
+    spk.pc_chebyshev(M, b, z, 1, r_out=r)
+    assert shim.short_memory_left() == int(armed)
+    if armed:
+        try:
+            spk.pc_chebyshev(M, b, z.clone(), 3)
+            raise SystemExit("found room")
+        except spk.SpkError as e:
+            assert e.status == spk.ENOMEM, e
+    failed()
+    outs.append((x, y, z, r))
+    M.close()
+for got, want in zip(*outs):
+    assert torch.equal(got, want) and torch.isfinite(got).all()
+""")
