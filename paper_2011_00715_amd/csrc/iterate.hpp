@@ -105,6 +105,23 @@ void launch_update(spk_mat *A, Workspace *w, hipStream_t s)
     else hipLaunchKernelGGL((k_pcg_update<V, One>), g, t, 0, s, b);
 }
 
+// Pairs per round of F for a matrix whose walk takes u.  A start runs once a
+// sequence: one size will do for it (the list for a whole matrix has to fit its
+// round).  In FP32, 27 z and p in flight hold 169 registers, two waves to a SIMD;
+// two rounds, of 9 and 4 pairs, hold 122, four waves.  Mixed solves of 27-point
+// 96^3 11.1 -> 9.7 ms, 61 x 47 x 53 3.34 -> 3.02, 30^3 1.39 -> 1.36 (rounds of 7: 9.4,
+// 3.03 and 1.42; of 5: 9.7, 2.99 and 1.39).  In FP64 27 of them leave two waves
+// either way; 15 leave three, where two rounds of 4 leave five, which pays once
+// the persistent grid's waves take more than one slice each (15-point 96^3, 60
+// iterations: 3.20 -> 2.78 ms; 30^3 0.81 -> 0.84).
+template <class V, class CI, bool kStart>
+constexpr int fused_round(int u)
+{
+    if (std::is_same<CI, Stencil>::value) return u;
+    if (kStart) return 4;
+    return std::is_same<V, float>::value && std::is_same<CI, int32_t>::value && u == 13 ? 9 : u;
+}
+
 // F of the fused iteration (the C part, then the next product).
 template <class V, bool kStart>
 void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
@@ -113,9 +130,12 @@ void launch_fused(spk_mat *A, Workspace *w, hipStream_t s)
     const dim3 g(b.d.nblk), t(kBlock);
     with_sell(A, [&](auto ci, auto uc) {
         using CI = decltype(ci);
-        // a start runs once a sequence: one size of round will do for it (the
-        // list for a whole matrix has to fit its round)
-        constexpr int U = kStart && !std::is_same<CI, Stencil>::value ? 4 : decltype(uc)::value;
+        constexpr int U = fused_round<V, CI, kStart>(decltype(uc)::value);
+        if constexpr (std::is_same<V, double>::value && std::is_same<CI, int32_t>::value && U == 7)
+            if (ceil_div(A->n, kSell) > b.d.nblk * (kBlock / kWave)) {
+                hipLaunchKernelGGL((k_pcg_fused_sell<V, CI, 4, kStart, One>), g, t, 0, s, b);
+                return;
+            }
         hipLaunchKernelGGL((k_pcg_fused_sell<V, CI, U, kStart, One>), g, t, 0, s, b);
     });
 }

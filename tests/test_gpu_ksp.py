@@ -485,3 +485,25 @@ def test_pcg_one_launch_gives_up(monkeypatch, n, start, polls):
         xp, rp, _ = _solve(spk, M, b, profile=1, **kw)
         assert np.array_equal(x, xp) and (res.reason, res.iterations) == (rp.reason, rp.iterations)
     M.close()
+
+
+@pytest.mark.parametrize("half,precision,n", [(7, "fp64", 262144), (7, "fp64", 262145), (7, "fp64", 300000),
+                                              (13, "fp64", 5000), (13, "mixed", 1000), (13, "mixed", 5000),
+                                              (13, "mixed", 300000), (12, "mixed", 70001)])
+@pytest.mark.parametrize("layout", [1, 32])
+def test_fused_rounds_same_bits(half, precision, n, layout):
+    """The fused kernel walks long rows in rounds of another size than the
+    products do (2 half + 1 entries a row; in FP64 by the number of slices):
+    the bits are those of the three-kernel iteration that a profiled solve runs."""
+    spk = need_gpu()
+    A = spkgen.banded_spd(n, list(range(1, half + 1)), seed=n + half, margin=0.1)
+    M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+    spk.mat_set_kernel(M, spk.KERNEL_SELL, layout)
+    b = spkgen.rhs_uniform(n, 4)
+    kw = {"precision": spk.PREC_MIXED} if precision == "mixed" else {"maxit": 12, "rtol": 1e-30}
+    x, res, hist = _solve(spk, M, b, hist_len=200, **kw)
+    xp, rp, hp = _solve(spk, M, b, hist_len=200, profile=1, **kw)
+    assert np.array_equal(x, xp) and np.array_equal(hist, hp, equal_nan=True)
+    assert (res.reason, res.iterations, res.inner_iterations) == (rp.reason, rp.iterations, rp.inner_iterations)
+    assert res.inner_iterations > 2 if precision == "mixed" else res.iterations == 12
+    M.close()
