@@ -449,8 +449,6 @@ __device__ __forceinline__ void shared_slices(int n, int s0, int stride, const S
         const bool odd = slen & 1;
         const auto *o = lists + b / kSell;
         const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
-        // the list ascends
-        const bool in = slen > 0 && r0 + o[0] >= 0 && (int64_t)r0 + (kSell - 1) + o[slen - 1] < n;
         auto gather = [&](int off) -> Raw { return gat.at(min(max(row + off, 0), n - 1)); };
         // the odd last entry is gathered with the first round and added last
         V at = V(0);
@@ -471,6 +469,10 @@ __device__ __forceinline__ void shared_slices(int n, int s0, int stride, const S
                 c[2 * u + 1] = o[2 * p + 1];
                 a[u] = sell_ld<NT>(vp + (size_t)p * kSell);
             }
+            // the list ascends; asked of the round's own entries, so that they and
+            // the values are on their way before the first is waited for
+            const int last = p0 == 0 && odd ? ot : c[2 * UP - 1];
+            const bool in = r0 + c[0] >= 0 && (int64_t)r0 + (kSell - 1) + last < n;
             Raw xv[2 * UP];
             if (in) {
 #pragma unroll
