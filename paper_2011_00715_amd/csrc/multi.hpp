@@ -115,8 +115,9 @@ __device__ __forceinline__ void sell_row_multi(const SellView &sv, const double 
     using VP = typename Pair2<double>::type;
     const CP *__restrict__ cp = reinterpret_cast<const CP *>(reinterpret_cast<const CI *>(sv.col) + b) + lane;
     const int32_t first = UNI ? 0 : __builtin_amdgcn_readfirstlane(b) >> 6;  // the slice's first list element
-    const int32_t *__restrict__ ou = reinterpret_cast<const int32_t *>(sv.col) + first;
-    const double *__restrict__ uv = val + first;
+    // lists by scalar loads, whatever the caller's stores may alias
+    const auto *ou = as_constant(reinterpret_cast<const int32_t *>(sv.col)) + first;
+    const auto *uv = as_constant(val) + first;
     const VP *__restrict__ vp = reinterpret_cast<const VP *>(val + b) + lane;
     auto values = [&](int p) -> VP {
         if constexpr (UNI) {
