@@ -240,8 +240,13 @@ struct Mul {
 // chunk per block; k_dot_fin sums them in a fixed order.  A lane's next
 // kDotAhead elements are loaded before the first is added: a chunk is a few
 // steps long, and one load a step waited out the memory's latency each time
-// (1.9 M elements, cached: 8.7 -> 7.2 to 8.0 us).
+// (1.9 M elements, cached: 8.7 -> 7.2 to 8.0 us).  Two dots gain from that at
+// every size (2^24: 87.4 us with one element ahead, 77.9 with four); a single
+// one of longer chunks loses by it (nrm2 of 2^23 15.1 against 16.4, x.y of 2^25
+// 91.7 against 95.2).
 constexpr int kDotAhead = 4;
+constexpr int kDotAheadMax = 1 << 22;  // elements of a single dot, exclusive
+template <int kAhead>
 __global__ __launch_bounds__(kBlock) void k_dot(int n, const double *__restrict__ x,
                                                 const double *__restrict__ y,
                                                 const double *__restrict__ w,
@@ -254,20 +259,20 @@ __global__ __launch_bounds__(kBlock) void k_dot(int n, const double *__restrict_
     const int rb = (int)min((int64_t)n, j * chunk);
     const int re = (int)min((int64_t)n, (j + 1) * chunk);
     double a = 0.0, b = 0.0;
-    for (int64_t i0 = rb + (int)threadIdx.x; i0 < re; i0 += kDotAhead * kBlock) {
-        double xv[kDotAhead], yv[kDotAhead], wv[kDotAhead];
+    for (int64_t i0 = rb + (int)threadIdx.x; i0 < re; i0 += kAhead * kBlock) {
+        double xv[kAhead], yv[kAhead], wv[kAhead];
 #pragma unroll
-        for (int u = 0; u < kDotAhead; ++u) {
+        for (int u = 0; u < kAhead; ++u) {
             const int64_t i = min(i0 + u * kBlock, (int64_t)re - 1);  // past the end: the last one, unused
             xv[u] = x[i];
             yv[u] = y[i];
         }
         if (w) {
 #pragma unroll
-            for (int u = 0; u < kDotAhead; ++u) wv[u] = w[min(i0 + u * kBlock, (int64_t)re - 1)];
+            for (int u = 0; u < kAhead; ++u) wv[u] = w[min(i0 + u * kBlock, (int64_t)re - 1)];
         }
 #pragma unroll
-        for (int u = 0; u < kDotAhead; ++u) {
+        for (int u = 0; u < kAhead; ++u) {
             if (i0 + u * kBlock >= re) break;
             a = fma(xv[u], yv[u], a);
             if (w) b = fma(xv[u], wv[u], b);
@@ -1424,8 +1429,8 @@ static int dot_enqueue(int32_t n, const double *x, const double *y, const double
 {
     int grid = grid_for(n > 0 ? n : 1);
     if (grid >= kXcd) grid -= grid % kXcd;
-    hipLaunchKernelGGL(k_dot, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, n, x,
-                       mode == 2 ? x : y, w, part);
+    auto dot = w || n < kDotAheadMax ? k_dot<kDotAhead> : k_dot<1>;
+    hipLaunchKernelGGL(dot, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, n, x, mode == 2 ? x : y, w, part);
     hipLaunchKernelGGL(k_dot_fin, dim3(1), dim3(kBlock), 0, (hipStream_t)stream, grid,
                        w ? 1 : 0, mode, part, result);
     SPK_HIP(hipGetLastError());

@@ -673,3 +673,25 @@ def test_vector_kernels_pairs(n, shift):
     assert res[0].item() == float(np.dot(xh, want))
     spk.vec_dot2(x, y, x, res)
     assert res.tolist() == [float(np.dot(xh, want)), float(np.dot(xh, xh))]
+
+
+@pytest.mark.parametrize("n", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 23) + 5])
+def test_dot_alone_and_with_another(n):
+    """A single dot of a long vector loads one element ahead, two dots four:
+    the lanes' sums and so the bits are the same."""
+    spk = need_gpu()
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    x, y, w = (torch.randn(n, generator=g, device="cuda", dtype=torch.float64) for _ in range(3))
+    one, two, norm = (torch.zeros(k, dtype=torch.float64, device="cuda") for k in (1, 2, 1))
+    spk.vec_dot(x, y, one)
+    spk.vec_dot2(x, y, w, two)
+    assert one[0].item() == two[0].item()
+    spk.vec_dot(x, x, one)
+    spk.vec_nrm2(x, norm)
+    assert norm[0].item() == np.sqrt(one[0].item())
+    xi, yi = (v.mul(4).round() for v in (x, y))
+    spk.vec_dot(xi, yi, one)
+    assert one[0].item() == (xi.to(torch.int64) * yi.to(torch.int64)).sum().item()
