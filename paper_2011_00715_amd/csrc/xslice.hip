@@ -145,20 +145,31 @@ int ensure_sliced_f32(spk_mat *A, hipStream_t s)
         A->bn_bytes += 4 * (A->nnz + 2);
         SPK_HIP(hipGetLastError());
     }
-    if (!A->xs_ptr || A->xs_val32 || A->nnz == 0) return SPK_OK;
-    SPK_HIP(hipMalloc(&A->xs_val32, sizeof(float) * (size_t)A->nnz));
-    hipLaunchKernelGGL(k_xs_f32, dim3(grid_rows(A->nnz)), dim3(kBlock), 0, s, A->nnz, (const double *)A->xs_val,
-                       A->xs_val32);
+    if (!A->xs_ptr || A->xs_val32) return SPK_OK;
+    SPK_HIP(hipMalloc(&A->xs_val32, sizeof(float) * (size_t)std::max<int64_t>(A->nnz, 1)));
+    if (A->nnz > 0)
+        hipLaunchKernelGGL(k_xs_f32, dim3(grid_rows(A->nnz)), dim3(kBlock), 0, s, A->nnz, (const double *)A->xs_val,
+                           A->xs_val32);
     A->bytes += 4 * A->nnz;
     A->xs_bytes += 4 * A->nnz;
     SPK_HIP(hipGetLastError());
     return SPK_OK;
 }
 
+// From this many rows on x no longer lies in the L2s beside what streams through
+// them, and the products by bin pay.  FP64 / FP32 over the slices and binned:
+// 40^3 27-point 18.3 / 17.0 and 28.4 / 21.8 us, 61 x 47 x 53 7-point 22.1 / 17.6 and
+// 26.2 / 20.7, 64^3 32.1 / 21.7 and 28.3 / 22.7, 80^3 51.9 / 34.5 and 36.8 / 29.0.  (The
+// automatic choice takes the family from 2^19 rows on.)  SPK_BINNED_ROWS in the
+// environment sets another line (testing).
+constexpr int kBinRows = 1 << 18;
+
 // The bins cover n and the merge path over the rows has int32 diagonals.
 bool binned_fits(const spk_mat *A)
 {
-    return A->n > 0 && A->n <= kBinMax * kBinCols && (int64_t)A->n + A->nnz < 0x7fff0000LL;
+    const char *e = getenv("SPK_BINNED_ROWS");
+    return A->n > 0 && A->n >= (e ? atoi(e) : kBinRows) && A->n <= kBinMax * kBinCols &&
+           (int64_t)A->n + A->nnz < 0x7fff0000LL;
 }
 
 static int setup_binned(spk_mat *A, hipStream_t s)

@@ -695,3 +695,15 @@ def test_dot_alone_and_with_another(n):
     xi, yi = (v.mul(4).round() for v in (x, y))
     spk.vec_dot(xi, yi, one)
     assert one[0].item() == (xi.to(torch.int64) * yi.to(torch.int64)).sum().item()
+
+
+@pytest.mark.parametrize("param", [0, 4, 2048])
+def test_sliced_fp32_without_entries(param):
+    """An empty matrix has an FP32 product in the sliced family too."""
+    spk = need_gpu()
+    M = mat_on_gpu(spk, spkgen.CSR(300, np.zeros(301, np.int32), np.zeros(0, np.int32), np.zeros(0)), flags=spk.MAT_MIXED)
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, param)
+    x, y = to_dev(np.ones(300, np.float32)), to_dev(np.full(300, np.nan, np.float32))
+    spk.mat_mult_f32(M, x, y)
+    assert np.array_equal(y.cpu().numpy(), np.zeros(300, np.float32))
+    M.close()
