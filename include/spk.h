@@ -102,8 +102,8 @@ enum {
                                in its own L2; a merge path over the stacked
                                slices, or lanes per slice row) into 8 partial
                                vectors that a second pass sums per row in
-                               slice order.  Up to 512 bins of 16384 columns
-                               the merge path runs over bins instead: a first
+                               slice order.  From 2^18 rows to 512 bins of 16384
+                               columns the merge path runs over bins instead: a first
                                pass forms the products with a bin's x in LDS, a
                                second sums them by row.  A copy of the matrix
                                built at selection (12 nnz + 4 (8n + 1) bytes +

@@ -6,6 +6,8 @@
 #include "xslice.hpp"
 #include "runtime.hpp"
 
+#include <cstdlib>
+
 namespace spk {
 
 static int grid_rows(int64_t n)
@@ -295,7 +297,7 @@ static int setup_slices(spk_mat *A, hipStream_t s)
     return rc;
 }
 
-// merge: rows of any lengths, binned where that fits, else and where there is
+// merge: rows of any lengths, binned where that fits (binned_fits), else and where there is
 // no room for it the merge path over the slices; the other copy is given back.
 // Power-law matrices, FP64 / FP32: 600 k rows 165 / 148 us over the slices, 139 /
 // 99 binned; 2 M rows 516 / 475 and 456 / 311; 4 M rows (133 M entries, FP64)

@@ -270,13 +270,14 @@ def test_fp32_cycle_fine_families(kernel):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-def test_solve_follows_the_fine_layout(precision):
+def test_solve_follows_the_fine_layout(precision, monkeypatch):
     """Level 0 may change its SpMV layout between solves: every solve on the
     hierarchy, the replayed ones among them, runs on the layout of the moment
     and gives the bits of a new hierarchy's first solve on it."""
     spk = need_gpu()
     import torch
 
+    monkeypatch.setenv("SPK_BINNED_ROWS", "1")
     A = spkgen.diffusion3d27_lognormal(15, seed=3)
     opts = spk.mg_opts(coarse_max=64, precision=spk.PREC_MIXED if precision == "mixed" else spk.PREC_FP64)
     b = to_dev(spkgen.rhs_uniform(A.n, 4))

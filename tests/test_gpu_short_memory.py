@@ -64,8 +64,9 @@ def child(tmp_path_factory):
     subprocess.run([cc, "-shared", "-fPIC", "-O1", os.path.join(HERE, "short_memory.c"), "-o", so], check=True)
 
     def run(code):
+        env = dict(os.environ, SPK_BINNED_ROWS="1")  # small matrices take the binned copy too
         r = subprocess.run([sys.executable, "-u", "-c", PRELUDE + code + "\nprint('done')", so, os.path.dirname(HERE),
-                            HERE], capture_output=True, text=True, timeout=100)
+                            HERE], capture_output=True, text=True, timeout=100, env=env)
         assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout + r.stderr
 
     return run

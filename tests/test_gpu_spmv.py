@@ -697,6 +697,38 @@ def test_dot_alone_and_with_another(n):
     assert one[0].item() == (xi.to(torch.int64) * yi.to(torch.int64)).sum().item()
 
 
+@pytest.mark.parametrize("case", ["one_row", "one_tile", "two_tiles", "bins_1", "bins_2", "bins_2_full", "bins_3",
+                                  "long_row", "longest_row", "empty_rows", "one_bin_used", "no_entries"])
+def test_binned_products_of_few_rows(case, monkeypatch):
+    """The binned kernels at their edges, on sizes that by themselves take the
+    merge path over the slices."""
+    monkeypatch.setenv("SPK_BINNED_ROWS", "1")
+    test_binned_products(case)
+
+
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18])
+def test_sliced_or_binned(n):
+    """The sliced family's merge path runs over bins from 2^18 rows on: exact
+    on integers, and 20 bytes an entry instead of 12 and the slices' partials."""
+    spk = need_gpu()
+    A = _scattered(n, np.full(n, 16), 5)
+    M = mat_on_gpu(spk, A, flags=spk.MAT_MIXED)
+    spk.mat_set_kernel(M, spk.KERNEL_VECTOR, 8)
+    before = M.info.device_bytes
+    spk.mat_set_kernel(M, spk.KERNEL_SLICED, 2048)
+    assert spk.KERNEL_NAMES[M.info.kernel] == "sliced" and M.info.lanes == 2048
+    extra = (M.info.device_bytes - before) / A.nnz
+    assert (24 <= extra < 25) if n >= 1 << 18 else (16 + 96 / 16 <= extra < 16 + 96 / 16 + 1), extra
+    x = np.random.default_rng(1).integers(-50, 50, n).astype(np.float64)
+    ref = oracle.spmv(A, x)
+    y, y32 = to_dev(np.full(n, np.nan)), to_dev(np.full(n, np.nan, np.float32))
+    spk.mat_mult(M, to_dev(x), y)
+    spk.mat_mult_f32(M, to_dev(x.astype(np.float32)), y32)
+    assert np.array_equal(y.cpu().numpy(), ref)
+    assert np.array_equal(y32.cpu().numpy().astype(np.float64), ref)
+    M.close()
+
+
 @pytest.mark.parametrize("param", [0, 4, 2048])
 def test_sliced_fp32_without_entries(param):
     """An empty matrix has an FP32 product in the sliced family too."""
