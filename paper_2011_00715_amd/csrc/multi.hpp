@@ -406,16 +406,17 @@ __device__ __forceinline__ void block_partials_elem(typename Flat<K>::Elem v, do
 {
     constexpr int C = Flat<K>::kCols, L = Flat<K>::kLanes;
     const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    // the butterfly's levels down to the distance L (K = 2 sums two columns over
-    // all six: with shuffles the update of 152,000 rows took 5.2 us, so 4.2)
+    // K = 2 sums two columns over all six levels: with shuffles the update of
+    // 152,000 rows took 5.2 us, with the lane swaps and rotations 4.2 (for K = 8
+    // they cost the product 86.0 -> 87.3)
+    if constexpr (L == 1) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-        double s = wave_level<16>(wave_level<32>(v[c]));
-        s = wave_level<8>(s);
-        if constexpr (L <= 4) s = wave_level<4>(s);
-        if constexpr (L <= 2) s = wave_level<2>(s);
-        if constexpr (L <= 1) s = wave_level<1>(s);
-        v[c] = s;
+        for (int c = 0; c < C; ++c) v[c] = wave_sum((double)v[c]);
+    } else {
+#pragma unroll
+        for (int off = kWave / 2; off >= L; off >>= 1)
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] += __shfl_xor(v[c], off, kWave);
     }
     __syncthreads();
     if (lane < L)
