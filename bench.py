@@ -46,8 +46,11 @@ SPMV_KERNELS = {
 
 
 def sell_ci(info):
-    """Offset type in the SELL kernels' names: int16 per lane ("short"), or
-    int32 (per lane, or shared per slice: info.lanes 0)."""
+    """Offset type in the SELL kernels' names: int16 per lane ("short"), int32
+    (per lane, or shared per slice: info.lanes 0), or "Stencil" where one list of
+    at most 27 offsets and numbers stands for the whole matrix."""
+    if info.lanes == 0 and 0 < info.stored_nnz <= 27:
+        return "Stencil"
     return "short" if info.lanes == 16 else "int"
 
 
@@ -256,7 +259,7 @@ def c2_extra_legs(spk, M, A, b, bd, xs, info, args, jacobi_s):
     # interval [g/10, g] from the Gershgorin bound; outside the timed steps
     cheb = {}
     xc = torch.zeros_like(xs)
-    mat_bytes = 12 * info.nnz + 4 * (info.n + 1)
+    mat_bytes = info.format_bytes_spmv_f64 - 16 * info.n  # the layout that the passes read
     for steps in (2, 8):
         us = []
         for _ in range(20):
@@ -266,11 +269,12 @@ def c2_extra_legs(spk, M, A, b, bd, xs, info, args, jacobi_s):
             e1.record()
             torch.cuda.synchronize()
             us.append(e0.elapsed_time(e1) * 1e3)
-        nb = 40 * info.n + (steps - 1) * (mat_bytes + 56 * info.n) + 24 * info.n
+        nb = (steps - 1) * mat_bytes + (24 if steps == 2 else 80 + 56 * (steps - 3)) * info.n
         t = float(np.median(us))
         cheb[f"steps_{steps}"] = {"us_p50": t, "bytes": nb, "gbps": nb / (t * 1e-6) / 1e9}
-    cheb["note"] = ("x0 = 0, no residual output: 40n (init) + (steps-1) x (12 nnz + 4(n+1) + 56n) "
-                    "fused SpMV+update passes + 24n (last x += d)")
+    cheb["note"] = ("x0 = 0, no residual output: steps-1 passes over the layout (format bytes); the first reads "
+                    "b and D^-1 (16n) and stores r, x, d (24n), the last reads d, x, r, D^-1 (32n) and stores x "
+                    "(8n), those between 56n; a single pass reads b and D^-1 and stores x (24n)")
 
     # single-reduction (Chronopoulos-Gear) FP64 solve of the same system
     osr = spk.ksp_opts(graph_k=args.graph_k, single_reduction=1)
@@ -621,6 +625,7 @@ def bench_all(args):
         "format_bytes": i2.format_bytes_spmv_f64,
         "cold_us_avg": cold, "cold_gbps": i2.bytes_spmv_f64 / cold / 1e3,
         "cold_frac": i2.bytes_spmv_f64 / cold / 1e3 / HBM_PEAK_GBS,
+        "cold_format_gbps": i2.format_bytes_spmv_f64 / cold / 1e3,
         "warm_us_avg": warm, "warm_gbps": i2.bytes_spmv_f64 / warm / 1e3,
         "warm_frac": i2.bytes_spmv_f64 / warm / 1e3 / HBM_PEAK_GBS,
         "traffic_warm": traffic_from_profiles(spmv_kernel_name(spk, i2) + "@c2", i2.bytes_spmv_f64),
@@ -689,6 +694,8 @@ def bench_all(args):
                       % (sell_ci(i3), ", column offsets shared per slice" if i3.lanes == 0 else ""),
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
+            "format_gbps": i3.format_bytes_spmv_f64 / prod_us / 1e3,
+            "format_frac": i3.format_bytes_spmv_f64 / prod_us / 1e3 / HBM_PEAK_GBS,
             "traffic": traffic_from_profiles("k_pcg_spmv_sell_wide<double, %s>@c3" % sell_ci(i3),
                                              i3.bytes_spmv_f64),
             "bytes_per_launch": i3.bytes_spmv_f64, "format_bytes_per_launch": i3.format_bytes_spmv_f64,
@@ -700,7 +707,8 @@ def bench_all(args):
                     "around each of the probe's product kernels in the timed steps (the one-block fold of the "
                     "partials, about 4.6 us, runs after the pair); the SELL layout (format_bytes_per_launch "
                     "with p and q) is several times the 256 MB Infinity Cache, so the bytes come from HBM; "
-                    "format bytes below the algorithmic ones are the layout's index compression",
+                    "format bytes below the algorithmic ones are the layout's index compression, and "
+                    "format_frac is the share of the peak at which they move",
         },
         "extras": extras,
     }

@@ -399,7 +399,7 @@ int spk_mat_mult_multi(const spk_mat *A, int32_t k, const double *X, double *Y, 
  * B: device n x k, read only; X: device n x k, initial guesses when
  * opts->x0_nonzero, solutions on return.  res: host spk_ksp_result[k].
  * SPK_EINVAL for a bad k, a mixed precision, NULL or overlapping B and X;
- * SPK_EZERODIAG.  The workspace (6 n k doubles) is kept on the handle for
+ * SPK_EZERODIAG.  The workspace (5 n k doubles) is kept on the handle for
  * the next call with the same k.  Returns when every column is done. */
 int spk_ksp_solve_multi(spk_mat *A, int32_t k, const double *B, double *X,
                         const spk_ksp_opts *opts, spk_ksp_result *res, void *stream);

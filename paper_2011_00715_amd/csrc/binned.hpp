@@ -15,7 +15,7 @@
 // bin; `dst`, stored by tile, puts them back in CSR order in LDS, where the
 // lanes sum them along the merge path.  28 bytes per entry are moved in FP64
 // (10 read and 8 written, then 10 read) instead of 12 and a gather: 1130 us ->
-// 512 us for the products (2.7 GB) and 408 for the sums (1.35 GB, 295 us with
+// 510 us for the products (2.7 GB) and 411 for the sums (1.35 GB, 295 us with
 // the merge path left out, which a second block on the CU hides in part), FP32
 // about 990 -> 600.
 #pragma once
@@ -28,7 +28,8 @@ namespace spk {
 // and 454 for the sums of segments half as long.  Tiles of 4096 items and 512
 // threads, four blocks a CU, took 404 us where 8192 and 1024 took 435.
 constexpr int kBinCols = 16384;   // columns of a bin
-constexpr int kBinMax = 512;      // bins at most: a segment then has 8 products or more on average
+constexpr int kBinMax = 512;      // bins at most: a segment then has 8 products at most on average
+                                  // (4096 / 512, less a tile's row ends)
 constexpr int kBinProdThreads = 1024;
 constexpr int kBinThreads = 512;
 constexpr int kBinItems = 4096;   // merge-path items of a tile

@@ -555,7 +555,7 @@ static bool merge_fits(const spk_mat *A) { return (int64_t)A->n + A->nnz < 0x7ff
 // for long, even rows; merge-path for skewed lengths).
 // The sliced layout pays when x does not fit one XCD's 4 MB L2 and rows
 // reach across it (scattered columns).  For 4M skewed power-law rows of 32
-// entries on average 0.93 ms binned and 1.14 with the merge path over the
+// entries on average 0.90 ms binned and 1.14 with the merge path over the
 // slices against 1.94 ms (merge); lanes per slice row take 1.95 ms.  Below the
 // line the product gains little (270 k rows of 32, FP64: 72 us against 65 of the
 // stream kernel; 450 k power-law rows: 104 against 116) for a copy of the matrix.

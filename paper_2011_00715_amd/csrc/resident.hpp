@@ -2,7 +2,7 @@
 //
 // A system of up to 2^18 rows stays in the caches, and its two kernels per
 // iteration then cost launches and ramp-up, not bandwidth (64 x 64 five-point:
-// 11.5 us an iteration for 0.5 MB of data).  Here the blocks stay for the whole
+// 10.4 us an iteration for 0.5 MB of data).  Here the blocks stay for the whole
 // solve: a row's x, r, p, q and D^-1 live in its lane's registers, and the
 // iteration's two reductions are the only meetings.
 //

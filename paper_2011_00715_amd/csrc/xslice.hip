@@ -301,7 +301,7 @@ static int setup_slices(spk_mat *A, hipStream_t s)
 // no room for it the merge path over the slices; the other copy is given back.
 // Power-law matrices, FP64 / FP32: 600 k rows 165 / 148 us over the slices, 139 /
 // 99 binned; 2 M rows 516 / 475 and 456 / 311; 4 M rows (133 M entries, FP64)
-// 1142 and 930.  Above kBinMax bins the segments get too short.
+// 1142 and 898.  Above kBinMax bins the segments get too short.
 int setup_sliced(spk_mat *A, int merge, hipStream_t s)
 {
     if (merge && binned_fits(A) && setup_binned(A, s) == SPK_OK) {
